@@ -106,50 +106,64 @@ __global__ void k_prep(const double* __restrict__ Y, const int32_t* __restrict__
   }
 }
 
-// FP32 pair sum.  Per pair, with R1 = s_k - r (from the grid difference)
-// and d = s_next(k) - s_k:
-//   R1 x R2 = R1 x d,  R1.R2 = |R1|^2 + R1.d,  |R2|^2 = |R1|^2 + 2 R1.d + |d|^2,
-//   v = (R1 x R2) (i1 + i2) i1 i2 / (1 + (R1.R2) i1 i2),  i_m = 1/|R_m|,
-// the closed form (|R1| + |R2|) / (|R1||R2| (|R1||R2| + R1.R2)) rewritten with
-// inverse norms.  Uniform grid: R1 stays in grid units and the result is
-// rescaled once per target (v is homogeneous of degree -1 in R).
+// FP32 pair sum.  Per pair, with R1 = s_k - r (from the grid difference),
+// d = s_next(k) - s_k, q = |d|^2 and R2 = R1 + d:
+//   R1 x R2 = R1 x d,  |R2|^2 = |R1|^2 + (2 R1.d + q),
+//   (|R1| + |R2|)^2 - q = 2 (|R1||R2| + R1.R2),
+// so the closed form (R1 x R2) (|R1| + |R2|) / (|R1||R2| (|R1||R2| + R1.R2))
+// becomes (R1 x 2d) (i1 + i2) / (s^2 - q) with i_m = 1/|R_m| and
+// s = |R1| + |R2| = |R1|^2 i1 + |R2|^2 i2: 27 ordinary and 3 transcendental
+// instructions per pair (sources are staged as 2d and q).  Uniform grid: R1
+// stays in grid units and the result is rescaled once per target (v is
+// homogeneous of degree -1 in R).
+//
+// What bounds it: VALU issue.  Ordinary FP32 and integer instructions of two
+// waves issue together (1.45 to 1.73 wave instructions per CU and cycle with
+// 8 waves per SIMD; 0.89 when an operand is a scalar register, so the source
+// data must come from vector registers), a transcendental one takes two
+// cycles alone; the loop's mix takes 23.5 cycles per pair of wave and source
+// by those rates, 25.7 measured.  Against the form with
+// 1 + (R1.R2) i1 i2 in the denominator (29.5 ordinary): 1.45 -> 1.52 Tpairs/s
+// at 1.0e5 points, the error against FP64 6.0e-7 -> 5.5e-7.  Two or four
+// targets per lane measured 3% and 13% slower (fewer waves in flight).
+struct __align__(16) BsSrc {
+  uint32_t x, y, z;  // grid coordinates of the segment's start
+  float q;           // |d|^2
+  float dx, dy, dz;  // 2 d
+  float pad;
+};
+
 template <bool kCheck, bool kUniform>
-__device__ inline void bs_tile_f32(const uint32_t* sx, const uint32_t* sy, const uint32_t* sz,
-                                   const float* dx, const float* dy, const float* dz,
-                                   const float* dq, int cnt, int t0, uint32_t xt, uint32_t yt,
+__device__ inline void bs_tile_f32(const BsSrc* src, int cnt, int t0, uint32_t xt, uint32_t yt,
                                    uint32_t zt, float iqx, float iqy, float iqz, int jj, int pj,
                                    float& ax, float& ay, float& az) {
-  // unrolled twice: 52 VGPRs, 8 waves per SIMD (four ways: 79 VGPRs and 6
-  // waves, 2.6% slower although a quarter instruction per pair shorter)
+  // unrolled twice: 8 waves per SIMD (four ways: 2% slower)
 #pragma unroll 2
   for (int s = 0; s < cnt; ++s) {
-    float r1x = (float)(int)(sx[s] - xt);
-    float r1y = (float)(int)(sy[s] - yt);
-    float r1z = (float)(int)(sz[s] - zt);
+    const BsSrc g = src[s];
+    float r1x = (float)(int)(g.x - xt);
+    float r1y = (float)(int)(g.y - yt);
+    float r1z = (float)(int)(g.z - zt);
     if (!kUniform) {
       r1x *= iqx;
       r1y *= iqy;
       r1z *= iqz;
     }
-    const float ex = dx[s], ey = dy[s], ez = dz[s];
-    const float t = r1x * ex + r1y * ey + r1z * ez;
-    const float n1 = r1x * r1x + r1y * r1y + r1z * r1z;
-    const float n2 = fmaf(2.0f, t, n1 + dq[s]);
+    const float ex = g.dx, ey = g.dy, ez = g.dz;
+    const float t = fmaf(r1x, ex, fmaf(r1y, ey, fmaf(r1z, ez, g.q)));
+    const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
+    const float n2 = n1 + t;
     const float i1 = __builtin_amdgcn_rsqf(n1);
     const float i2 = __builtin_amdgcn_rsqf(n2);
-    const float crx = r1y * ez - r1z * ey;
-    const float cry = r1z * ex - r1x * ez;
-    const float crz = r1x * ey - r1y * ex;
-    const float a = i1 * i2;
-    const float den = fmaf(n1 + t, a, 1.0f);
-    float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(den);
+    const float sum = fmaf(n1, i1, n2 * i2);
+    float f = (i1 + i2) * __builtin_amdgcn_rcpf(fmaf(sum, sum, -g.q));
     if (kCheck) {
       const int k = t0 + s;
       f = (k == jj || k == pj) ? 0.0f : f;
     }
-    ax = fmaf(f, crx, ax);
-    ay = fmaf(f, cry, ay);
-    az = fmaf(f, crz, az);
+    ax = fmaf(f, fmaf(r1y, ez, -(r1z * ey)), ax);
+    ay = fmaf(f, fmaf(r1z, ex, -(r1x * ez)), ay);
+    az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
   }
 }
 
@@ -187,8 +201,7 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
   const bool exl = valid && (copy == 0 || copy == oc);
   const int pj = exl ? prv[j] : -1;
   const int jj = exl ? j : -1;
-  __shared__ __align__(16) uint32_t sx[kTile], sy[kTile], sz[kTile];
-  __shared__ __align__(16) float dx[kTile], dy[kTile], dz[kTile], dq[kTile];
+  __shared__ BsSrc src[kTile];
   __shared__ float red[3][3][kTargets];  // sums of waves 1..3
   float ax = 0.f, ay = 0.f, az = 0.f;
   for (int t0 = kb; t0 < ke; t0 += kTile) {
@@ -205,13 +218,16 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
         ey *= iqy;
         ez *= iqz;
       }
-      sx[threadIdx.x] = ax0;
-      sy[threadIdx.x] = ay0;
-      sz[threadIdx.x] = az0;
-      dx[threadIdx.x] = ex;
-      dy[threadIdx.x] = ey;
-      dz[threadIdx.x] = ez;
-      dq[threadIdx.x] = ex * ex + ey * ey + ez * ez;
+      BsSrc g;
+      g.x = ax0;
+      g.y = ay0;
+      g.z = az0;
+      g.q = ex * ex + ey * ey + ez * ez;
+      g.dx = 2.0f * ex;
+      g.dy = 2.0f * ey;
+      g.dz = 2.0f * ez;
+      g.pad = 0.0f;
+      src[threadIdx.x] = g;
     }
     __syncthreads();
     int lo, hi;
@@ -220,11 +236,11 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
       const int s0 = t0 + lo, s1 = t0 + hi;
       const bool hit = exl && ((jj >= s0 && jj < s1) || (pj >= s0 && pj < s1));
       if (__any(hit))
-        bs_tile_f32<true, kUniform>(sx + lo, sy + lo, sz + lo, dx + lo, dy + lo, dz + lo, dq + lo,
-                                    hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax, ay, az);
+        bs_tile_f32<true, kUniform>(src + lo, hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax,
+                                    ay, az);
       else
-        bs_tile_f32<false, kUniform>(sx + lo, sy + lo, sz + lo, dx + lo, dy + lo, dz + lo, dq + lo,
-                                     hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax, ay, az);
+        bs_tile_f32<false, kUniform>(src + lo, hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax,
+                                     ay, az);
     }
     __syncthreads();
   }
