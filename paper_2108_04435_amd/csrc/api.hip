@@ -148,13 +148,13 @@ size_t layout(Run& r, char* base) {
                        &r.scan_a, &r.scan_b, &r.used};
   for (int32_t** p : ibufs) *p = (int32_t*)B.take((nc + 1) * sizeof(int32_t));
   const int nco = r.bsax.copies;
-  r.bsX = (uint32_t*)B.take((size_t)nco * 3 * nc * sizeof(uint32_t));
-  r.bsD = B.take((size_t)nco * (r.prec == VLB_F64 ? 6 : 4) * nc * fe);  // FP64: d (3) and residuals (3)
+  // grid coordinates (the FP64 sum reads the positions)
+  r.bsX = r.prec == VLB_F64 ? nullptr : (uint32_t*)B.take((size_t)nco * 3 * nc * sizeof(uint32_t));
   size_t pbytes = (size_t)nco * r.bsS * 3 * nc * fe;
   if (r.vor.ff_cell > 0 && (size_t)r.ffS * 3 * nc * fe > pbytes) pbytes = (size_t)r.ffS * 3 * nc * fe;
   r.bsP = B.take(pbytes);
   r.ffws = r.vor.ff_cell > 0 ? B.take(ff_run_bytes(r)) : nullptr;
-  r.bsown = nco > 1 ? (int32_t*)B.take(nc * sizeof(int32_t)) : nullptr;
+  r.bsown = nco > 1 && r.prec != VLB_F64 ? (int32_t*)B.take(nc * sizeof(int32_t)) : nullptr;
   r.cnt = (int32_t*)B.take(32 * sizeof(int32_t));
   r.marked = (uint32_t*)B.take(nc * sizeof(uint32_t));
   r.keys_a = (uint32_t*)B.take(nc * sizeof(uint32_t));
@@ -578,8 +578,8 @@ int one_step(vlb_run* h, bool first, bool last) {
     if (r.vor.ff_cell > 0) {
       HIP_OR_FAIL(h, ff_run_sum(r, Ys[s]));
     } else {
-      if (r.prec == VLB_F64 || r.bsax.copies > 1) HIP_OR_FAIL(h, bs_prep(r, Ys[s]));
-      HIP_OR_FAIL(h, bs_sum(r));
+      if (r.bsax.copies > 1) HIP_OR_FAIL(h, bs_prep(r, Ys[s]));
+      HIP_OR_FAIL(h, bs_sum(r, Ys[s]));
     }
     // the first finalize reads the velocity field and the superflow
     if (gs == 0) HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_mom, 0));
@@ -735,7 +735,7 @@ int vlb_eval_line_velocity(vlb_run* h, double* vs, double* vn, double* sdot, dou
     HIP_OR_FAIL(h, ff_run_sum(r, r.pos));
   } else {
     HIP_OR_FAIL(h, bs_prep(r, r.pos));
-    HIP_OR_FAIL(h, bs_sum(r));
+    HIP_OR_FAIL(h, bs_sum(r, r.pos));
   }
   HIP_OR_FAIL(h, fil_finalize(r, 1, 1, 1, r.pos, r.ya, 1));
   if (r.vor.coupling) HIP_OR_FAIL(h, fil_spread(r));
@@ -936,7 +936,7 @@ int vlb_time_kernel(vlb_run* h, int32_t cls, int32_t reps, double* avg_ms) {
     if (ff)
       HIP_OR_FAIL(h, ff_run_sum(r, r.pos));
     else if (cls == 0)
-      HIP_OR_FAIL(h, bs_sum(r));
+      HIP_OR_FAIL(h, bs_sum(r, r.pos));
     else
       HIP_OR_FAIL(h, lbm_step(r));
   }

@@ -4,9 +4,11 @@
 // it (k = prev(j) and k = j; their divergent contribution is the LIA term).
 //
 // Layout and decomposition:
-//  * per point: 32-bit grid coordinates X (3 x u32, SoA); the segment
-//    vector d_k = s_next(k) - s_k is the wrapped grid difference in the FP32
-//    sum and an FP64 nearest-image vector in the FP64 sum;
+//  * FP32: per point 32-bit grid coordinates X (3 x u32, SoA); the segment
+//    vector d_k = s_next(k) - s_k is the wrapped grid difference.  FP64: the
+//    sum reads the positions themselves (grid coordinates, residuals and
+//    FP64 nearest-image segment vectors are formed while a tile is staged,
+//    about 1% of the pair work, so that no kernel precedes the sum);
 //  * a 2-D grid: blockIdx.x picks 64 consecutive targets (one per lane of
 //    every wave), blockIdx.y one contiguous chunk of sources; the chunk is
 //    staged through LDS in tiles of 256 sources, each of the block's 4
@@ -28,6 +30,21 @@ namespace {
 
 constexpr int kTile = 256;
 constexpr int kTargets = 64;  // targets per block, one per lane of each wave
+// Point count from which the FP64 sum takes two targets per lane: a record
+// read from LDS then serves two pairs and two dependence chains overlap (2e4
+// points 557 against 594 us, 6e4 points 4883 against 5010); with fewer points
+// the blocks of half as many targets fill the chip better.
+constexpr long long kWideTargets = 4096;
+
+// Points of an FP64 sum: component a of point j at Y[a sa + j sj], links
+// (entries of nxt are clamped into the points; prv is read with image
+// copies only).
+struct BsPts {
+  const double* Y;
+  long long sa, sj;
+  const int32_t* nxt;
+  const int32_t* prv;
+};
 
 // Quarter of a staged tile of cnt sources walked by wave w: [lo, hi) (empty
 // when lo >= hi), lo a multiple of 4 so that the unrolled loop reads the
@@ -38,70 +55,52 @@ __device__ inline void wave_range(int cnt, int w, int& lo, int& hi) {
   hi = __builtin_amdgcn_readfirstlane(min(cnt, lo + q));
 }
 
-// Grid coordinates of the points at positions Y, and for the FP64 path the
-// segment vectors (nearest image, lattice units) and the residuals
-// rho = (y + off) - X / q of the positions below their grid value (taken
-// with the unwrapped grid value), so that y_s - y_t of the image the grid
-// difference chooses is (X_s - X_t) / q + rho_s - rho_t.  The FP32 sum
-// takes each segment vector as the wrapped grid difference to the successor.
-//
-// With image copies (own non-null), own[j] is the copy mirrored in the wall
-// that point j is bound to when j is an end of an open line (the lowest
-// closed axis whose wall plane it lies on; nothing else reflected), else 0:
-// in that copy the images of j's two segments meet j and are excluded, as
-// the real ones are in copy 0.
-template <class T>
+// A coordinate mirrored for an image copy: 0 itself, 1 in the wall plane
+// -1/2, 2 in the plane L - 1/2.
+__device__ inline double bs_mirror(double y, int m, double L) {
+  return m == 0 ? y : (m == 1 ? 2.0 * (-0.5) - y : 2.0 * (L - 0.5) - y);
+}
+
+// The image copy mirrored in the wall that the end of an open line at y is
+// bound to (the lowest closed axis whose wall plane it lies on; nothing else
+// reflected), 0 if none: in that copy the images of the end's two segments
+// meet it and are excluded, as the real ones are in copy 0.
+__device__ inline int bs_own_copy(const double* y, const BsAxes& ax) {
+  int ea = -1, es = 0, oc = 0;
+  for (int a = 2; a >= 0; --a)
+    if (!ax.periodic[a] && (y[a] == -0.5 || y[a] == ax.L[a] - 0.5)) {
+      ea = a;
+      es = y[a] == -0.5 ? 1 : 2;
+    }
+  if (ea >= 0)
+    for (int c = 1; c < ax.copies; ++c) {
+      bool only = true;
+      for (int a = 0; a < 3; ++a) only = only && ax.refl[c][a] == (a == ea ? es : 0);
+      if (only) oc = c;
+    }
+  return oc;
+}
+
+// FP32: grid coordinates of the points at positions Y (copy 0) and of their
+// images in the wall planes (copies 1..); with image copies (own non-null)
+// the own copy of every open line's end (0 for other points).
 __global__ void k_prep(const double* __restrict__ Y, const int32_t* __restrict__ nxt,
                        const int32_t* __restrict__ prv, const int32_t* __restrict__ cnt,
-                       long long ncap, BsAxes ax, uint32_t* __restrict__ X, T* __restrict__ D,
+                       long long ncap, BsAxes ax, uint32_t* __restrict__ X,
                        int32_t* __restrict__ own) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int n = cnt[0];
   if (j >= n) return;
-  const int k = nxt[j];
-  double y[3], d[3];
+  double y[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    y[a] = Y[a * ncap + j];
-    d[a] = Y[a * ncap + k] - y[a];
-    if (ax.periodic[a]) {
-      if (d[a] > 0.5 * ax.L[a])
-        d[a] = d[a] - ax.L[a];
-      else if (d[a] < -0.5 * ax.L[a])
-        d[a] = d[a] + ax.L[a];
-    }
-  }
-  if (own) {
-    int oc = 0;
-    if (k == j || prv[j] == j) {
-      int ea = -1, es = 0;
-      for (int a = 2; a >= 0; --a)
-        if (!ax.periodic[a] && (y[a] == -0.5 || y[a] == ax.L[a] - 0.5)) {
-          ea = a;
-          es = y[a] == -0.5 ? 1 : 2;
-        }
-      if (ea >= 0)
-        for (int c = 1; c < ax.copies; ++c) {
-          bool only = true;
-          for (int a = 0; a < 3; ++a) only = only && ax.refl[c][a] == (a == ea ? es : 0);
-          if (only) oc = c;
-        }
-    }
-    own[j] = oc;
-  }
-  // copy 0: the point itself; copies 1..: its images in the wall planes
+  for (int a = 0; a < 3; ++a) y[a] = Y[a * ncap + j];
+  if (own) own[j] = (nxt[j] == j || prv[j] == j) ? bs_own_copy(y, ax) : 0;
   for (int c = 0; c < ax.copies; ++c) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const int m = ax.refl[c][a];
-      const double yc = m == 0 ? y[a] : (m == 1 ? 2.0 * (-0.5) - y[a] : 2.0 * (ax.L[a] - 0.5) - y[a]);
-      const double s = floor((yc + ax.off[a]) * ax.q[a]);
+      const double s = floor((bs_mirror(y[a], ax.refl[c][a], ax.L[a]) + ax.off[a]) * ax.q[a]);
       X[((long long)c * 3 + a) * ncap + j] =
           ax.periodic[a] ? (uint32_t)(long long)s : (uint32_t)(int)(long long)s;
-      if (sizeof(T) == 8) {
-        D[((long long)c * 6 + a) * ncap + j] = (T)(m == 0 ? d[a] : -d[a]);
-        D[((long long)c * 6 + 3 + a) * ncap + j] = (T)((yc + ax.off[a]) - s * ax.invq_d[a]);
-      }
     }
   }
 }
@@ -259,166 +258,223 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
   }
 }
 
-// FP64 pair sum (plain path).  R1 = (X_s - X_t) / q + (rho_s - rho_t): the
-// wrapped grid difference picks the image (the same decision as the FP32
-// sum), the residuals restore the FP64 separation of that image to
-// rounding; R2 = R1 + d enters through |R2|^2 = |R1|^2 + 2 R1.d + |d|^2 and
-// R1.R2 = |R1|^2 + R1.d, as in the FP32 sum.  The closed form is evaluated
-// with the inverse norms and the reciprocal of the hardware approximations
-// (relative error up to about 5e-8), each refined by one Newton step (which
-// squares it: at most 4.1e-15 for the inverse root and 2.1e-15 for the
-// reciprocal over 1e6 arguments from 1e-8 to 1e22, measured against
-// long-double references), and the same checked / unchecked tile split as
-// the FP32 sum.
-__device__ inline double rsq_nr(double n) {
-  const double y = __builtin_amdgcn_rsq(n);
-  const double e = fma(-(n * y), y, 1.0);  // 1 - n y^2
-  return fma(0.5 * y, e, y);
+// FP64 pair sum (plain path), with the FP32 sum's q, R2 and s^2:
+//   s^2 = |R1|^2 + |R2|^2 + 2 p,  p = |R1||R2| = sqrt(|R1|^2 |R2|^2),
+//   (|R1| + |R2|) / (p (p + R1.R2)) = 2 s / (p (s^2 - q))
+//                                   = 2 s^2 / sqrt(s^2 p^2 (s^2 - q)^2),
+// two inverse roots instead of two and a reciprocal.  Each is the hardware
+// approximation (relative error up to about 5e-8) refined by one Newton step
+// (which squares it), the first inside s^2, the second inside the factor:
+// f = s^2 z (3 - arg z^2) with z ~ 1/sqrt(arg).  Sources are staged as 2 d;
+// the partial sums take the 1/2.
+//
+// The separation R1: on a closed axis the difference of the positions; on a
+// periodic axis (X_s - X_t) / q + (rho_s - rho_t), where the wrapped grid
+// difference picks the image (the same decision as the FP32 sum) and the
+// residuals rho = y - X / q restore the FP64 separation of that image to
+// rounding.  The set of periodic axes is a template argument.
+//
+// What bounds it: VALU issue.  FP64 and conversions take one cycle per wave
+// instruction and CU (no two waves issue together), an FP64 transcendental
+// four; 62.5 cycles per pair with three of them and four instructions per
+// axis of R1, 50 now (41 with two closed axes).  2e4 points, two closed axes:
+// 0.61 -> 0.76 Tpairs/s with the error against 64 bits 5.9e-15 -> 1.3e-15.
+struct __align__(16) BsSrcD {
+  double rx, ry, rz;  // the segment's start: residual (periodic axis) or position (closed axis)
+  double q;           // |d|^2
+  double dx, dy, dz;  // 2 d
+  uint32_t x, y, z;   // grid coordinates (periodic axes)
+  int32_t kn;         // index of the segment's end
+};
+
+template <bool kPeriodic>
+__device__ inline double bs_sep(uint32_t xs, uint32_t xt, double rs, double rt, double g) {
+  return kPeriodic ? fma((double)(int)(xs - xt), g, rs - rt) : rs - rt;
 }
 
-__device__ inline double rcp_nr(double d) {
-  const double q = __builtin_amdgcn_rcp(d);
-  const double e = fma(-d, q, 1.0);
-  return fma(q, e, q);
-}
+// Targets per lane of the FP64 sum: index, exclusion index (-1: none),
+// position data and the sums.
+struct BsTgtD {
+  uint32_t x, y, z;
+  int jj;
+  double rx, ry, rz, ax, ay, az;
+};
 
-template <bool kCheck>
-__device__ inline void bs_tile_f64(const uint32_t* sx, const uint32_t* sy, const uint32_t* sz,
-                                   const double* rx, const double* ry, const double* rz,
-                                   const double* dx, const double* dy, const double* dz,
-                                   const double* dq, int cnt,
-                                   int t0, uint32_t xt, uint32_t yt, uint32_t zt, double rtx,
-                                   double rty, double rtz, double gx, double gy, double gz, int jj,
-                                   int pj, double& ax, double& ay, double& az) {
-#pragma unroll 2
+template <int kPer, int NT, bool kCheck>
+__device__ inline void bs_tile_f64(const BsSrcD* src, int cnt, int t0, BsTgtD* tg, double gx,
+                                   double gy, double gz) {
+#pragma unroll(NT == 1 ? 2 : 1)
   for (int s = 0; s < cnt; ++s) {
-    const double r1x = fma((double)(int)(sx[s] - xt), gx, rx[s] - rtx);
-    const double r1y = fma((double)(int)(sy[s] - yt), gy, ry[s] - rty);
-    const double r1z = fma((double)(int)(sz[s] - zt), gz, rz[s] - rtz);
-    const double ex = dx[s], ey = dy[s], ez = dz[s];
-    const double t = r1x * ex + r1y * ey + r1z * ez;
-    const double n1 = r1x * r1x + r1y * r1y + r1z * r1z;
-    const double n2 = fma(2.0, t, n1 + dq[s]);
-    const double u = n1 + t;
-    const double crx = r1y * ez - r1z * ey;
-    const double cry = r1z * ex - r1x * ez;
-    const double crz = r1x * ey - r1y * ex;
-    const double i1 = rsq_nr(n1);
-    const double i2 = rsq_nr(n2);
-    const double a = i1 * i2;
-    double f = (i1 + i2) * a * rcp_nr(fma(u, a, 1.0));
-    if (kCheck) {
-      const int k = t0 + s;
-      f = (k == jj || k == pj) ? 0.0 : f;
+    const BsSrcD g = src[s];
+#pragma unroll
+    for (int m = 0; m < NT; ++m) {
+      BsTgtD& t = tg[m];
+      const double r1x = bs_sep<(kPer & 1) != 0>(g.x, t.x, g.rx, t.rx, gx);
+      const double r1y = bs_sep<(kPer & 2) != 0>(g.y, t.y, g.ry, t.ry, gy);
+      const double r1z = bs_sep<(kPer & 4) != 0>(g.z, t.z, g.rz, t.rz, gz);
+      const double n1 = fma(r1x, r1x, fma(r1y, r1y, r1z * r1z));
+      const double n2 = n1 + fma(r1x, g.dx, fma(r1y, g.dy, fma(r1z, g.dz, g.q)));
+      const double n12 = n1 * n2;
+      const double y = __builtin_amdgcn_rsq(n12);
+      const double p = n12 * y;
+      const double s2 = fma(p, fma(-p, y, 1.0), fma(2.0, p, n1 + n2));
+      const double w = s2 - g.q;
+      const double arg = (s2 * n12) * (w * w);
+      const double z = __builtin_amdgcn_rsq(arg);
+      double f = (s2 * z) * fma(-(arg * z), z, 3.0);
+      if (kCheck) f = (t0 + s == t.jj || g.kn == t.jj) ? 0.0 : f;
+      t.ax = fma(f, fma(r1y, g.dz, -(r1z * g.dy)), t.ax);
+      t.ay = fma(f, fma(r1z, g.dx, -(r1x * g.dz)), t.ay);
+      t.az = fma(f, fma(r1x, g.dy, -(r1y * g.dx)), t.az);
     }
-    ax = fma(f, crx, ax);
-    ay = fma(f, cry, ay);
-    az = fma(f, crz, az);
   }
 }
 
-__global__ __launch_bounds__(256) void k_bs_f64(const uint32_t* __restrict__ X,
-                                               const double* __restrict__ D,
-                                               const int32_t* __restrict__ prv,
-                                               int32_t* __restrict__ cntp, long long ncap,
-                                               int S, double gx, double gy, double gz,
-                                               double* __restrict__ P, BsAxes bx,
-                                               const int32_t* __restrict__ own) {
-  const int n = cntp[0];
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && n > 2)
+// Grid coordinate and residual of a coordinate on a periodic axis.
+__device__ inline void bs_grid_f64(double y, double q, double invq, uint32_t& x, double& r) {
+  const double s = floor(y * q);
+  x = (uint32_t)(long long)s;
+  r = y - s * invq;
+}
+
+template <int kPer, int NT>
+__global__ __launch_bounds__(256) void k_bs_f64(BsPts in, int32_t* __restrict__ cntp, int n_arg,
+                                               long long nc, int S, double* __restrict__ P,
+                                               BsAxes bx) {
+  const int n = cntp ? cntp[0] : n_arg;
+  if (cntp && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && n > 2)
     *(long long*)(cntp + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
-  const int j0 = blockIdx.x * kTargets;
+  constexpr int kT = kTargets * NT;  // targets per block
+  const int j0 = blockIdx.x * kT;
   if (j0 >= n) return;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
-  const int j = j0 + lane;
-  const bool valid = j < n;
   const int copy = blockIdx.y / S;
-  const uint32_t* __restrict__ Xs = X + (long long)copy * 3 * ncap;  // this copy's sources
-  const double* __restrict__ Ds = D + (long long)copy * 6 * ncap;
   const int per = (n + S - 1) / S;
   const int kb = (blockIdx.y - copy * S) * per;
   const int ke = min(n, kb + per);
-  const uint32_t xt = valid ? X[j] : 0u;
-  const uint32_t yt = valid ? X[ncap + j] : 0u;
-  const uint32_t zt = valid ? X[2 * ncap + j] : 0u;
-  const double rtx = valid ? D[3 * ncap + j] : 0.0;
-  const double rty = valid ? D[4 * ncap + j] : 0.0;
-  const double rtz = valid ? D[5 * ncap + j] : 0.0;
-  const int oc = (valid && own) ? own[j] : 0;
-  const bool exl = valid && (copy == 0 || copy == oc);
-  const int pj = exl ? prv[j] : -1;
-  const int jj = exl ? j : -1;
-  __shared__ __align__(16) uint32_t sx[kTile], sy[kTile], sz[kTile];
-  __shared__ __align__(16) double rx[kTile], ry[kTile], rz[kTile];
-  __shared__ __align__(16) double dx[kTile], dy[kTile], dz[kTile], dq[kTile];
-  __shared__ double red[3][3][kTargets];  // sums of waves 1..3
-  double ax = 0.0, ay = 0.0, az = 0.0;
+  BsTgtD tg[NT];
+  bool exl = false;
+#pragma unroll
+  for (int m = 0; m < NT; ++m) {
+    const int j = j0 + m * kTargets + lane;
+    const int jc = min(j, n - 1);  // lanes beyond the points repeat the last one, unwritten
+    double y[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
+    BsTgtD& t = tg[m];
+    t.x = t.y = t.z = 0u;
+    t.rx = y[0];
+    t.ry = y[1];
+    t.rz = y[2];
+    if (kPer & 1) bs_grid_f64(y[0], bx.q[0], bx.invq_d[0], t.x, t.rx);
+    if (kPer & 2) bs_grid_f64(y[1], bx.q[1], bx.invq_d[1], t.y, t.ry);
+    if (kPer & 4) bs_grid_f64(y[2], bx.q[2], bx.invq_d[2], t.z, t.rz);
+    t.ax = t.ay = t.az = 0.0;
+    // the target's own two segments are excluded in copy 0 and, for the end
+    // of an open line, in the copy mirrored in its wall
+    bool ex = j < n && copy == 0;
+    if (copy > 0 && j < n && (in.nxt[jc] == jc || in.prv[jc] == jc))
+      ex = bs_own_copy(y, bx) == copy;
+    t.jj = ex ? j : -1;
+    exl = exl || ex;
+  }
+  const bool exany = __any(exl);
+  __shared__ BsSrcD src[kTile];
+  static_assert(sizeof(src) >= 9 * kT * sizeof(double), "the wave sums reuse the tile");
   for (int t0 = kb; t0 < ke; t0 += kTile) {
     const int k = t0 + threadIdx.x;
     if (k < ke) {
-      sx[threadIdx.x] = Xs[k];
-      sy[threadIdx.x] = Xs[ncap + k];
-      sz[threadIdx.x] = Xs[2 * ncap + k];
-      const double ex = Ds[k], ey = Ds[ncap + k], ez = Ds[2 * ncap + k];
-      dx[threadIdx.x] = ex;
-      dy[threadIdx.x] = ey;
-      dz[threadIdx.x] = ez;
-      dq[threadIdx.x] = ex * ex + ey * ey + ez * ez;
-      rx[threadIdx.x] = Ds[3 * ncap + k];
-      ry[threadIdx.x] = Ds[4 * ncap + k];
-      rz[threadIdx.x] = Ds[5 * ncap + k];
+      BsSrcD g;
+      g.kn = min(max(in.nxt[k], 0), n - 1);
+      double r[3], d[3];
+      uint32_t x[3] = {0u, 0u, 0u};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double y = in.Y[a * in.sa + k * in.sj];
+        d[a] = in.Y[a * in.sa + g.kn * in.sj] - y;
+        if ((kPer >> a) & 1) {
+          if (d[a] > 0.5 * bx.L[a])
+            d[a] = d[a] - bx.L[a];
+          else if (d[a] < -0.5 * bx.L[a])
+            d[a] = d[a] + bx.L[a];
+          bs_grid_f64(y, bx.q[a], bx.invq_d[a], x[a], r[a]);
+        } else {
+          const int rm = bx.refl[copy][a];
+          r[a] = bs_mirror(y, rm, bx.L[a]);
+          d[a] = rm ? -d[a] : d[a];
+        }
+      }
+      g.rx = r[0];
+      g.ry = r[1];
+      g.rz = r[2];
+      g.x = x[0];
+      g.y = x[1];
+      g.z = x[2];
+      g.q = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+      g.dx = 2.0 * d[0];
+      g.dy = 2.0 * d[1];
+      g.dz = 2.0 * d[2];
+      src[threadIdx.x] = g;
     }
     __syncthreads();
     int lo, hi;
     wave_range(min(kTile, ke - t0), w, lo, hi);
     if (lo < hi) {
-      const int s0 = t0 + lo, s1 = t0 + hi;
-      const bool hit = exl && ((jj >= s0 && jj < s1) || (pj >= s0 && pj < s1));
-      if (__any(hit))
-        bs_tile_f64<true>(sx + lo, sy + lo, sz + lo, rx + lo, ry + lo, rz + lo, dx + lo, dy + lo,
-                          dz + lo, dq + lo, hi - lo, s0, xt, yt, zt, rtx, rty, rtz, gx, gy, gz, jj,
-                          pj, ax, ay, az);
+      // does this wave's quarter (at most 64 sources) start or end at one of
+      // the block's targets?
+      bool hit = false;
+      if (lane < hi - lo)
+        hit = (uint32_t)(t0 + lo + lane - j0) < (uint32_t)kT ||
+              (uint32_t)(src[lo + lane].kn - j0) < (uint32_t)kT;
+      if (exany && __any(hit))
+        bs_tile_f64<kPer, NT, true>(src + lo, hi - lo, t0 + lo, tg, bx.invq_d[0], bx.invq_d[1],
+                                    bx.invq_d[2]);
       else
-        bs_tile_f64<false>(sx + lo, sy + lo, sz + lo, rx + lo, ry + lo, rz + lo, dx + lo, dy + lo,
-                           dz + lo, dq + lo, hi - lo, s0, xt, yt, zt, rtx, rty, rtz, gx, gy, gz, jj,
-                           pj, ax, ay, az);
+        bs_tile_f64<kPer, NT, false>(src + lo, hi - lo, t0 + lo, tg, bx.invq_d[0], bx.invq_d[1],
+                                     bx.invq_d[2]);
     }
     __syncthreads();
   }
-  if (w > 0) {
-    red[w - 1][0][lane] = ax;
-    red[w - 1][1][lane] = ay;
-    red[w - 1][2][lane] = az;
-  }
+  double(*red)[3][kT] = reinterpret_cast<double(*)[3][kT]>(src);  // sums of waves 1..3
+#pragma unroll
+  for (int m = 0; m < NT; ++m)
+    if (w > 0) {
+      red[w - 1][0][m * kTargets + lane] = tg[m].ax;
+      red[w - 1][1][m * kTargets + lane] = tg[m].ay;
+      red[w - 1][2][m * kTargets + lane] = tg[m].az;
+    }
   __syncthreads();
-  if (w == 0 && valid) {
-    const double sg = (double)bx.sign[copy];
-    double* out = P + (long long)blockIdx.y * 3 * ncap;
-    out[j] = sg * (((ax + red[0][0][lane]) + red[1][0][lane]) + red[2][0][lane]);
-    out[ncap + j] = sg * (((ay + red[0][1][lane]) + red[1][1][lane]) + red[2][1][lane]);
-    out[2 * ncap + j] = sg * (((az + red[0][2][lane]) + red[1][2][lane]) + red[2][2][lane]);
+  const double sg = 0.5 * (double)bx.sign[copy];
+  double* out = P + (long long)blockIdx.y * 3 * nc;
+#pragma unroll
+  for (int m = 0; m < NT; ++m) {
+    const int e = m * kTargets + lane, j = j0 + e;
+    if (w == 0 && j < n) {
+      out[j] = sg * (((tg[m].ax + red[0][0][e]) + red[1][0][e]) + red[2][0][e]);
+      out[nc + j] = sg * (((tg[m].ay + red[0][1][e]) + red[1][1][e]) + red[2][1][e]);
+      out[2 * nc + j] = sg * (((tg[m].az + red[0][2][e]) + red[1][2][e]) + red[2][2][e]);
+    }
   }
 }
 
 // ---- standalone sum (positions and links from the caller, no run)
 
-// Links and grid data of a caller's filaments: next is clamped into [0, n)
-// (an invalid permutation gives meaningless velocities, never an access out
-// of bounds) and inverted into prev; grid coordinates and, for the FP64
-// sum, segment vectors and residuals as k_prep, from [n][3] positions.
-// Thread 0 writes the point count and clears the pair counter.
+// FP32: links and grid coordinates of a caller's filaments: next is clamped
+// into [0, n) (an invalid permutation gives meaningless velocities, never an
+// access out of bounds) and inverted into prev; grid coordinates as k_prep,
+// from [n][3] positions.  Thread 0 writes the point count and clears the pair
+// counter.
 // prv[j] = j: the first point of an open line keeps it (no real link to it)
 __global__ void k_solo_init(int32_t* __restrict__ prv, int n) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j < n) prv[j] = j;
 }
 
-template <class T>
 __global__ void k_solo_prep(const double* __restrict__ xyz, const int32_t* __restrict__ next,
                             int n, BsAxes ax, int32_t* __restrict__ cnt,
-                            uint32_t* __restrict__ X, T* __restrict__ D,
-                            int32_t* __restrict__ nxt, int32_t* __restrict__ prv) {
+                            uint32_t* __restrict__ X, int32_t* __restrict__ nxt,
+                            int32_t* __restrict__ prv) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j == 0) {
     cnt[0] = n;
@@ -430,21 +486,9 @@ __global__ void k_solo_prep(const double* __restrict__ xyz, const int32_t* __res
   if (k != j) prv[k] = j;  // the last point of an open line links to itself
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double y = xyz[3LL * j + a];
-    const double s = floor((y + ax.off[a]) * ax.q[a]);
+    const double s = floor((xyz[3LL * j + a] + ax.off[a]) * ax.q[a]);
     X[(long long)a * n + j] = ax.periodic[a] ? (uint32_t)(long long)s
                                              : (uint32_t)(int)(long long)s;
-    if (sizeof(T) == 8) {
-      double d = xyz[3LL * k + a] - y;
-      if (ax.periodic[a]) {
-        if (d > 0.5 * ax.L[a])
-          d = d - ax.L[a];
-        else if (d < -0.5 * ax.L[a])
-          d = d + ax.L[a];
-      }
-      D[(long long)a * n + j] = (T)d;
-      D[(long long)(3 + a) * n + j] = (T)((y + ax.off[a]) - s * ax.invq_d[a]);
-    }
   }
 }
 
@@ -556,27 +600,48 @@ int bs_chunks(long long ncap) {
 }
 
 hipError_t bs_prep(Run& r, const double* Y) {
+  if (r.prec == VLB_F64) return hipSuccess;  // that sum reads the positions
   const int nb = (int)((r.ncap + 255) / 256);
-  int32_t* own = r.bsax.copies > 1 ? r.bsown : nullptr;
-  if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_prep<double>, dim3(nb), dim3(256), 0, r.stream, Y, r.nxt, r.prv, r.cnt,
-                       r.ncap, r.bsax, r.bsX, (double*)r.bsD, own);
-  else
-    hipLaunchKernelGGL(k_prep<float>, dim3(nb), dim3(256), 0, r.stream, Y, r.nxt, r.prv, r.cnt,
-                       r.ncap, r.bsax, r.bsX, (float*)r.bsD, own);
+  hipLaunchKernelGGL(k_prep, dim3(nb), dim3(256), 0, r.stream, Y, r.nxt, r.prv, r.cnt, r.ncap,
+                     r.bsax, r.bsX, r.bsax.copies > 1 ? r.bsown : nullptr);
   return hipGetLastError();
 }
 
-hipError_t bs_sum(Run& r) {
+namespace {
+
+template <int NT>
+hipError_t launch_bs_f64(const BsPts& in, int32_t* cnt, long long n, int S, double* P,
+                         const BsAxes& ax, hipStream_t stream) {
+  using K = void (*)(BsPts, int32_t*, int, long long, int, double*, BsAxes);
+  static constexpr K kern[8] = {k_bs_f64<0, NT>, k_bs_f64<1, NT>, k_bs_f64<2, NT>,
+                                k_bs_f64<3, NT>, k_bs_f64<4, NT>, k_bs_f64<5, NT>,
+                                k_bs_f64<6, NT>, k_bs_f64<7, NT>};
+  const int per = (ax.periodic[0] ? 1 : 0) | (ax.periodic[1] ? 2 : 0) | (ax.periodic[2] ? 4 : 0);
+  const int tb = (int)((n + kTargets * NT - 1) / (kTargets * NT));
+  hipLaunchKernelGGL(kern[per], dim3(tb, S * ax.copies), dim3(256), 0, stream, in, cnt, (int)n, n,
+                     S, P, ax);
+  return hipGetLastError();
+}
+
+// FP64 sum over n points (the capacity when the count is on the device).
+hipError_t bs_f64(const BsPts& in, int32_t* cnt, long long n, int S, double* P, const BsAxes& ax,
+                  hipStream_t stream) {
+  return n >= kWideTargets ? launch_bs_f64<2>(in, cnt, n, S, P, ax, stream)
+                           : launch_bs_f64<1>(in, cnt, n, S, P, ax, stream);
+}
+
+}  // namespace
+
+hipError_t bs_sum(Run& r, const double* Y) {
   const int tb = (int)((r.ncap + kTargets - 1) / kTargets);
   dim3 grid(tb, r.bsS * r.bsax.copies);
   hipEvent_t b = nullptr;
   time_begin(r, 0, &b);
   const int32_t* own = r.bsax.copies > 1 ? r.bsown : nullptr;
+  hipError_t e = hipSuccess;
   if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_bs_f64, grid, dim3(256), 0, r.stream, r.bsX, (const double*)r.bsD,
-                       r.prv, r.cnt, r.ncap, r.bsS, r.bsax.invq_d[0], r.bsax.invq_d[1],
-                       r.bsax.invq_d[2], (double*)r.bsP, r.bsax, own);
+    e = bs_f64(BsPts{Y, r.ncap, 1, r.nxt, r.prv}, r.cnt, r.ncap, r.bsS, (double*)r.bsP, r.bsax,
+               r.stream);
   else if (r.bsax.uniform)
     hipLaunchKernelGGL(k_bs_f32<true>, grid, dim3(256), 0, r.stream, r.bsX, r.nxt,
                        r.prv, r.cnt, r.ncap, r.bsS, r.bsax.invq_f[0], r.bsax.invq_f[1],
@@ -586,7 +651,7 @@ hipError_t bs_sum(Run& r) {
                        r.prv, r.cnt, r.ncap, r.bsS, r.bsax.invq_f[0], r.bsax.invq_f[1],
                        r.bsax.invq_f[2], (float*)r.bsP, r.bsax, own);
   time_end(r, 0, b);
-  return hipGetLastError();
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
 int bs_check_desc(const vlb_bs_desc* d, int64_t n, std::string& msg) {
@@ -622,10 +687,11 @@ size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b) {
   };
   BsSolo s{};
   s.cnt = (int32_t*)take(32 * sizeof(int32_t));
-  s.X = (uint32_t*)take(3 * (size_t)n * sizeof(uint32_t));
-  s.D = take((prec == VLB_F64 ? 6 : 1) * (size_t)n * fe);
-  s.nxt = (int32_t*)take((size_t)n * sizeof(int32_t));
-  s.prv = (int32_t*)take((size_t)n * sizeof(int32_t));
+  if (prec != VLB_F64) {
+    s.X = (uint32_t*)take(3 * (size_t)n * sizeof(uint32_t));
+    s.nxt = (int32_t*)take((size_t)n * sizeof(int32_t));
+    s.prv = (int32_t*)take((size_t)n * sizeof(int32_t));
+  }
   s.P = take((size_t)S * 3 * n * fe);
   s.S = S;
   if (b) *b = s;
@@ -639,18 +705,16 @@ hipError_t bs_solo(const BsAxes& ax, int prec, long long n, const double* xyz,
   const int tb = (int)((n + kTargets - 1) / kTargets);
   const dim3 grid(tb, b.S);
   const double s = kappa / (4.0 * M_PI);
-  hipLaunchKernelGGL(k_solo_init, dim3(nb), dim3(256), 0, stream, b.prv, (int)n);
   if (prec == VLB_F64) {
-    hipLaunchKernelGGL(k_solo_prep<double>, dim3(nb), dim3(256), 0, stream, xyz, next, (int)n,
-                       ax, b.cnt, b.X, (double*)b.D, b.nxt, b.prv);
-    hipLaunchKernelGGL(k_bs_f64, grid, dim3(256), 0, stream, b.X, (const double*)b.D, b.prv,
-                       b.cnt, n, b.S, ax.invq_d[0], ax.invq_d[1], ax.invq_d[2], (double*)b.P, ax,
-                       nullptr);
+    const hipError_t e = bs_f64(BsPts{xyz, 1, 3, next, nullptr}, nullptr, n, b.S, (double*)b.P, ax,
+                                stream);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_solo_sum<double>, dim3(nb), dim3(256), 0, stream, (const double*)b.P,
                        b.S, (int)n, s, v);
   } else {
-    hipLaunchKernelGGL(k_solo_prep<float>, dim3(nb), dim3(256), 0, stream, xyz, next, (int)n,
-                       ax, b.cnt, b.X, (float*)b.D, b.nxt, b.prv);
+    hipLaunchKernelGGL(k_solo_init, dim3(nb), dim3(256), 0, stream, b.prv, (int)n);
+    hipLaunchKernelGGL(k_solo_prep, dim3(nb), dim3(256), 0, stream, xyz, next, (int)n, ax, b.cnt,
+                       b.X, b.nxt, b.prv);
     if (ax.uniform)
       hipLaunchKernelGGL(k_bs_f32<true>, grid, dim3(256), 0, stream, b.X, b.nxt, b.prv, b.cnt,
                          n, b.S, ax.invq_f[0], ax.invq_f[1], ax.invq_f[2], (float*)b.P, ax,

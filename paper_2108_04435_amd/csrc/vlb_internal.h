@@ -521,7 +521,6 @@ struct Run {
 
   // Biot-Savart
   uint32_t* bsX = nullptr;  // 3 * ncap grid coordinates
-  void* bsD = nullptr;      // 3 * ncap segment vectors (float or double)
   void* bsP = nullptr;      // S * 3 * ncap partial sums
   int32_t* bsown = nullptr;
   // far-field approximation of the non-local sum (vor.ff_cell > 0): its
@@ -617,12 +616,11 @@ hipError_t diag_cylindrical(Run& r, const double point[3], const double unit_dir
 BsAxes bs_make_axes(const int n[3], const int wall[3], bool images);
 
 // Scratch of the standalone Biot-Savart sum (vlb_biot_savart*): point
-// count and pair counter, grid coordinates, FP64 segment data, sanitised
-// links, chunk partials.
+// count and pair counter; FP32 also grid coordinates and sanitised links;
+// chunk partials.
 struct BsSolo {
   int32_t* cnt;
   uint32_t* X;
-  void* D;
   int32_t* nxt;
   int32_t* prv;
   void* P;
@@ -650,7 +648,7 @@ size_t ff_workspace(const vlb_bs_desc* d, const vlb_ff_params* p, long long n);
 hipError_t ff_solo(const vlb_bs_desc* d, const vlb_ff_params* p, long long n, const double* xyz,
                    const int32_t* next, double* v, void* ws, hipStream_t stream);
 hipError_t bs_prep(Run& r, const double* Y);
-hipError_t bs_sum(Run& r);
+hipError_t bs_sum(Run& r, const double* Y);
 int bs_chunks(long long ncap);
 
 // One finalize of a filament stage: stage of the Runge-Kutta method (1..rk),
