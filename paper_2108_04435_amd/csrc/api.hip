@@ -154,7 +154,6 @@ size_t layout(Run& r, char* base) {
   if (r.vor.ff_cell > 0 && (size_t)r.ffS * 3 * nc * fe > pbytes) pbytes = (size_t)r.ffS * 3 * nc * fe;
   r.bsP = B.take(pbytes);
   r.ffws = r.vor.ff_cell > 0 ? B.take(ff_run_bytes(r)) : nullptr;
-  r.bsown = nco > 1 && r.prec != VLB_F64 ? (int32_t*)B.take(nc * sizeof(int32_t)) : nullptr;
   r.cnt = (int32_t*)B.take(32 * sizeof(int32_t));
   r.marked = (uint32_t*)B.take(nc * sizeof(uint32_t));
   r.keys_a = (uint32_t*)B.take(nc * sizeof(uint32_t));
@@ -219,7 +218,7 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   g.fpref_f = (float)g.fpref;
   const int n[3] = {g.nx, g.ny, g.nz};
   r.bsax = bs_make_axes(n, g.wall, vor->wall_images != 0);
-  r.bsS = bs_chunks(r.ncap);
+  r.bsS = bs_chunks(r.ncap, r.bsax.copies);
   r.ffS = vor->ff_cell > 0 ? ff_run_chunks(r) : 0;
   // spreading bins: lower stencil corner, n (+1 on wall axes) per axis
   const unsigned long long ext = (unsigned long long)(n[0] + g.wall[0]) * (n[1] + g.wall[1]) * (n[2] + g.wall[2]);

@@ -32,13 +32,19 @@ constexpr int kTile = 256;
 constexpr int kTargets = 64;  // targets per block, one per lane of each wave
 // Point count from which the FP64 sum takes two targets per lane: a record
 // read from LDS then serves two pairs and two dependence chains overlap (2e4
-// points 557 against 594 us, 6e4 points 4883 against 5010); with fewer points
-// the blocks of half as many targets fill the chip better.
-constexpr long long kWideTargets = 4096;
+// points 550 against 578 us, 6e4 points 4560 against 4710); with fewer points
+// the blocks of half as many targets fill the chip better (1e4 points 159
+// against 164 us).
+constexpr long long kWideTargets = 16384;
 
-// Points of an FP64 sum: component a of point j at Y[a sa + j sj], links
-// (entries of nxt are clamped into the points; prv is read with image
-// copies only).
+// Point count up to which the FP32 stand-alone sum forms grid coordinates
+// while it stages a tile (about 5% of the pair work) instead of in a launch
+// before it: 1e3 points 13.4 against 16.9 us per call, 4e3 22.5 against 25.3,
+// level from 8e3 on.
+constexpr long long kDirectPoints = 4096;
+
+// Points of a sum: component a of point j at Y[a sa + j sj], links (entries
+// of nxt are clamped into the points; prv is read with image copies only).
 struct BsPts {
   const double* Y;
   long long sa, sj;
@@ -47,10 +53,9 @@ struct BsPts {
 };
 
 // Quarter of a staged tile of cnt sources walked by wave w: [lo, hi) (empty
-// when lo >= hi), lo a multiple of 4 so that the unrolled loop reads the
-// tile with 16-byte loads.
+// when lo >= hi), at most 64 of a tile of 256.
 __device__ inline void wave_range(int cnt, int w, int& lo, int& hi) {
-  const int q = (((cnt + 3) >> 2) + 3) & ~3;
+  const int q = (cnt + 3) >> 2;
   lo = w * q;
   hi = __builtin_amdgcn_readfirstlane(min(cnt, lo + q));
 }
@@ -81,27 +86,26 @@ __device__ inline int bs_own_copy(const double* y, const BsAxes& ax) {
   return oc;
 }
 
-// FP32: grid coordinates of the points at positions Y (copy 0) and of their
-// images in the wall planes (copies 1..); with image copies (own non-null)
-// the own copy of every open line's end (0 for other points).
-__global__ void k_prep(const double* __restrict__ Y, const int32_t* __restrict__ nxt,
-                       const int32_t* __restrict__ prv, const int32_t* __restrict__ cnt,
-                       long long ncap, BsAxes ax, uint32_t* __restrict__ X,
-                       int32_t* __restrict__ own) {
+// FP32 grid coordinate of a coordinate on axis a.
+__device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
+  const double s = floor((y + ax.off[a]) * ax.q[a]);
+  return ax.periodic[a] ? (uint32_t)(long long)s : (uint32_t)(int)(long long)s;
+}
+
+// FP32: grid coordinates X (stride nc) of the points (copy 0) and of their
+// images in the wall planes (copies 1..).
+__global__ void k_prep(BsPts in, const int32_t* __restrict__ cntp, int n_arg, long long nc,
+                       BsAxes ax, uint32_t* __restrict__ X) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = cnt[0];
+  const int n = cntp ? cntp[0] : n_arg;
   if (j >= n) return;
   double y[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) y[a] = Y[a * ncap + j];
-  if (own) own[j] = (nxt[j] == j || prv[j] == j) ? bs_own_copy(y, ax) : 0;
+  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + j * in.sj];
   for (int c = 0; c < ax.copies; ++c) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const double s = floor((bs_mirror(y[a], ax.refl[c][a], ax.L[a]) + ax.off[a]) * ax.q[a]);
-      X[((long long)c * 3 + a) * ncap + j] =
-          ax.periodic[a] ? (uint32_t)(long long)s : (uint32_t)(int)(long long)s;
-    }
+    for (int a = 0; a < 3; ++a)
+      X[((long long)c * 3 + a) * nc + j] = bs_grid_f32(bs_mirror(y[a], ax.refl[c][a], ax.L[a]), ax, a);
   }
 }
 
@@ -129,12 +133,24 @@ struct __align__(16) BsSrc {
   uint32_t x, y, z;  // grid coordinates of the segment's start
   float q;           // |d|^2
   float dx, dy, dz;  // 2 d
-  float pad;
+  int32_t kn;        // index of the segment's end
 };
+
+// Does one of the wave's sources [t0 + lo, t0 + hi) (at most 64, staged at
+// src) start or end at one of the nt targets from j0 on?  Uniform per wave.
+template <class Src>
+__device__ inline bool bs_hit(const Src* src, int t0, int lo, int hi, int j0, int nt) {
+  const int lane = threadIdx.x & 63;
+  bool hit = false;
+  if (lane < hi - lo)
+    hit = (uint32_t)(t0 + lo + lane - j0) < (uint32_t)nt ||
+          (uint32_t)(src[lo + lane].kn - j0) < (uint32_t)nt;
+  return __any(hit);
+}
 
 template <bool kCheck, bool kUniform>
 __device__ inline void bs_tile_f32(const BsSrc* src, int cnt, int t0, uint32_t xt, uint32_t yt,
-                                   uint32_t zt, float iqx, float iqy, float iqz, int jj, int pj,
+                                   uint32_t zt, float iqx, float iqy, float iqz, int jj,
                                    float& ax, float& ay, float& az) {
   // unrolled twice: 8 waves per SIMD (four ways: 2% slower)
 #pragma unroll 2
@@ -156,10 +172,7 @@ __device__ inline void bs_tile_f32(const BsSrc* src, int cnt, int t0, uint32_t x
     const float i2 = __builtin_amdgcn_rsqf(n2);
     const float sum = fmaf(n1, i1, n2 * i2);
     float f = (i1 + i2) * __builtin_amdgcn_rcpf(fmaf(sum, sum, -g.q));
-    if (kCheck) {
-      const int k = t0 + s;
-      f = (k == jj || k == pj) ? 0.0f : f;
-    }
+    if (kCheck) f = (t0 + s == jj || g.kn == jj) ? 0.0f : f;
     ax = fmaf(f, fmaf(r1y, ez, -(r1z * ey)), ax);
     ay = fmaf(f, fmaf(r1z, ex, -(r1x * ez)), ay);
     az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
@@ -168,17 +181,16 @@ __device__ inline void bs_tile_f32(const BsSrc* src, int cnt, int t0, uint32_t x
 
 // Grid y: S chunks of every source copy (copy 0 the filaments, the others
 // their wall images, which take no exclusion and carry the copy's sign).
-template <bool kUniform>
-__global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
-                                               const int32_t* __restrict__ nxt,
-                                               const int32_t* __restrict__ prv,
-                                               int32_t* __restrict__ cntp, long long ncap,
-                                               int S, float iqx, float iqy, float iqz,
-                                               float* __restrict__ P, BsAxes bx,
-                                               const int32_t* __restrict__ own) {
-  const int n = cntp[0];
+// kDirect: grid coordinates from the positions (stand-alone sums of few
+// points, one copy), else from X.
+template <bool kUniform, bool kDirect>
+__global__ __launch_bounds__(256) void k_bs_f32(BsPts in, const uint32_t* __restrict__ X,
+                                               int32_t* __restrict__ cntp, int n_arg,
+                                               long long nc, int S, float iqx, float iqy,
+                                               float iqz, float* __restrict__ P, BsAxes bx) {
+  const int n = cntp ? cntp[0] : n_arg;
   // work counter: (target, segment) pairs of this sum
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && n > 2)
+  if (cntp && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && n > 2)
     *(long long*)(cntp + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
   const int j0 = blockIdx.x * kTargets;
   if (j0 >= n) return;
@@ -186,20 +198,33 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform per wave
   const int j = j0 + lane;
   const bool valid = j < n;
+  const int jc = min(j, n - 1);  // lanes beyond the points repeat the last one, unwritten
   const int copy = blockIdx.y / S;
-  const uint32_t* __restrict__ Xs = X + (long long)copy * 3 * ncap;  // this copy's sources
+  const uint32_t* __restrict__ Xs = X + (long long)copy * 3 * nc;  // this copy's sources
   const int per = (n + S - 1) / S;
   const int kb = (blockIdx.y - copy * S) * per;
   const int ke = min(n, kb + per);
-  const uint32_t xt = valid ? X[j] : 0u;
-  const uint32_t yt = valid ? X[ncap + j] : 0u;
-  const uint32_t zt = valid ? X[2 * ncap + j] : 0u;
+  uint32_t xt, yt, zt;
+  if (kDirect) {
+    xt = bs_grid_f32(in.Y[jc * in.sj], bx, 0);
+    yt = bs_grid_f32(in.Y[in.sa + jc * in.sj], bx, 1);
+    zt = bs_grid_f32(in.Y[2 * in.sa + jc * in.sj], bx, 2);
+  } else {
+    xt = X[jc];
+    yt = X[nc + jc];
+    zt = X[2 * nc + jc];
+  }
   // the target's own two segments are excluded in copy 0 and, for the end
   // of an open line, in the copy mirrored in its wall
-  const int oc = (valid && own) ? own[j] : 0;
-  const bool exl = valid && (copy == 0 || copy == oc);
-  const int pj = exl ? prv[j] : -1;
+  bool exl = valid && copy == 0;
+  if (copy > 0 && valid && (in.nxt[jc] == jc || in.prv[jc] == jc)) {
+    double y[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
+    exl = bs_own_copy(y, bx) == copy;
+  }
   const int jj = exl ? j : -1;
+  const bool exany = __any(exl);
   __shared__ BsSrc src[kTile];
   __shared__ float red[3][3][kTargets];  // sums of waves 1..3
   float ax = 0.f, ay = 0.f, az = 0.f;
@@ -207,38 +232,46 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
     const int k = t0 + threadIdx.x;
     if (k < ke) {
       // segment vector: wrapped grid difference to the successor
-      const int kn = nxt[k];
-      const uint32_t ax0 = Xs[k], ay0 = Xs[ncap + k], az0 = Xs[2 * ncap + k];
-      float ex = (float)(int)(Xs[kn] - ax0);
-      float ey = (float)(int)(Xs[ncap + kn] - ay0);
-      float ez = (float)(int)(Xs[2 * ncap + kn] - az0);
+      const int kn = min(max(in.nxt[k], 0), n - 1);
+      uint32_t x0[3], x1[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (kDirect) {
+          x0[a] = bs_grid_f32(in.Y[a * in.sa + k * in.sj], bx, a);
+          x1[a] = bs_grid_f32(in.Y[a * in.sa + kn * in.sj], bx, a);
+        } else {
+          x0[a] = Xs[a * nc + k];
+          x1[a] = Xs[a * nc + kn];
+        }
+      }
+      float ex = (float)(int)(x1[0] - x0[0]);
+      float ey = (float)(int)(x1[1] - x0[1]);
+      float ez = (float)(int)(x1[2] - x0[2]);
       if (!kUniform) {
         ex *= iqx;
         ey *= iqy;
         ez *= iqz;
       }
       BsSrc g;
-      g.x = ax0;
-      g.y = ay0;
-      g.z = az0;
+      g.x = x0[0];
+      g.y = x0[1];
+      g.z = x0[2];
       g.q = ex * ex + ey * ey + ez * ez;
       g.dx = 2.0f * ex;
       g.dy = 2.0f * ey;
       g.dz = 2.0f * ez;
-      g.pad = 0.0f;
+      g.kn = kn;
       src[threadIdx.x] = g;
     }
     __syncthreads();
     int lo, hi;
     wave_range(min(kTile, ke - t0), w, lo, hi);
     if (lo < hi) {
-      const int s0 = t0 + lo, s1 = t0 + hi;
-      const bool hit = exl && ((jj >= s0 && jj < s1) || (pj >= s0 && pj < s1));
-      if (__any(hit))
-        bs_tile_f32<true, kUniform>(src + lo, hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax,
+      if (exany && bs_hit(src, t0, lo, hi, j0, kTargets))
+        bs_tile_f32<true, kUniform>(src + lo, hi - lo, t0 + lo, xt, yt, zt, iqx, iqy, iqz, jj, ax,
                                     ay, az);
       else
-        bs_tile_f32<false, kUniform>(src + lo, hi - lo, s0, xt, yt, zt, iqx, iqy, iqz, jj, pj, ax,
+        bs_tile_f32<false, kUniform>(src + lo, hi - lo, t0 + lo, xt, yt, zt, iqx, iqy, iqz, jj, ax,
                                      ay, az);
     }
     __syncthreads();
@@ -251,10 +284,10 @@ __global__ __launch_bounds__(256) void k_bs_f32(const uint32_t* __restrict__ X,
   __syncthreads();
   if (w == 0 && valid) {
     const float sg = bx.sign[copy];
-    float* out = P + (long long)blockIdx.y * 3 * ncap;
+    float* out = P + (long long)blockIdx.y * 3 * nc;
     out[j] = sg * (((ax + red[0][0][lane]) + red[1][0][lane]) + red[2][0][lane]);
-    out[ncap + j] = sg * (((ay + red[0][1][lane]) + red[1][1][lane]) + red[2][1][lane]);
-    out[2 * ncap + j] = sg * (((az + red[0][2][lane]) + red[1][2][lane]) + red[2][2][lane]);
+    out[nc + j] = sg * (((ay + red[0][1][lane]) + red[1][1][lane]) + red[2][1][lane]);
+    out[2 * nc + j] = sg * (((az + red[0][2][lane]) + red[1][2][lane]) + red[2][2][lane]);
   }
 }
 
@@ -421,13 +454,7 @@ __global__ __launch_bounds__(256) void k_bs_f64(BsPts in, int32_t* __restrict__ 
     int lo, hi;
     wave_range(min(kTile, ke - t0), w, lo, hi);
     if (lo < hi) {
-      // does this wave's quarter (at most 64 sources) start or end at one of
-      // the block's targets?
-      bool hit = false;
-      if (lane < hi - lo)
-        hit = (uint32_t)(t0 + lo + lane - j0) < (uint32_t)kT ||
-              (uint32_t)(src[lo + lane].kn - j0) < (uint32_t)kT;
-      if (exany && __any(hit))
+      if (exany && bs_hit(src, t0, lo, hi, j0, kT))
         bs_tile_f64<kPer, NT, true>(src + lo, hi - lo, t0 + lo, tg, bx.invq_d[0], bx.invq_d[1],
                                     bx.invq_d[2]);
       else
@@ -459,52 +486,20 @@ __global__ __launch_bounds__(256) void k_bs_f64(BsPts in, int32_t* __restrict__ 
 }
 
 // ---- standalone sum (positions and links from the caller, no run)
-
-// FP32: links and grid coordinates of a caller's filaments: next is clamped
-// into [0, n) (an invalid permutation gives meaningless velocities, never an
-// access out of bounds) and inverted into prev; grid coordinates as k_prep,
-// from [n][3] positions.  Thread 0 writes the point count and clears the pair
-// counter.
-// prv[j] = j: the first point of an open line keeps it (no real link to it)
-__global__ void k_solo_init(int32_t* __restrict__ prv, int n) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n) prv[j] = j;
-}
-
-__global__ void k_solo_prep(const double* __restrict__ xyz, const int32_t* __restrict__ next,
-                            int n, BsAxes ax, int32_t* __restrict__ cnt,
-                            uint32_t* __restrict__ X, int32_t* __restrict__ nxt,
-                            int32_t* __restrict__ prv) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j == 0) {
-    cnt[0] = n;
-    for (int i = 1; i < 32; ++i) cnt[i] = 0;
-  }
-  if (j >= n) return;
-  const int k = min(max(next[j], 0), n - 1);
-  nxt[j] = k;
-  if (k != j) prv[k] = j;  // the last point of an open line links to itself
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double s = floor((xyz[3LL * j + a] + ax.off[a]) * ax.q[a]);
-    X[(long long)a * n + j] = ax.periodic[a] ? (uint32_t)(long long)s
-                                             : (uint32_t)(int)(long long)s;
-  }
-}
-
+//
 // v[j][a] = scale * (sum over the S chunk partials of target j, in chunk
-// order, in FP64).
+// order, in FP64); one thread per (a, j).
 template <class PT>
-__global__ void k_solo_sum(const PT* __restrict__ P, int S, int n, double scale,
-                           double* __restrict__ v) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    double t = 0.0;
-    for (int c = 0; c < S; ++c) t += (double)P[((long long)c * 3 + a) * n + j];
-    v[3LL * j + a] = t * scale;
-  }
+__global__ __launch_bounds__(256) void k_solo_sum(const PT* __restrict__ P, int S, int n,
+                                                  double scale, double* __restrict__ v) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long n3 = 3LL * n;
+  if (i >= n3) return;
+  double t = 0.0;
+#pragma unroll 8
+  for (int c = 0; c < S; ++c) t += (double)P[c * n3 + i];
+  const long long a = i / n;
+  v[3 * (i - a * n) + a] = t * scale;
 }
 
 }  // namespace
@@ -579,20 +574,24 @@ BsAxes bs_make_axes(const int n[3], const int wall[3], bool images) {
   return ax;
 }
 
-// Source chunks S: about 16384 blocks over the target blocks, or up to
-// 32768 while every chunk keeps at least 1024 sources (large point counts:
-// the launch's tail shortens), at least 256 sources per chunk (64 per
-// wave), at most 256 chunks; the chunk partials are added by the finalize
-// kernel.  (At 1.2e4 points 512 and 1024 sources per chunk measured 1.5%
-// and 6% slower per step, 128 and 192 no faster; at 1.0e5 points 14 chunks
-// instead of 7 measured 1.1% faster, at 5e4 points 28 instead of 14 0.9%.)
-int bs_chunks(long long ncap) {
+// Source chunks S of each of the sum's copies: about 16384 blocks over the
+// target blocks, or up to 32768 while every chunk keeps at least 1024
+// sources (large point counts: the launch's tail shortens), at least 256
+// sources per chunk (64 per wave), at most 256 chunks; the chunk partials
+// are added by the finalize kernel.  (At 1.2e4 points 512 and 1024 sources
+// per chunk measured 1.5% and 6% slower per step, 128 and 192 no faster; at
+// 1.0e5 points 14 chunks instead of 7 measured 1.1% faster, at 5e4 points 28
+// instead of 14 0.9%.)  Few points leave the chip idle under that rule, and
+// their time is the longest block's: up to 32 chunks in all (what the
+// finalize kernel loads at once) while each keeps 32 sources (2000 points,
+// the sum alone: 7 chunks 17.7 us, 13 12.0, 30 10.2, 60 9.4).
+int bs_chunks(long long ncap, int copies) {
   const long long tb = (ncap + kTargets - 1) / kTargets;
   const long long t = tb > 0 ? tb : 1;
   long long S = 16384 / t;
   const long long wide = std::min(32768 / t, ncap / 1024);
   if (wide > S) S = wide;
-  const long long maxS = ncap / 256;
+  const long long maxS = std::max(ncap / 256, std::min<long long>(32 / copies, ncap / 32));
   if (S > maxS) S = maxS;
   if (S < 1) S = 1;
   if (S > 256) S = 256;
@@ -602,8 +601,8 @@ int bs_chunks(long long ncap) {
 hipError_t bs_prep(Run& r, const double* Y) {
   if (r.prec == VLB_F64) return hipSuccess;  // that sum reads the positions
   const int nb = (int)((r.ncap + 255) / 256);
-  hipLaunchKernelGGL(k_prep, dim3(nb), dim3(256), 0, r.stream, Y, r.nxt, r.prv, r.cnt, r.ncap,
-                     r.bsax, r.bsX, r.bsax.copies > 1 ? r.bsown : nullptr);
+  hipLaunchKernelGGL(k_prep, dim3(nb), dim3(256), 0, r.stream,
+                     BsPts{Y, r.ncap, 1, r.nxt, r.prv}, r.cnt, 0, r.ncap, r.bsax, r.bsX);
   return hipGetLastError();
 }
 
@@ -630,28 +629,29 @@ hipError_t bs_f64(const BsPts& in, int32_t* cnt, long long n, int S, double* P, 
                            : launch_bs_f64<1>(in, cnt, n, S, P, ax, stream);
 }
 
+// FP32 sum; X the grid coordinates, or null: from the positions.
+hipError_t bs_f32(const BsPts& in, const uint32_t* X, int32_t* cnt, long long n, int S, float* P,
+                  const BsAxes& ax, hipStream_t stream) {
+  const int tb = (int)((n + kTargets - 1) / kTargets);
+  auto kern = ax.uniform ? (X ? k_bs_f32<true, false> : k_bs_f32<true, true>)
+                         : (X ? k_bs_f32<false, false> : k_bs_f32<false, true>);
+  hipLaunchKernelGGL(kern, dim3(tb, S * ax.copies), dim3(256), 0, stream, in, X, cnt, (int)n, n, S,
+                     ax.invq_f[0], ax.invq_f[1], ax.invq_f[2], P, ax);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t bs_sum(Run& r, const double* Y) {
-  const int tb = (int)((r.ncap + kTargets - 1) / kTargets);
-  dim3 grid(tb, r.bsS * r.bsax.copies);
   hipEvent_t b = nullptr;
   time_begin(r, 0, &b);
-  const int32_t* own = r.bsax.copies > 1 ? r.bsown : nullptr;
-  hipError_t e = hipSuccess;
-  if (r.prec == VLB_F64)
-    e = bs_f64(BsPts{Y, r.ncap, 1, r.nxt, r.prv}, r.cnt, r.ncap, r.bsS, (double*)r.bsP, r.bsax,
-               r.stream);
-  else if (r.bsax.uniform)
-    hipLaunchKernelGGL(k_bs_f32<true>, grid, dim3(256), 0, r.stream, r.bsX, r.nxt,
-                       r.prv, r.cnt, r.ncap, r.bsS, r.bsax.invq_f[0], r.bsax.invq_f[1],
-                       r.bsax.invq_f[2], (float*)r.bsP, r.bsax, own);
-  else
-    hipLaunchKernelGGL(k_bs_f32<false>, grid, dim3(256), 0, r.stream, r.bsX, r.nxt,
-                       r.prv, r.cnt, r.ncap, r.bsS, r.bsax.invq_f[0], r.bsax.invq_f[1],
-                       r.bsax.invq_f[2], (float*)r.bsP, r.bsax, own);
+  const BsPts in{Y, r.ncap, 1, r.nxt, r.prv};
+  const hipError_t e =
+      r.prec == VLB_F64
+          ? bs_f64(in, r.cnt, r.ncap, r.bsS, (double*)r.bsP, r.bsax, r.stream)
+          : bs_f32(in, r.bsX, r.cnt, r.ncap, r.bsS, (float*)r.bsP, r.bsax, r.stream);
   time_end(r, 0, b);
-  return e == hipSuccess ? hipGetLastError() : e;
+  return e;
 }
 
 int bs_check_desc(const vlb_bs_desc* d, int64_t n, std::string& msg) {
@@ -665,19 +665,20 @@ int bs_check_desc(const vlb_bs_desc* d, int64_t n, std::string& msg) {
   return VLB_OK;
 }
 
-// Standalone sum: the chunk count, scratch layout and launches.  The
-// chunks are capped at kSoloChunks, so that the scratch of the largest
-// allocation-free call stays small.
-constexpr int kSoloChunks = 8;
+// Standalone sum: the chunk count, scratch layout and launches.  Up to the
+// size of the largest allocation-free call (16384 points) the chunk partials
+// are kept within 4 MB (FP64 10 chunks there, 32 from 5461 points down).
+constexpr long long kSoloPartialBytes = 4LL << 20;
 
-int bs_solo_chunks(long long n) {
-  const int S = bs_chunks(n);
-  return S < kSoloChunks ? S : kSoloChunks;
+int bs_solo_chunks(long long n, size_t fe) {
+  const int S = bs_chunks(n, 1);
+  const long long most = std::max(1LL, kSoloPartialBytes / (3 * n * (long long)fe));
+  return n <= 16384 && S > most ? (int)most : S;
 }
 
 size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b) {
   const size_t fe = prec == VLB_F64 ? 8 : 4;
-  const int S = bs_solo_chunks(n);
+  const int S = bs_solo_chunks(n, fe);
   size_t off = 0;
   auto take = [&](size_t bytes) -> void* {
     off = (off + 255) / 256 * 256;
@@ -686,12 +687,7 @@ size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b) {
     return p;
   };
   BsSolo s{};
-  s.cnt = (int32_t*)take(32 * sizeof(int32_t));
-  if (prec != VLB_F64) {
-    s.X = (uint32_t*)take(3 * (size_t)n * sizeof(uint32_t));
-    s.nxt = (int32_t*)take((size_t)n * sizeof(int32_t));
-    s.prv = (int32_t*)take((size_t)n * sizeof(int32_t));
-  }
+  if (prec != VLB_F64 && n > kDirectPoints) s.X = (uint32_t*)take(3 * (size_t)n * sizeof(uint32_t));
   s.P = take((size_t)S * 3 * n * fe);
   s.S = S;
   if (b) *b = s;
@@ -701,30 +697,23 @@ size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b) {
 hipError_t bs_solo(const BsAxes& ax, int prec, long long n, const double* xyz,
                    const int32_t* next, double kappa, double* v, const BsSolo& b,
                    hipStream_t stream) {
-  const int nb = (int)((n + 255) / 256);
-  const int tb = (int)((n + kTargets - 1) / kTargets);
-  const dim3 grid(tb, b.S);
+  const BsPts in{xyz, 1, 3, next, nullptr};
+  const int nb3 = (int)((3 * n + 255) / 256);
   const double s = kappa / (4.0 * M_PI);
+  hipError_t e;
   if (prec == VLB_F64) {
-    const hipError_t e = bs_f64(BsPts{xyz, 1, 3, next, nullptr}, nullptr, n, b.S, (double*)b.P, ax,
-                                stream);
+    e = bs_f64(in, nullptr, n, b.S, (double*)b.P, ax, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_solo_sum<double>, dim3(nb), dim3(256), 0, stream, (const double*)b.P,
+    hipLaunchKernelGGL(k_solo_sum<double>, dim3(nb3), dim3(256), 0, stream, (const double*)b.P,
                        b.S, (int)n, s, v);
   } else {
-    hipLaunchKernelGGL(k_solo_init, dim3(nb), dim3(256), 0, stream, b.prv, (int)n);
-    hipLaunchKernelGGL(k_solo_prep, dim3(nb), dim3(256), 0, stream, xyz, next, (int)n, ax, b.cnt,
-                       b.X, b.nxt, b.prv);
-    if (ax.uniform)
-      hipLaunchKernelGGL(k_bs_f32<true>, grid, dim3(256), 0, stream, b.X, b.nxt, b.prv, b.cnt,
-                         n, b.S, ax.invq_f[0], ax.invq_f[1], ax.invq_f[2], (float*)b.P, ax,
-                         nullptr);
-    else
-      hipLaunchKernelGGL(k_bs_f32<false>, grid, dim3(256), 0, stream, b.X, b.nxt, b.prv, b.cnt,
-                         n, b.S, ax.invq_f[0], ax.invq_f[1], ax.invq_f[2], (float*)b.P, ax,
-                         nullptr);
-    hipLaunchKernelGGL(k_solo_sum<float>, dim3(nb), dim3(256), 0, stream, (const float*)b.P,
-                       b.S, (int)n, ax.uniform ? s * ax.q[0] : s, v);
+    if (b.X)
+      hipLaunchKernelGGL(k_prep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, in,
+                         nullptr, (int)n, n, ax, b.X);
+    e = bs_f32(in, b.X, nullptr, n, b.S, (float*)b.P, ax, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_solo_sum<float>, dim3(nb3), dim3(256), 0, stream, (const float*)b.P, b.S,
+                       (int)n, ax.uniform ? s * ax.q[0] : s, v);
   }
   return hipGetLastError();
 }

@@ -522,11 +522,10 @@ struct Run {
   // Biot-Savart
   uint32_t* bsX = nullptr;  // 3 * ncap grid coordinates
   void* bsP = nullptr;      // S * 3 * ncap partial sums
-  int32_t* bsown = nullptr;
   // far-field approximation of the non-local sum (vor.ff_cell > 0): its
   // workspace and chunk count (its partials go to bsP)
   void* ffws = nullptr;
-  int ffS = 0; // ncap, with image copies: the copy mirrored in an end's own wall
+  int ffS = 0;
   int bsS = 1;
 
   // counters on the device: [0] n points, [1] n touched slots,
@@ -615,20 +614,15 @@ hipError_t diag_cylindrical(Run& r, const double point[3], const double unit_dir
 
 BsAxes bs_make_axes(const int n[3], const int wall[3], bool images);
 
-// Scratch of the standalone Biot-Savart sum (vlb_biot_savart*): point
-// count and pair counter; FP32 also grid coordinates and sanitised links;
-// chunk partials.
+// Scratch of the standalone Biot-Savart sum (vlb_biot_savart*): FP32 grid
+// coordinates (null: formed in the sum) and the chunk partials.
 struct BsSolo {
-  int32_t* cnt;
   uint32_t* X;
-  int32_t* nxt;
-  int32_t* prv;
   void* P;
   int S;
 };
 constexpr long long kSoloMaxPoints = 1LL << 26;
 int bs_check_desc(const vlb_bs_desc* d, int64_t n, std::string& msg);
-int bs_solo_chunks(long long n);
 size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b);
 hipError_t bs_solo(const BsAxes& ax, int prec, long long n, const double* xyz,
                    const int32_t* next, double kappa, double* v, const BsSolo& b,
@@ -649,7 +643,7 @@ hipError_t ff_solo(const vlb_bs_desc* d, const vlb_ff_params* p, long long n, co
                    const int32_t* next, double* v, void* ws, hipStream_t stream);
 hipError_t bs_prep(Run& r, const double* Y);
 hipError_t bs_sum(Run& r, const double* Y);
-int bs_chunks(long long ncap);
+int bs_chunks(long long ncap, int copies);
 
 // One finalize of a filament stage: stage of the Runge-Kutta method (1..rk),
 // first = the first stage of the step's first substep (leaves the stage-1

@@ -1,7 +1,7 @@
 """The stand-alone sum over every route it can take: each set of closed axes
 (the FP64 kernel is specialised on it), point counts on both sides of the
-count from which it takes two targets per lane, ragged last blocks and
-tiles.  Against the oracle's sum at sampled targets, in FP64."""
+count from which it takes two targets per lane and of the one up to which
+the FP32 sum reads positions, ragged last blocks and tiles.  Against the oracle's sum at sampled targets, in FP64."""
 
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ if not torch.cuda.is_available():
 
 import paper_2108_04435_amd as vlb  # noqa: E402
 
-# FP64: about 30 roundings of 1.1e-16 per pair and a sum of up to 5e3 terms
+# FP64: about 30 roundings of 1.1e-16 per pair and a sum of up to 1.7e4 terms
 # whose magnitudes exceed the result's a few times over.  FP32: the same
 # count of 6e-8.
 TOL = {"f64": 1e-12, "f32": 1e-5}
@@ -64,6 +64,6 @@ def test_every_set_of_closed_axes(mask):
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-@pytest.mark.parametrize("n", [3, 63, 65, 257, 1023, 4095, 4096, 4225])
+@pytest.mark.parametrize("n", [3, 63, 65, 257, 1023, 4096, 4097, 16383, 16385])
 def test_point_counts(n, precision):
     _check(n, (64, 64, 64), (False, True, False), precision)
