@@ -131,13 +131,13 @@ size_t layout(Run& r, char* base) {
   const size_t fe = r.prec == VLB_F64 ? 8 : 4;
   r.pops = B.take(19 * cells * elt_size(r.prec));
   r.force = B.take(3 * cells * fe);
-  // superflow per cross-section along the flow axis; along x or y also the
-  // per-z-slice partial sums of its mean
+  // superflow per cross-section along the flow axis, and the partial sums of
+  // its mean
   const int mba = r.vor.mass_balance_axis;
   const int nmb = mba == 0 ? r.geom.nx : (mba == 1 ? r.geom.ny : r.geom.nz);
   r.Vs = (double*)B.take(nmb * sizeof(double));
   r.Vs_next = (double*)B.take(nmb * sizeof(double));
-  r.mbP = (double*)B.take((r.vor.mass_balance && mba != 2 ? (size_t)r.geom.nz * nmb : 0) * sizeof(double));
+  r.mbP = (double*)B.take(lbm_mb_doubles(r) * sizeof(double));
   r.diag = (double*)B.take((8 + (size_t)kSlabChunks * r.geom.nz) * sizeof(double));
   r.seg = (double*)B.take(3 * (size_t)nc * sizeof(double));
   r.fric = (double*)B.take((2 * (size_t)r.geom.nz + 1) * sizeof(double));
@@ -225,6 +225,22 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   r.key_bits = bits_for(ext);  // pad key 2^bits - 1 >= ext
   if (r.key_bits > 32) r.key_bits = 32;
   r.nbins_table = (long long)ext;
+  // Which part of a step is the longer one, by its work at the rates they
+  // reach: pairs of the Biot-Savart sums (1.5e12 per second in FP32, half of
+  // that in FP64; with the far field 28 ns per point and sum) against the
+  // bytes of the update and the moments at 5 TB/s.  128x128x256 FP32 with
+  // 2e3 points (30 us of pairs, 210 us of lattice): see the moments kernel;
+  // counterflow (64x64x256, 9.4e3 points: 480 against 53 us) keeps the narrow
+  // grid, which the full one beside the sums lengthened by 25 us a step.
+  {
+    const double sums = (double)r.vor.rk_stages * r.vor.vfm_substeps;
+    const double nn = (double)r.ncap;
+    const double fil = r.vor.ff_cell > 0
+                           ? sums * nn * 28e-9
+                           : sums * nn * nn * r.bsax.copies / (r.prec == VLB_F64 ? 0.75e12 : 1.5e12);
+    const double latt = (double)r.cells * (57.0 * elt_size(r.prec) + (r.prec == VLB_F64 ? 48 : 24)) / 5e12;
+    r.narrow_steps = fil > latt;
+  }
   // reconnection bins of edge >= reconnect distance
   if (vor->reconnect) {
     const double h0 = vor->reconnect_dist * (1.0 + 1e-9);
@@ -527,9 +543,9 @@ struct OnStream {
 // superflow); the spreading needs finalize 1, which leaves it the point
 // forces, bin keys, stencil offsets and point count, so the spreading reads
 // nothing the later stages or the topology rewrite.  The LBM update follows
-// the spreading on the side stream, launched on a narrow grid (two blocks
-// per CU) so that it leaves most CU slots to the filament kernels beside
-// it.  The next step's moments follow the LBM update on the side stream
+// the spreading on the side stream; where the filament part is the longer
+// one it is launched on a narrow grid (two blocks per CU), which leaves most
+// CU slots to the filament kernels beside it.  The next step's moments follow the LBM update on the side stream
 // and write the second velocity field (this step's stages read the first;
 // the two swap at the end of the step).  The first step of a call forks
 // the side stream from main and computes its own moments; the last one
@@ -593,10 +609,10 @@ int one_step(vlb_run* h, bool first, bool last) {
       HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fin1, 0));
       OnStream on(r, S);
       if (spread) HIP_OR_FAIL(h, fil_spread(r));
-      // the LBM update on a narrow grid beside the Biot-Savart sums, then
-      // the moments of f^(n+1) into the next step's field (the stages of
-      // this step still read the current one)
-      r.lbm_narrow = true;
+      // the LBM update (on a narrow grid where the filament part is the
+      // longer one), then the moments of f^(n+1) into the next step's field
+      // (the stages of this step still read the current one)
+      r.lbm_narrow = r.narrow_steps;
       hipError_t le = lbm_step(r);
       if (le == hipSuccess && !last) {
         std::swap(r.ub, r.ub_next);

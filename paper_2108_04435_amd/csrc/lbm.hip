@@ -510,21 +510,43 @@ __global__ void k_read_force(const T* __restrict__ F, long long n, double* out) 
 
 // Bare normal-fluid velocity u_b = sum(c f)/sum(f) of every node (velocity
 // planes applied), written once per step for the interpolation onto the
-// filaments, fused (flow along z) with the mean of u_z over each z slice
-// that the mass-balance superflow needs (Sec. III.C, Eq. mass cons): one
-// block per slice walks the slice in tiles (x fastest), each thread adds
-// its nodes' u_z in order, the block adds the threads' sums in a fixed
-// tree, and Vs[z] = scale * sum.  Vs is null otherwise.
+// filaments, fused (flow along z) with the sum of u_z over each z slice that
+// the mass-balance superflow needs (Sec. III.C, Eq. mass cons).  Item
+// (z, part) is a range of y rows of slice z: the block of 256 threads walks
+// it in tiles (x fastest), each thread adds its nodes' u_z in order and the
+// block adds the threads in a fixed tree.  The parts depend on the lattice
+// alone, so the sums do not depend on the grid, which may be narrower than
+// the items.  One part per slice: P[z] = scale * sum is the superflow; else
+// P[z * parts + part] the part's sum (k_mb_total adds them).  P is null
+// without mass balance along z.
+//
+// What bounds it: HBM (19 populations read, three velocities written), given
+// enough waves in flight: with one block per slice, 128x128x256 FP32 took
+// 94 to 110 us beside the filament kernels (3.4 TB/s); parts of at most
+// kMomentNodes nodes keep 8 blocks on every CU.
+constexpr int kMomentNodes = 2048;
+
+inline int moment_parts(const Geom& g) {
+  const long long ns = (long long)g.nx * g.ny;
+  const long long p = (ns + kMomentNodes - 1) / kMomentNodes;
+  return (int)(p > g.ny ? g.ny : p);
+}
+
 template <class S, class UT>
-__global__ __launch_bounds__(1024) void k_moments(const S* __restrict__ M, Geom g, int parity,
-                                                 UT* __restrict__ ub, double scale,
-                                                 double* __restrict__ Vs) {
-  const int z = blockIdx.x;
-  double uzv = 0.0;
-  for (int y0 = 0; y0 < g.ny; y0 += blockDim.y)
-    for (int x0 = 0; x0 < g.nx; x0 += blockDim.x) {
-      const int x = x0 + threadIdx.x, y = y0 + threadIdx.y;
-      if (x < g.nx && y < g.ny) {
+__global__ __launch_bounds__(256) void k_moments(const S* __restrict__ M, Geom g, int parity,
+                                                UT* __restrict__ ub, double scale, int parts,
+                                                int items, double* __restrict__ P) {
+  __shared__ double red[256];
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+  const int nt = blockDim.x * blockDim.y;
+  const int rows = (g.ny + parts - 1) / parts;
+  for (int hw = blockIdx.x; hw < items; hw += gridDim.x) {
+    const int it = xcd_remap(hw, items);
+    const int z = it / parts;
+    const int yb = (it - z * parts) * rows, ye = min(g.ny, yb + rows);
+    double uzv = 0.0;
+    for (int y = yb + threadIdx.y; y < ye; y += blockDim.y)
+      for (int x = threadIdx.x; x < g.nx; x += blockDim.x) {
         double rho, ux, uy, uz;
         node_rho_u<S>(M, g, parity, x, y, z, rho, ux, uy, uz);
         const long long c = ((long long)z * g.ny + y) * g.nx + x;
@@ -533,18 +555,16 @@ __global__ __launch_bounds__(1024) void k_moments(const S* __restrict__ M, Geom 
         ub[2 * g.cells + c] = (UT)uz;
         uzv += uz;
       }
-    }
-  if (!Vs) return;
-  __shared__ double red[1024];
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-  const int nt = blockDim.x * blockDim.y;
-  red[tid] = uzv;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if (tid < s && tid + s < nt) red[tid] += red[tid + s];
+    if (!P) continue;
+    red[tid] = uzv;
     __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+      if (tid < s && tid + s < nt) red[tid] += red[tid + s];
+      __syncthreads();
+    }
+    if (tid == 0) P[it] = parts == 1 ? scale * red[0] : red[0];
+    __syncthreads();  // the next item writes red
   }
-  if (tid == 0) Vs[z] = scale * red[0];
 }
 
 // Mass balance along x or y (flow axis a): for each z slice and each node
@@ -567,12 +587,13 @@ __global__ void k_mb_partial(const UT* __restrict__ ua, Geom g, int axis, double
   P[(long long)z * n + i] = s;
 }
 
-__global__ void k_mb_total(const double* __restrict__ P, int nz, int n, double scale,
-                           double* __restrict__ Vs) {
+// Vs[i] = scale * the sum of k values P[i si + j sj] in ascending j.
+__global__ void k_mb_total(const double* __restrict__ P, int k, int n, int si, int sj,
+                           double scale, double* __restrict__ Vs) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double s = 0.0;
-  for (int z = 0; z < nz; ++z) s += P[(long long)z * n + i];
+  for (int j = 0; j < k; ++j) s += P[(long long)i * si + (long long)j * sj];
   Vs[i] = scale * s;
 }
 
@@ -633,6 +654,9 @@ inline int blocks_for(long long n, int b) { return (int)((n + b - 1) / b); }
 // from one step to the next).
 constexpr double kStreamBytes = 192.0 * (1 << 20);
 
+// Grid of a lattice kernel beside longer filament kernels: two blocks per CU.
+constexpr int kNarrowBlocks = 512;
+
 template <class S>
 hipError_t launch_collide(Run& r) {
   using T = typename Store<S>::T;
@@ -647,10 +671,10 @@ hipError_t launch_collide(Run& r) {
   // the spread force field exists once filaments were seeded into a coupled run
   const T* F = (r.vor.coupling && r.has_points) ? (const T*)r.force : nullptr;
   dim3 blk(bx, by);
-  // beside the filament kernels the update runs on a narrow grid (two
-  // blocks per CU), leaving most CU slots to the other stream
+  // beside the filament kernels the update runs on a narrow grid, leaving
+  // most CU slots to the other stream
   int grid = nblk;
-  if (r.lbm_narrow && grid > 512) grid = 512;
+  if (r.lbm_narrow && grid > kNarrowBlocks) grid = kNarrowBlocks;
   // populations far above the last-level cache: non-temporal accesses
   const bool nt = 19.0 * (double)g.cells * sizeof(S) > kStreamBytes;
   // odd passes: 32-bit slot offsets when the population array spans less than 4 GiB
@@ -660,7 +684,7 @@ hipError_t launch_collide(Run& r) {
     if (i32 && g.nx == 256 && !g.wall[0] && !g.wall[1]) {
       const int nrb = (g.ny * g.nz + 3) / 4;  // blocks of four rows
       int grid4 = nrb;
-      if (r.lbm_narrow && grid4 > 512) grid4 = 512;
+      if (r.lbm_narrow && grid4 > kNarrowBlocks) grid4 = kNarrowBlocks;
       auto k4 = r.parity == 0 ? (nt ? k_collide_rows4<0, true> : k_collide_rows4<0, false>)
                               : (nt ? k_collide_rows4<1, true> : k_collide_rows4<1, false>);
       hipLaunchKernelGGL(k4, dim3(grid4), dim3(256), 0, r.stream, (__half*)r.pops, (const float*)F,
@@ -785,38 +809,51 @@ hipError_t lbm_read_force(Run& r, double* out) {
   return hipGetLastError();
 }
 
+size_t lbm_mb_doubles(const Run& r) {
+  if (!r.vor.mass_balance) return 0;
+  const int axis = r.vor.mass_balance_axis;
+  const Geom& g = r.geom;
+  return (size_t)g.nz * (axis == 0 ? g.nx : (axis == 1 ? g.ny : moment_parts(g)));
+}
+
 hipError_t lbm_moments(Run& r) {
   const Geom& g = r.geom;
   const int bx = g.nx < 64 ? g.nx : 64;
-  // beside the filament kernels: 256 threads per slice block, else 1024
-  int by = (r.lbm_narrow ? 256 : 1024) / bx;
+  int by = 256 / bx;
   if (by < 1) by = 1;
   if (by > g.ny) by = g.ny;
   dim3 blk(bx, by);
-  // flow along z: the slice means come with the moments (one block per z
-  // slice); along x or y: two small passes over u_a afterwards
+  const int parts = moment_parts(g);
+  const int items = g.nz * parts;
+  int grid = items;
+  if (r.lbm_narrow && grid > kNarrowBlocks) grid = kNarrowBlocks;
+  // flow along z: the slice sums come with the moments; along x or y: two
+  // small passes over u_a afterwards
   const int axis = r.vor.mass_balance_axis;
   const int n = axis == 0 ? g.nx : (axis == 1 ? g.ny : g.nz);
-  double* Vs = (r.vor.mass_balance && axis == 2) ? r.Vs : nullptr;
+  const bool mbz = r.vor.mass_balance && axis == 2;
+  double* P = mbz ? (parts == 1 ? r.Vs : r.mbP) : nullptr;
   const double scale = -(1.0 / r.vor.rho_s_over_rho_n) / ((double)g.cells / n);
   switch (r.prec) {
     case VLB_F64:
-      hipLaunchKernelGGL((k_moments<double, double>), dim3(g.nz), blk, 0, r.stream, (const double*)r.pops, g, r.parity, (double*)r.ub, scale, Vs);
+      hipLaunchKernelGGL((k_moments<double, double>), dim3(grid), blk, 0, r.stream, (const double*)r.pops, g, r.parity, (double*)r.ub, scale, parts, items, P);
       break;
     case VLB_F32:
-      hipLaunchKernelGGL((k_moments<float, float>), dim3(g.nz), blk, 0, r.stream, (const float*)r.pops, g, r.parity, (float*)r.ub, scale, Vs);
+      hipLaunchKernelGGL((k_moments<float, float>), dim3(grid), blk, 0, r.stream, (const float*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P);
       break;
     default:
-      hipLaunchKernelGGL((k_moments<__half, float>), dim3(g.nz), blk, 0, r.stream, (const __half*)r.pops, g, r.parity, (float*)r.ub, scale, Vs);
+      hipLaunchKernelGGL((k_moments<__half, float>), dim3(grid), blk, 0, r.stream, (const __half*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P);
       break;
   }
+  if (mbz && parts > 1)
+    hipLaunchKernelGGL(k_mb_total, dim3((n + 63) / 64), dim3(64), 0, r.stream, (const double*)r.mbP, parts, n, parts, 1, scale, r.Vs);
   if (r.vor.mass_balance && axis != 2) {
     const dim3 pg((n + 63) / 64, g.nz);
     if (r.prec == VLB_F64)
       hipLaunchKernelGGL(k_mb_partial<double>, pg, dim3(64), 0, r.stream, (const double*)r.ub + (long long)axis * g.cells, g, axis, r.mbP);
     else
       hipLaunchKernelGGL(k_mb_partial<float>, pg, dim3(64), 0, r.stream, (const float*)r.ub + (long long)axis * g.cells, g, axis, r.mbP);
-    hipLaunchKernelGGL(k_mb_total, dim3((n + 63) / 64), dim3(64), 0, r.stream, (const double*)r.mbP, g.nz, n, scale, r.Vs);
+    hipLaunchKernelGGL(k_mb_total, dim3((n + 63) / 64), dim3(64), 0, r.stream, (const double*)r.mbP, g.nz, n, 1, n, scale, r.Vs);
   }
   return hipGetLastError();
 }

@@ -494,7 +494,7 @@ struct Run {
   // update while the stages of this step still read ub (swapped at the
   // end of the step)
   double* Vs_next = nullptr;
-  double* mbP = nullptr;       // flow along x or y: per (z, cross-section) partial sums of the mass balance
+  double* mbP = nullptr;       // partial sums of the mass balance
   double* diag = nullptr;      // diagnostics results (8 + kSlabChunks nz doubles)
   double* seg = nullptr;       // diagnostics: z extent and length per segment (3 n_cap doubles)
   double* fric = nullptr;      // alpha(z), alpha'(z) profiles and their on flag (2 nz + 1 doubles)
@@ -576,7 +576,8 @@ struct Run {
   int64_t step = 0;
   int parity = 0;
   int point_parity = 0;     // which of the two point-array sets is current
-  bool lbm_narrow = false;  // LBM update launched beside the filament kernels
+  bool narrow_steps = false;  // in a step, lattice kernels on a narrow grid
+  bool lbm_narrow = false;    // the same, for the launches in progress
   bool has_fields = false;
   bool has_points = false;  // set once filaments were seeded
 
@@ -603,6 +604,7 @@ hipError_t lbm_read_pops(Run& r, double* f);
 hipError_t lbm_read_state(Run& r, void* out);
 hipError_t lbm_read_force(Run& r, double* out);
 hipError_t lbm_moments(Run& r);
+size_t lbm_mb_doubles(const Run& r);  // size of mbP
 hipError_t lbm_flow_stats(Run& r, double* out);
 
 // The per-slab line length is added over this many chunks of the segments.
