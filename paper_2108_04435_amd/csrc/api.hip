@@ -117,12 +117,6 @@ void release_streams(Run& r) {
   }
 }
 
-int bits_for(unsigned long long v) {  // smallest b with v < 2^b
-  int b = 1;
-  while (b < 64 && (v >> b) != 0) ++b;
-  return b;
-}
-
 // Carve the workspace (base == nullptr: only measure).
 size_t layout(Run& r, char* base) {
   Bump B(base);
@@ -155,13 +149,8 @@ size_t layout(Run& r, char* base) {
   r.bsP = B.take(pbytes);
   r.ffws = r.vor.ff_cell > 0 ? B.take(ff_run_bytes(r)) : nullptr;
   r.cnt = (int32_t*)B.take(32 * sizeof(int32_t));
-  r.marked = (uint32_t*)B.take(nc * sizeof(uint32_t));
-  r.keys_a = (uint32_t*)B.take(nc * sizeof(uint32_t));
-  r.keys_b = (uint32_t*)B.take(nc * sizeof(uint32_t));
-  r.vals_a = (int32_t*)B.take(nc * sizeof(int32_t));
-  r.vals_b = (int32_t*)B.take(nc * sizeof(int32_t));
-  r.sort_tmp_bytes = sort_tmp_bytes(nc);
-  r.sort_tmp = B.take(r.sort_tmp_bytes);
+  r.skeys = (uint32_t*)B.take(nc * sizeof(uint32_t));
+  r.bnext = (int32_t*)B.take(nc * sizeof(int32_t));
   {
     const long long nw = (nc + 255) / 256 * 4;  // waves of the per-point grids
     r.wmask = (uint64_t*)B.take(nw * sizeof(uint64_t));
@@ -222,8 +211,6 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   r.ffS = vor->ff_cell > 0 ? ff_run_chunks(r) : 0;
   // spreading bins: lower stencil corner, n (+1 on wall axes) per axis
   const unsigned long long ext = (unsigned long long)(n[0] + g.wall[0]) * (n[1] + g.wall[1]) * (n[2] + g.wall[2]);
-  r.key_bits = bits_for(ext);  // pad key 2^bits - 1 >= ext
-  if (r.key_bits > 32) r.key_bits = 32;
   r.nbins_table = (long long)ext;
   // Which part of a step is the longer one, by its work at the rates they
   // reach: pairs of the Biot-Savart sums (1.5e12 per second in FP32, half of
@@ -418,7 +405,6 @@ int vlb_create_lattice(const vlb_lattice_desc* lat, const vlb_vortex_desc* vor, 
   if (e == hipSuccess) e = hipMemsetAsync(r.fric, 0, (2 * (size_t)r.geom.nz + 1) * sizeof(double), r.stream);
   if (e == hipSuccess) e = hipMemsetAsync(r.pops, 0, 19 * r.cells * elt_size(r.prec), r.stream);
   if (e == hipSuccess) e = hipMemsetAsync(r.bins, 0xFF, (size_t)r.nbins_table * sizeof(int32_t), r.stream);
-  if (e == hipSuccess) e = hipMemsetAsync(r.marked, 0xFF, (size_t)r.ncap * sizeof(uint32_t), r.stream);
   if (e == hipSuccess && r.rc_head)
     e = hipMemsetAsync(r.rc_head, 0xFF, (size_t)r.rc_nbins * sizeof(int32_t), r.stream);
   if (e == hipSuccess) e = hipStreamSynchronize(r.stream);

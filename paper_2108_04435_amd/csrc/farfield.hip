@@ -877,7 +877,7 @@ hipError_t ff_solo(const vlb_bs_desc* d, const vlb_ff_params* p, long long n, co
   while ((1LL << bits) < ax.C[0]) ++bits;
   uint32_t* sk = nullptr;
   int32_t* so = nullptr;
-  hipError_t e = sort_pairs_raw(n, bits, 0, b.stmp, b.ka, b.kb, b.va, b.vb, stream, &sk, &so);
+  hipError_t e = sort_pairs(n, bits, b.stmp, b.ka, b.kb, b.va, b.vb, stream, &sk, &so);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_ff_seg, dim3(nb), dim3(256), 0, stream, so, b.X, b.nxt, b.cnt, n, ax,
                      b.recs);
@@ -940,7 +940,7 @@ hipError_t ff_run_sum(Run& r, const double* Y) {
   while ((1LL << bits) < ax.C[0]) ++bits;
   uint32_t* sk = nullptr;
   int32_t* so = nullptr;
-  hipError_t e = sort_pairs_raw(nc, bits, 0, b.stmp, b.ka, b.kb, b.va, b.vb, stream, &sk, &so);
+  hipError_t e = sort_pairs(nc, bits, b.stmp, b.ka, b.kb, b.va, b.vb, stream, &sk, &so);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_ff_seg, dim3(nb), dim3(256), 0, stream, so, b.X, r.nxt, r.cnt, nc, ax,
                      b.recs);

@@ -4,10 +4,10 @@
 //    fluid, Schwarz line velocity, mutual-friction force and the RK4
 //    bookkeeping of one stage;
 //  * spreading of the point forces onto the lattice, without atomics on
-//    the forces: points are binned by the cell of their stencil's lower
-//    corner with the library's stable radix sort; each touched node is then
+//    the forces: the stage-1 finalize pushes every point on the list of the
+//    cell of its stencil's lower corner (its bin); each touched node is then
 //    owned by exactly one bin and gathers the contributions of the (at most
-//    8) bins around it in a fixed order.
+//    8) bins around it, each bin's points in ascending order.
 #include "vlb_internal.h"
 
 namespace vlb {
@@ -94,11 +94,15 @@ struct FinArgs {
   double* gpt;
   uint32_t* X;      // grid coordinates of the next stage's positions (FP32 sum), or null
   BsAxes ax;
-  // stage 1 with spreading: per point, the bin key and the fractional
-  // stencil offsets of the step's positions, and the point count
+  // stage 1 with spreading: per point, the bin key, the fractional stencil
+  // offsets of the step's positions and its place on the bin's list (which
+  // lists are empty before: the moments kernel clears them), and the point
+  // count
   SpreadGeom sg;
   uint32_t* skeys;  // or null
   double* sfrac;
+  int32_t* bins;    // per bin the last point pushed (-1: none)
+  int32_t* bnext;   // per point the one pushed before it
 };
 
 // Nearest-image separation on the filament axes (wall axes: plain).
@@ -215,7 +219,9 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
     for (int a = 0; a < 3; ++a) s_vn[a][lane] = vn[a];
     if (live && A.skeys) {
       int b[3];
-      A.skeys[j] = base_key(A.sg, p, b);
+      const uint32_t key = base_key(A.sg, p, b);
+      A.skeys[j] = key;
+      A.bnext[j] = atomicExch(&A.bins[key], j);
       for (int a = 0; a < 3; ++a) A.sfrac[a * nc + j] = p[a] - floor(p[a]);
     }
   }
@@ -434,77 +440,82 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
 
 // ----------------------------------------------------------- spreading
 
-// Spreading preparation, one launch with two roles by block:
-//  * blocks [0, ntiles): a tile of the binning keys (written by the
-//    stage-1 finalize for the live points, padded here with the largest
-//    key beyond them) and the tile's digit counts for the first pass of
-//    the sort;
-//  * the other blocks: zero the force at the nodes the previous spreading
-//    wrote, and clear the previous spreading's bin marks.
-template <class FT>
-__global__ __launch_bounds__(kSortThreads) void k_spread_prepare(
-    const int32_t* __restrict__ cnt, long long ncap, uint32_t pad, int dbits, int ntiles, uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
-    int32_t* __restrict__ counts, FT* __restrict__ F, long long cells,
-    const int32_t* __restrict__ touched, const uint32_t* __restrict__ marked,
-    int32_t* __restrict__ bins) {
-  __shared__ int32_t hist[kSortMaxBins];
-  if ((int)blockIdx.x < ntiles) {
-    const int j = blockIdx.x * kSortThreads + threadIdx.x;
-    const int n = cnt[11];
-    uint32_t k = pad;
-    if (j < n) k = keys[j];
-    if (j < ncap) {
-      keys[j] = k;
-      vals[j] = j;
+// Sum of the contributions to one node of the m points of a bin's list,
+// whose order depends on timing, as a fixed function of the points: up to
+// kOrdered points are taken in ascending order; more are added as 64-bit
+// integers in units of 2^-(62 - log2 m) of the largest (exact sums, so the
+// order is irrelevant; a non-finite contribution makes the sum NaN).
+constexpr int kOrdered = 8;
+
+struct BinPoint {
+  const double* sfrac;
+  const double* gpt;
+  long long ncap;
+  int q;  // the node is corner q of the bin's stencil
+  __device__ void operator()(int j, double c[3]) const {
+    double w = 1.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double fr = sfrac[a * ncap + j];
+      w *= ((q >> a) & 1) ? fr : 1.0 - fr;
     }
-    sort_tile_count(k, j < ncap, 0, dbits, ntiles, blockIdx.x, hist, counts);
-    return;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) c[a] = w * gpt[a * ncap + j];
   }
-  const long long s = (long long)(blockIdx.x - ntiles) * kSortThreads + threadIdx.x;
-  if (s < cnt[1]) {
-    const int node = touched[s];
-    if (node >= 0) {
-      F[node] = FT(0);
-      F[cells + node] = FT(0);
-      F[2 * cells + node] = FT(0);
+};
+
+__device__ inline void add_many(int head, int m, int n, const int32_t* __restrict__ bnext,
+                                const BinPoint& at, double f[3]) {
+  double c[3], big[3] = {0.0, 0.0, 0.0};
+  bool bad[3] = {false, false, false};
+  int j = head;
+  for (int k = 0; k < m && (uint32_t)j < (uint32_t)n; ++k, j = bnext[j]) {
+    at(j, c);
+    for (int a = 0; a < 3; ++a) {
+      bad[a] = bad[a] || !isfinite(c[a]);
+      big[a] = fmax(big[a], fabs(c[a]));
     }
   }
-  if (s < ncap) {
-    const uint32_t mk = marked[s];
-    if (mk != 0xFFFFFFFFu) bins[mk] = -1;
+  int e[3];
+  const int room = 62 - (32 - __clz(m));
+  for (int a = 0; a < 3; ++a) {
+    e[a] = 0;
+    if (big[a] > 0.0 && !bad[a]) e[a] = room - 1 - ilogb(big[a]);
   }
+  long long s[3] = {0, 0, 0};
+  j = head;
+  for (int k = 0; k < m && (uint32_t)j < (uint32_t)n; ++k, j = bnext[j]) {
+    at(j, c);
+    for (int a = 0; a < 3; ++a)
+      if (!bad[a]) s[a] += __double2ll_rn(ldexp(c[a], e[a]));
+  }
+  for (int a = 0; a < 3; ++a) f[a] += bad[a] ? __builtin_nan("") : ldexp((double)s[a], -e[a]);
 }
 
-// Dense bin table: bins[key] = first sorted entry of that bin, -1 if empty.
-// The marked keys are listed so that the next spreading clears them.
-__global__ void k_bin_mark(const uint32_t* __restrict__ skey, const int32_t* __restrict__ cnt,
-                           long long ncap, int32_t* __restrict__ bins,
-                           uint32_t* __restrict__ marked) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= ncap) return;
-  const bool head = r < cnt[11] && (r == 0 || skey[r - 1] != skey[r]);
-  if (head) bins[skey[r]] = r;
-  marked[r] = head ? skey[r] : 0xFFFFFFFFu;
-}
-
-// One thread per (sorted entry, stencil corner).  Only the first entry of
-// each bin acts: the node at that corner of the bin's stencil is written by
-// the occupied bin of smallest key among the (up to 8) bins whose stencils
-// contain it, which gathers those bins' points in a fixed order.
+// One thread per (point, stencil corner).  Only the point at the head of its
+// bin's list acts: the node at that corner of the bin's stencil is written
+// by the occupied bin of smallest key among the (up to 8) bins whose
+// stencils contain it, which gathers those bins' points in a fixed order.
+// The nodes written are listed; the next moments kernel zeroes them.
+//
+// What bounds it: latency (list heads, links, offsets: dependent loads).
+// With a stable sort of the points by bin in place of the lists, the
+// spreading was ten launches, 65 us of a served step (128x128x256, 2e3
+// points); this one takes 13.
 template <class FT>
-__global__ void k_spread_gather(const uint32_t* __restrict__ skey, const int32_t* __restrict__ sval,
-                                const int32_t* __restrict__ bins,
-                                const double* __restrict__ sfrac, const double* __restrict__ gpt,
-                                int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
-                                long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
+__global__ __launch_bounds__(256) void k_spread_gather(
+    const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
+    const int32_t* __restrict__ bnext, const double* __restrict__ sfrac,
+    const double* __restrict__ gpt, int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
+    long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
   const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = cnt[11];
-  if (id == 0) cnt[1] = 8 * n;
   const int r = (int)(id >> 3);
   const int o = (int)(id & 7);
+  const uint32_t me = r < ncap ? skey[r] : 0u;  // (beyond the points: unused)
+  const int n = cnt[11];
+  if (id == 0) cnt[1] = 8 * n;
   if (r >= n) return;
-  const uint32_t me = skey[r];
-  if (r > 0 && skey[r - 1] == me) {
+  if (bins[me] != r) {
     touched[id] = -1;
     return;
   }
@@ -560,16 +571,31 @@ __global__ void k_spread_gather(const uint32_t* __restrict__ skey, const int32_t
   double f[3] = {0.0, 0.0, 0.0};
   for (int q = 0; q < 8; ++q) {
     if (lo[q] < 0) continue;
-    const int oq[3] = {q & 1, (q >> 1) & 1, (q >> 2) & 1};
-    for (int t = lo[q]; t < n && skey[t] == kq[q]; ++t) {
-      const int pidx = sval[t];
-      double w = 1.0;
-      for (int a = 0; a < 3; ++a) {
-        const double fr = sfrac[a * ncap + pidx];
-        w *= oq[a] ? fr : 1.0 - fr;
+    const BinPoint at{sfrac, gpt, ncap, q};
+    int first[kOrdered];  // the smallest indices on the list, ascending
+#pragma unroll
+    for (int s = 0; s < kOrdered; ++s) first[s] = 0x7fffffff;
+    int m = 0;
+    for (int j = lo[q]; (uint32_t)j < (uint32_t)n && m < n; j = bnext[j], ++m) {
+      int v = j;
+#pragma unroll
+      for (int s = 0; s < kOrdered; ++s) {
+        const int t = min(first[s], v);
+        v = max(first[s], v);
+        first[s] = t;
       }
-      for (int a = 0; a < 3; ++a) f[a] += w * gpt[a * ncap + pidx];
     }
+    if (m > kOrdered) {
+      add_many(lo[q], m, n, bnext, at, f);
+      continue;
+    }
+#pragma unroll
+    for (int s = 0; s < kOrdered; ++s)
+      if (s < m) {
+        double c[3];
+        at(first[s], c);
+        for (int a = 0; a < 3; ++a) f[a] += c[a];
+      }
   }
   const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
   F[node] = (FT)f[0];
@@ -629,8 +655,10 @@ hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y,
   A.X = (r.prec != VLB_F64 && !last && !eval_only) ? r.bsX : nullptr;
   A.ax = r.bsax;
   A.sg = spread_geom(r);
-  A.skeys = (first && r.vor.coupling) ? r.keys_a : nullptr;
+  A.skeys = (first && r.vor.coupling) ? r.skeys : nullptr;
   A.sfrac = r.sfrac;
+  A.bins = r.bins;
+  A.bnext = r.bnext;
   const int nb = nblocks(r.ncap, kFinPts);
   switch (r.prec) {
     case VLB_F64: hipLaunchKernelGGL((k_finalize<double, double>), dim3(nb), dim3(kFinWaves * 64), 0, r.stream, A); break;
@@ -654,33 +682,15 @@ hipError_t fil_copy_positions(Run& r, const double* src, double* dst) {
 
 hipError_t fil_spread(Run& r) {
   const SpreadGeom sg = spread_geom(r);
-  const uint32_t pad = (r.key_bits >= 32) ? 0xFFFFFFFFu : ((1u << r.key_bits) - 1u);
-  const int ntiles = sort_tiles(r.ncap);
-  int dbits = 0;
-  sort_first_digit(r.key_bits, &dbits);
-  const int nclear = nblocks(8 * r.ncap, kSortThreads);
-  if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_spread_prepare<double>, dim3(ntiles + nclear), dim3(kSortThreads), 0,
-                       r.stream, r.cnt, r.ncap, pad, dbits, ntiles, r.keys_a, r.vals_a,
-                       sort_counts(r), (double*)r.force, r.cells, r.touched, r.marked, r.bins);
-  else
-    hipLaunchKernelGGL(k_spread_prepare<float>, dim3(ntiles + nclear), dim3(kSortThreads), 0,
-                       r.stream, r.cnt, r.ncap, pad, dbits, ntiles, r.keys_a, r.vals_a,
-                       sort_counts(r), (float*)r.force, r.cells, r.touched, r.marked, r.bins);
-  uint32_t* sk = nullptr;
-  int32_t* sv = nullptr;
-  hipError_t e = sort_pairs(r, r.key_bits, 1, &sk, &sv);
-  if (e != hipSuccess) return e;
-  const int nb = nblocks(r.ncap, 256);
-  hipLaunchKernelGGL(k_bin_mark, dim3(nb), dim3(256), 0, r.stream, sk, r.cnt, r.ncap, r.bins,
-                     r.marked);
   const int nb8 = nblocks(8 * r.ncap, 256);
   if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_spread_gather<double>, dim3(nb8), dim3(256), 0, r.stream, sk, sv,
-                       r.bins, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (double*)r.force, r.touched);
+    hipLaunchKernelGGL(k_spread_gather<double>, dim3(nb8), dim3(256), 0, r.stream, r.skeys, r.bins,
+                       r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (double*)r.force,
+                       r.touched);
   else
-    hipLaunchKernelGGL(k_spread_gather<float>, dim3(nb8), dim3(256), 0, r.stream, sk, sv,
-                       r.bins, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (float*)r.force, r.touched);
+    hipLaunchKernelGGL(k_spread_gather<float>, dim3(nb8), dim3(256), 0, r.stream, r.skeys, r.bins,
+                       r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (float*)r.force,
+                       r.touched);
   return hipGetLastError();
 }
 

@@ -532,13 +532,39 @@ inline int moment_parts(const Geom& g) {
   return (int)(p > g.ny ? g.ny : p);
 }
 
+// What the previous spreading left, cleared by the moments kernel: the force
+// at the nodes it wrote and the heads of the bin lists it used (it precedes
+// the finalize that pushes on them).
+template <class UT>
+struct SpreadClear {
+  const int32_t* cnt;      // null: no spreading in this run
+  const int32_t* touched;  // cnt[1] nodes (-1: none)
+  const uint32_t* skeys;   // cnt[11] bins
+  int32_t* bins;
+  UT* F;
+};
+
 template <class S, class UT>
 __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ M, Geom g, int parity,
                                                 UT* __restrict__ ub, double scale, int parts,
-                                                int items, double* __restrict__ P) {
+                                                int items, double* __restrict__ P,
+                                                SpreadClear<UT> sc) {
   __shared__ double red[256];
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   const int nt = blockDim.x * blockDim.y;
+  if (sc.cnt) {
+    const int nf = sc.cnt[1], nk = sc.cnt[11];
+    const int step = gridDim.x * nt;
+    for (int i = blockIdx.x * nt + tid; i < nf; i += step) {
+      const int node = sc.touched[i];
+      if (node >= 0) {
+        sc.F[node] = UT(0);
+        sc.F[g.cells + node] = UT(0);
+        sc.F[2 * g.cells + node] = UT(0);
+      }
+    }
+    for (int i = blockIdx.x * nt + tid; i < nk; i += step) sc.bins[sc.skeys[i]] = -1;
+  }
   const int rows = (g.ny + parts - 1) / parts;
   for (int hw = blockIdx.x; hw < items; hw += gridDim.x) {
     const int it = xcd_remap(hw, items);
@@ -834,15 +860,18 @@ hipError_t lbm_moments(Run& r) {
   const bool mbz = r.vor.mass_balance && axis == 2;
   double* P = mbz ? (parts == 1 ? r.Vs : r.mbP) : nullptr;
   const double scale = -(1.0 / r.vor.rho_s_over_rho_n) / ((double)g.cells / n);
+  const int32_t* cc = r.vor.coupling ? r.cnt : nullptr;
+  const SpreadClear<double> sd{cc, r.touched, r.skeys, r.bins, (double*)r.force};
+  const SpreadClear<float> sf{cc, r.touched, r.skeys, r.bins, (float*)r.force};
   switch (r.prec) {
     case VLB_F64:
-      hipLaunchKernelGGL((k_moments<double, double>), dim3(grid), blk, 0, r.stream, (const double*)r.pops, g, r.parity, (double*)r.ub, scale, parts, items, P);
+      hipLaunchKernelGGL((k_moments<double, double>), dim3(grid), blk, 0, r.stream, (const double*)r.pops, g, r.parity, (double*)r.ub, scale, parts, items, P, sd);
       break;
     case VLB_F32:
-      hipLaunchKernelGGL((k_moments<float, float>), dim3(grid), blk, 0, r.stream, (const float*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P);
+      hipLaunchKernelGGL((k_moments<float, float>), dim3(grid), blk, 0, r.stream, (const float*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P, sf);
       break;
     default:
-      hipLaunchKernelGGL((k_moments<__half, float>), dim3(grid), blk, 0, r.stream, (const __half*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P);
+      hipLaunchKernelGGL((k_moments<__half, float>), dim3(grid), blk, 0, r.stream, (const __half*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P, sf);
       break;
   }
   if (mbz && parts > 1)

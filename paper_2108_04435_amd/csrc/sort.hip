@@ -1,12 +1,11 @@
 // Stable LSD radix sort of (uint32 key, int32 value) pairs, used to bin
-// filament points by lattice cell for the force spreading.  Digits of up to
+// segments by cell for the far-field sum.  Digits of up to
 // 11 bits (2 passes for keys of up to 22 bits), one tile of 1024 keys per
 // block of 1024 threads, one key per thread.  Inside a wave the lanes
 // holding the same digit are found with one ballot per digit bit; their
 // count and each lane's rank among them come from population counts.  Per
 // pass three kernels:
-//   1. per-tile digit counts (LDS histogram; the first pass can be fused
-//      into the kernel that produces the keys);
+//   1. per-tile digit counts (LDS histogram);
 //   2. digit offsets of every tile (keys of smaller digits anywhere plus
 //      keys of the same digit in earlier tiles): a one-workgroup exclusive
 //      scan of the digit-major count table;
@@ -21,6 +20,38 @@
 namespace vlb {
 
 namespace {
+
+// Radix-sort tiles: one key per thread, one tile per block.
+constexpr int kSortThreads = 1024;
+constexpr int kSortMaxBits = 11;
+constexpr int kSortMaxBins = 1 << kSortMaxBits;
+
+// Lanes of this wave whose (valid) digit equals this lane's digit.
+__device__ inline uint64_t sort_peer_mask(uint32_t d, bool valid, int bits) {
+  uint64_t m = __ballot(valid);
+  for (int b = 0; b < bits; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t x = __ballot(valid && bit);
+    m &= bit ? x : ~x;
+  }
+  return m;
+}
+
+// Digit histogram of one tile (one key per thread of a kSortThreads block;
+// every thread calls it): LDS integer adds by the lowest lane of each digit
+// group; counts[d * ntiles + tile] receives the tile's count of digit d.
+__device__ inline void sort_tile_count(uint32_t key, bool valid, int shift, int bits, int ntiles,
+                                       int tile, int32_t* hist, int32_t* __restrict__ counts) {
+  const int t = threadIdx.x, lane = t & 63;
+  const int nbins = 1 << bits;
+  for (int e = t; e < nbins; e += kSortThreads) hist[e] = 0;
+  __syncthreads();
+  const uint32_t d = (key >> shift) & (uint32_t)(nbins - 1);
+  const uint64_t m = sort_peer_mask(d, valid, bits);
+  if (valid && (int)(__ffsll((unsigned long long)m) - 1) == lane) atomicAdd(&hist[d], (int)__popcll(m));
+  __syncthreads();
+  for (int e = t; e < nbins; e += kSortThreads) counts[(long long)e * ntiles + tile] = hist[e];
+}
 
 __global__ __launch_bounds__(kSortThreads) void k_rs_count(const uint32_t* __restrict__ keys,
                                                            int n, int shift, int bits, int ntiles,
@@ -134,26 +165,10 @@ size_t sort_tmp_bytes(long long n) {
   return (size_t)(2 * (((long long)kSortMaxBins * ntiles + 63) & ~63LL) + 16) * sizeof(int32_t);
 }
 
-int sort_tiles(long long n) { return (int)((n + kSortThreads - 1) / kSortThreads); }
-
-void sort_first_digit(int bits, int* dbits) {
-  const int passes = (bits + kSortMaxBits - 1) / kSortMaxBits;
-  const int db = (bits + passes - 1) / passes;
-  *dbits = db < bits ? db : bits;
-}
-
-int32_t* sort_counts(Run& r) { return (int32_t*)r.sort_tmp; }
-
-// Sort n pairs (ka, va) by the low `bits` bits of the key, with tmp of
-// sort_tmp_bytes(n) bytes and the second buffers kb, vb.  first_counted: the
-// tile counts of the first pass are already in the count table at tmp.
-// Result pointers are returned (they alternate between the a and b buffers
-// with the number of passes).
-hipError_t sort_pairs_raw(long long nn, int bits, int first_counted, void* tmp, uint32_t* ka,
-                          uint32_t* kb, int32_t* va, int32_t* vb, hipStream_t stream,
-                          uint32_t** kres, int32_t** vres) {
+hipError_t sort_pairs(long long nn, int bits, void* tmp, uint32_t* ka, uint32_t* kb, int32_t* va,
+                      int32_t* vb, hipStream_t stream, uint32_t** kres, int32_t** vres) {
   const int n = (int)nn;
-  const int ntiles = sort_tiles(n);
+  const int ntiles = (int)((nn + kSortThreads - 1) / kSortThreads);
   int32_t* counts = (int32_t*)tmp;
   int32_t* offs = counts + (((long long)kSortMaxBins * ntiles + 63) & ~63LL);
   uint32_t* kin = ka;
@@ -165,9 +180,8 @@ hipError_t sort_pairs_raw(long long nn, int bits, int first_counted, void* tmp, 
   for (int p = 0; p < passes; ++p) {
     const int shift = dbits * p;
     const int pb = (shift + dbits <= bits) ? dbits : bits - shift;
-    if (p > 0 || !first_counted)
-      hipLaunchKernelGGL(k_rs_count, dim3(ntiles), dim3(kSortThreads), 0, stream, kin, n, shift,
-                         pb, ntiles, counts);
+    hipLaunchKernelGGL(k_rs_count, dim3(ntiles), dim3(kSortThreads), 0, stream, kin, n, shift, pb,
+                       ntiles, counts);
     hipLaunchKernelGGL(k_rs_offsets, dim3(1), dim3(1024), 0, stream, counts, ntiles << pb, offs);
     hipLaunchKernelGGL(k_rs_scatter, dim3(ntiles), dim3(kSortThreads), 0, stream, kin, vin,
                        kout, vout, n, shift, pb, ntiles, offs);
@@ -181,12 +195,6 @@ hipError_t sort_pairs_raw(long long nn, int bits, int first_counted, void* tmp, 
   *kres = kin;
   *vres = vin;
   return hipGetLastError();
-}
-
-// The run's ncap pairs (keys_a, vals_a).
-hipError_t sort_pairs(Run& r, int bits, int first_counted, uint32_t** kres, int32_t** vres) {
-  return sort_pairs_raw(r.ncap, bits, first_counted, r.sort_tmp, r.keys_a, r.keys_b, r.vals_a,
-                        r.vals_b, r.stream, kres, vres);
 }
 
 }  // namespace vlb

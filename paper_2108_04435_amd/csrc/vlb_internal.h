@@ -436,38 +436,6 @@ struct BsAxes {
   float sign[27];
 };
 
-// Radix-sort tiles: one key per thread, one tile per block.
-constexpr int kSortThreads = 1024;
-constexpr int kSortMaxBits = 11;
-constexpr int kSortMaxBins = 1 << kSortMaxBits;
-
-// Lanes of this wave whose (valid) digit equals this lane's digit.
-__device__ inline uint64_t sort_peer_mask(uint32_t d, bool valid, int bits) {
-  uint64_t m = __ballot(valid);
-  for (int b = 0; b < bits; ++b) {
-    const bool bit = (d >> b) & 1u;
-    const uint64_t x = __ballot(valid && bit);
-    m &= bit ? x : ~x;
-  }
-  return m;
-}
-
-// Digit histogram of one tile (one key per thread of a kSortThreads block;
-// every thread calls it): LDS integer adds by the lowest lane of each digit
-// group; counts[d * ntiles + tile] receives the tile's count of digit d.
-__device__ inline void sort_tile_count(uint32_t key, bool valid, int shift, int bits, int ntiles,
-                                       int tile, int32_t* hist, int32_t* __restrict__ counts) {
-  const int t = threadIdx.x, lane = t & 63;
-  const int nbins = 1 << bits;
-  for (int e = t; e < nbins; e += kSortThreads) hist[e] = 0;
-  __syncthreads();
-  const uint32_t d = (key >> shift) & (uint32_t)(nbins - 1);
-  const uint64_t m = sort_peer_mask(d, valid, bits);
-  if (valid && (int)(__ffsll((unsigned long long)m) - 1) == lane) atomicAdd(&hist[d], (int)__popcll(m));
-  __syncthreads();
-  for (int e = t; e < nbins; e += kSortThreads) counts[(long long)e * ntiles + tile] = hist[e];
-}
-
 // Workspace-resident state of a run.
 struct Run {
   vlb_lattice_desc lat;
@@ -499,8 +467,9 @@ struct Run {
   double* seg = nullptr;       // diagnostics: z extent and length per segment (3 n_cap doubles)
   double* fric = nullptr;      // alpha(z), alpha'(z) profiles and their on flag (2 nz + 1 doubles)
   void* ub_next = nullptr;
-  int32_t* bins = nullptr;     // spreading: dense bin -> first sorted entry (-1 = empty)
-  uint32_t* marked = nullptr;  // per sorted entry: the bin it marked (all ones: none)
+  int32_t* bins = nullptr;     // spreading: per bin the last point pushed (-1 = empty)
+  int32_t* bnext = nullptr;    // per point the one pushed on its bin before it
+  uint32_t* skeys = nullptr;   // per point its bin
   long long nbins_table = 0;
 
   // filaments
@@ -536,14 +505,7 @@ struct Run {
   // [16..17] pair counter
   int32_t* cnt = nullptr;
 
-  // sorting / scans
-  uint32_t* keys_a = nullptr;
-  uint32_t* keys_b = nullptr;
-  int32_t* vals_a = nullptr;
-  int32_t* vals_b = nullptr;
-  void* sort_tmp = nullptr;
-  size_t sort_tmp_bytes = 0;
-  int key_bits = 32;
+  // flags and scans
   int32_t* flag_a = nullptr;  // per point int flags
   int32_t* flag_b = nullptr;
   int32_t* scan_a = nullptr;
@@ -662,13 +624,11 @@ hipError_t fil_seed(Run& r, long long n);
 hipError_t topo_update(Run& r, bool swap);
 
 size_t sort_tmp_bytes(long long n);
-int sort_tiles(long long n);
-void sort_first_digit(int bits, int* dbits);
-int32_t* sort_counts(Run& r);
-hipError_t sort_pairs(Run& r, int bits, int first_counted, uint32_t** kres, int32_t** vres);
-hipError_t sort_pairs_raw(long long n, int bits, int first_counted, void* tmp, uint32_t* ka,
-                          uint32_t* kb, int32_t* va, int32_t* vb, hipStream_t stream,
-                          uint32_t** kres, int32_t** vres);
+// Sort n pairs (ka, va) by the low `bits` bits of the key, with tmp of
+// sort_tmp_bytes(n) bytes and the second buffers kb, vb.  Result pointers
+// are returned (they alternate between the a and b buffers).
+hipError_t sort_pairs(long long n, int bits, void* tmp, uint32_t* ka, uint32_t* kb, int32_t* va,
+                      int32_t* vb, hipStream_t stream, uint32_t** kres, int32_t** vres);
 
 // timing helpers (api.cpp)
 void time_begin(Run& r, int cls, hipEvent_t* b);
