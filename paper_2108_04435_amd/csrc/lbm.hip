@@ -445,6 +445,48 @@ __device__ inline void node_rho_u(const S* M, const Geom& g, int parity, int x, 
   uz = (double)jz / rho;
 }
 
+// The same for one AA parity, with 32-bit slot offsets where the population
+// array spans less than 4 GiB (I32) and non-temporal loads of the slots that
+// no other node's line holds (NT: lattices above the last-level cache;
+// 128x128x256 FP32, even parity 76 -> 63 us).
+template <class S, int P, bool I32, bool NT>
+__device__ inline void node_u(const S* __restrict__ M, const Geom& g, int x, int y, int z,
+                              double u[3]) {
+  using T = typename Store<S>::T;
+  if constexpr (!I32) {
+    double rho;
+    node_rho_u<S>(M, g, P, x, y, z, rho, u[0], u[1], u[2]);
+  } else {
+    if (is_plane(g, z)) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) u[a] = g.plane_u[a];
+      return;
+    }
+    const uint32_t cells = (uint32_t)g.cells;
+    const uint32_t c = (uint32_t)((z * g.ny + y) * g.nx + x);
+    T d[19];
+    if (P == 0) {
+#pragma unroll
+      for (int i = 0; i < 19; ++i)
+        d[i] = pop_ld<S, NT>(at_byte(M + (long long)i * g.cells, c * (uint32_t)sizeof(S)));
+    } else {
+      Nbr32 nb;
+      make_nbr32(g, x, y, z, nb);
+#pragma unroll
+      for (int i = 0; i < 19; ++i) {
+        const int s = nbr_index32(nb, -cx(i), -cy(i), -cz(i));
+        const uint32_t e = s >= 0 ? (uint32_t)opp(i) * cells + (uint32_t)s : (uint32_t)i * cells + c;
+        d[i] = pop_ld<S, NT>(at_byte(M, e * (uint32_t)sizeof(S)));
+      }
+    }
+    T drho, j[3];
+    moments<T>(d, drho, j[0], j[1], j[2]);
+    const double rho = 1.0 + (double)drho;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) u[a] = (double)j[a] / rho;
+  }
+}
+
 template <class S>
 __global__ void k_read_fields(const S* __restrict__ M, Geom g, int parity, double* rho_out,
                               double* u_out) {
@@ -516,15 +558,16 @@ __global__ void k_read_force(const T* __restrict__ F, long long n, double* out) 
 // it in tiles (x fastest), each thread adds its nodes' u_z in order and the
 // block adds the threads in a fixed tree.  The parts depend on the lattice
 // alone, so the sums do not depend on the grid, which may be narrower than
-// the items.  One part per slice: P[z] = scale * sum is the superflow; else
-// P[z * parts + part] the part's sum (k_mb_total adds them).  P is null
+// the items.  One part per slice: Ps[z] = scale * sum is the superflow; else
+// Ps[z * parts + part] the part's sum (k_mb_total adds them).  Ps is null
 // without mass balance along z.
 //
 // What bounds it: HBM (19 populations read, three velocities written), given
 // enough waves in flight: with one block per slice, 128x128x256 FP32 took
-// 94 to 110 us beside the filament kernels (3.4 TB/s); parts of at most
-// kMomentNodes nodes keep 8 blocks on every CU.
-constexpr int kMomentNodes = 2048;
+// 94 to 110 us beside the filament kernels (3.4 TB/s); parts of about
+// kMomentNodes nodes take 63 (even parity) to 73 us (5.1 to 5.9 TB/s); longer
+// parts (2048 nodes) fill every CU at once and hold up the filament kernels.
+constexpr int kMomentNodes = 512;
 
 inline int moment_parts(const Geom& g) {
   const long long ns = (long long)g.nx * g.ny;
@@ -544,10 +587,10 @@ struct SpreadClear {
   UT* F;
 };
 
-template <class S, class UT>
-__global__ __launch_bounds__(256) void k_moments(const S* __restrict__ M, Geom g, int parity,
+template <class S, class UT, int P, bool I32, bool NT>
+__global__ __launch_bounds__(256) void k_moments(const S* __restrict__ M, Geom g,
                                                 UT* __restrict__ ub, double scale, int parts,
-                                                int items, double* __restrict__ P,
+                                                int items, double* __restrict__ Ps,
                                                 SpreadClear<UT> sc) {
   __shared__ double red[256];
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
@@ -573,22 +616,21 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ M, Geom g
     double uzv = 0.0;
     for (int y = yb + threadIdx.y; y < ye; y += blockDim.y)
       for (int x = threadIdx.x; x < g.nx; x += blockDim.x) {
-        double rho, ux, uy, uz;
-        node_rho_u<S>(M, g, parity, x, y, z, rho, ux, uy, uz);
+        double u[3];
+        node_u<S, P, I32, NT>(M, g, x, y, z, u);
         const long long c = ((long long)z * g.ny + y) * g.nx + x;
-        ub[c] = (UT)ux;
-        ub[g.cells + c] = (UT)uy;
-        ub[2 * g.cells + c] = (UT)uz;
-        uzv += uz;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ub[a * g.cells + c] = (UT)u[a];
+        uzv += u[2];
       }
-    if (!P) continue;
+    if (!Ps) continue;
     red[tid] = uzv;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
       if (tid < s && tid + s < nt) red[tid] += red[tid + s];
       __syncthreads();
     }
-    if (tid == 0) P[it] = parts == 1 ? scale * red[0] : red[0];
+    if (tid == 0) Ps[it] = parts == 1 ? scale * red[0] : red[0];
     __syncthreads();  // the next item writes red
   }
 }
@@ -683,6 +725,12 @@ constexpr double kStreamBytes = 192.0 * (1 << 20);
 // Grid of a lattice kernel beside longer filament kernels: two blocks per CU.
 constexpr int kNarrowBlocks = 512;
 
+// 32-bit slot offsets: the population array spans less than 4 GiB.
+template <class S>
+bool slots32(const Geom& g) {
+  return g.cells < (1LL << 29) && 19.0 * (double)g.cells * sizeof(S) < 4294967296.0;
+}
+
 template <class S>
 hipError_t launch_collide(Run& r) {
   using T = typename Store<S>::T;
@@ -703,8 +751,7 @@ hipError_t launch_collide(Run& r) {
   if (r.lbm_narrow && grid > kNarrowBlocks) grid = kNarrowBlocks;
   // populations far above the last-level cache: non-temporal accesses
   const bool nt = 19.0 * (double)g.cells * sizeof(S) > kStreamBytes;
-  // odd passes: 32-bit slot offsets when the population array spans less than 4 GiB
-  const bool i32 = g.cells < (1LL << 29) && 19.0 * (double)g.cells * sizeof(S) < 4294967296.0;
+  const bool i32 = slots32<S>(g);
   if constexpr (sizeof(S) == 2) {
     // rows of 256 nodes periodic in x and y: four nodes per lane
     if (i32 && g.nx == 256 && !g.wall[0] && !g.wall[1]) {
@@ -842,9 +889,32 @@ size_t lbm_mb_doubles(const Run& r) {
   return (size_t)g.nz * (axis == 0 ? g.nx : (axis == 1 ? g.ny : moment_parts(g)));
 }
 
+namespace {
+
+template <class S, class UT>
+void launch_moments(Run& r, dim3 blk, int grid, double scale, int parts, int items, double* Ps) {
+  const Geom& g = r.geom;
+  const SpreadClear<UT> sc{r.vor.coupling ? r.cnt : nullptr, r.touched, r.skeys, r.bins,
+                           (UT*)r.force};
+  const bool i32 = slots32<S>(g);
+  const bool nt = i32 && 19.0 * (double)g.cells * sizeof(S) > kStreamBytes;
+  auto kern = r.parity == 0 ? (nt    ? k_moments<S, UT, 0, true, true>
+                               : i32 ? k_moments<S, UT, 0, true, false>
+                                     : k_moments<S, UT, 0, false, false>)
+                            : (nt    ? k_moments<S, UT, 1, true, true>
+                               : i32 ? k_moments<S, UT, 1, true, false>
+                                     : k_moments<S, UT, 1, false, false>);
+  hipLaunchKernelGGL(kern, dim3(grid), blk, 0, r.stream, (const S*)r.pops, g, (UT*)r.ub, scale,
+                     parts, items, Ps, sc);
+}
+
+}  // namespace
+
 hipError_t lbm_moments(Run& r) {
   const Geom& g = r.geom;
-  const int bx = g.nx < 64 ? g.nx : 64;
+  // one x row of up to 256 nodes, as the update (odd parity 76 -> 73 us
+  // against rows of 64)
+  const int bx = g.nx < 256 ? g.nx : 256;
   int by = 256 / bx;
   if (by < 1) by = 1;
   if (by > g.ny) by = g.ny;
@@ -858,21 +928,12 @@ hipError_t lbm_moments(Run& r) {
   const int axis = r.vor.mass_balance_axis;
   const int n = axis == 0 ? g.nx : (axis == 1 ? g.ny : g.nz);
   const bool mbz = r.vor.mass_balance && axis == 2;
-  double* P = mbz ? (parts == 1 ? r.Vs : r.mbP) : nullptr;
+  double* Ps = mbz ? (parts == 1 ? r.Vs : r.mbP) : nullptr;
   const double scale = -(1.0 / r.vor.rho_s_over_rho_n) / ((double)g.cells / n);
-  const int32_t* cc = r.vor.coupling ? r.cnt : nullptr;
-  const SpreadClear<double> sd{cc, r.touched, r.skeys, r.bins, (double*)r.force};
-  const SpreadClear<float> sf{cc, r.touched, r.skeys, r.bins, (float*)r.force};
   switch (r.prec) {
-    case VLB_F64:
-      hipLaunchKernelGGL((k_moments<double, double>), dim3(grid), blk, 0, r.stream, (const double*)r.pops, g, r.parity, (double*)r.ub, scale, parts, items, P, sd);
-      break;
-    case VLB_F32:
-      hipLaunchKernelGGL((k_moments<float, float>), dim3(grid), blk, 0, r.stream, (const float*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P, sf);
-      break;
-    default:
-      hipLaunchKernelGGL((k_moments<__half, float>), dim3(grid), blk, 0, r.stream, (const __half*)r.pops, g, r.parity, (float*)r.ub, scale, parts, items, P, sf);
-      break;
+    case VLB_F64: launch_moments<double, double>(r, blk, grid, scale, parts, items, Ps); break;
+    case VLB_F32: launch_moments<float, float>(r, blk, grid, scale, parts, items, Ps); break;
+    default: launch_moments<__half, float>(r, blk, grid, scale, parts, items, Ps); break;
   }
   if (mbz && parts > 1)
     hipLaunchKernelGGL(k_mb_total, dim3((n + 63) / 64), dim3(64), 0, r.stream, (const double*)r.mbP, parts, n, parts, 1, scale, r.Vs);
