@@ -212,6 +212,7 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   // spreading bins: lower stencil corner, n (+1 on wall axes) per axis
   const unsigned long long ext = (unsigned long long)(n[0] + g.wall[0]) * (n[1] + g.wall[1]) * (n[2] + g.wall[2]);
   r.nbins_table = (long long)ext;
+  r.small = r.vor.ff_cell == 0 && r.ncap * r.bsax.copies <= kStagePoints;
   // Which part of a step is the longer one, by its work at the rates they
   // reach: pairs of the Biot-Savart sums (1.5e12 per second in FP32, half of
   // that in FP64; with the far field 28 ns per point and sum) against the
@@ -227,6 +228,7 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
                            : sums * nn * nn * r.bsax.copies / (r.prec == VLB_F64 ? 0.75e12 : 1.5e12);
     const double latt = (double)r.cells * (57.0 * elt_size(r.prec) + (r.prec == VLB_F64 ? 48 : 24)) / 5e12;
     r.narrow_steps = fil > latt;
+    r.one_stream = r.small && latt < kShortLattice;
   }
   // reconnection bins of edge >= reconnect distance
   if (vor->reconnect) {
@@ -545,14 +547,18 @@ int one_step(vlb_run* h, bool first, bool last) {
     r.last_nodes += r.cells;
     return VLB_OK;
   }
-  hipStream_t M = r.stream, S = r.side;
+  // a run whose kernels are all short keeps to the caller's stream
+  const bool two = !r.one_stream;
+  hipStream_t M = r.stream, S = two ? r.side : r.stream;
   if (first) {
-    HIP_OR_FAIL(h, hipEventRecord(r.ev_fork, M));
-    HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fork, 0));
+    if (two) {
+      HIP_OR_FAIL(h, hipEventRecord(r.ev_fork, M));
+      HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fork, 0));
+    }
     OnStream on(r, S);
     // bare velocity field and mass-balance superflow of f^n
     HIP_OR_FAIL(h, lbm_moments(r));
-    HIP_OR_FAIL(h, hipEventRecord(r.ev_mom, S));
+    if (two) HIP_OR_FAIL(h, hipEventRecord(r.ev_mom, S));
   }
   // filament stages: vfm_substeps substeps of the rk_stages-stage method,
   // each from the positions in pos back into pos; stage positions
@@ -576,23 +582,28 @@ int one_step(vlb_run* h, bool first, bool last) {
     // FP32: the grid coordinates of every stage's positions were written by
     // the kernel that wrote the positions (seeding and the topology's copy
     // for the step's first stage, the previous finalize for the others)
-    if (r.vor.ff_cell > 0) {
+    if (r.small) {
+      if (two && gs == 0) HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_mom, 0));
+      HIP_OR_FAIL(h, fil_stage(r, s + 1, gs == 0, gs == G - 1, Ys[s], Yn[s]));
+    } else if (r.vor.ff_cell > 0) {
       HIP_OR_FAIL(h, ff_run_sum(r, Ys[s]));
     } else {
       if (r.bsax.copies > 1) HIP_OR_FAIL(h, bs_prep(r, Ys[s]));
       HIP_OR_FAIL(h, bs_sum(r, Ys[s]));
     }
     // the first finalize reads the velocity field and the superflow
-    if (gs == 0) HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_mom, 0));
-    HIP_OR_FAIL(h, fil_finalize(r, s + 1, gs == 0, gs == G - 1, Ys[s], Yn[s], 0));
+    if (!r.small) {
+      if (gs == 0) HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_mom, 0));
+      HIP_OR_FAIL(h, fil_finalize(r, s + 1, gs == 0, gs == G - 1, Ys[s], Yn[s], 0));
+    }
     if (K == 1) HIP_OR_FAIL(h, fil_copy_positions(r, r.ya, r.pos));
     // finalize 1 leaves the spreading everything it reads, and it follows
     // the previous step's last reads of the field the next moments overwrite
-    if (gs == 0) HIP_OR_FAIL(h, hipEventRecord(r.ev_fin1, M));
+    if (two && gs == 0) HIP_OR_FAIL(h, hipEventRecord(r.ev_fin1, M));
     // the side stream's work is enqueued after the main stream's next
     // kernel, so that a graph keeps the main chain on one queue
     if (gs == gside) {
-      HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fin1, 0));
+      if (two) HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fin1, 0));
       OnStream on(r, S);
       if (spread) HIP_OR_FAIL(h, fil_spread(r));
       // the LBM update (on a narrow grid where the filament part is the
@@ -609,7 +620,7 @@ int one_step(vlb_run* h, bool first, bool last) {
       }
       r.lbm_narrow = false;
       if (le != hipSuccess) return hip_fail(h, le, "lbm_step / lbm_moments");
-      if (!last) HIP_OR_FAIL(h, hipEventRecord(r.ev_mom, S));
+      if (two && !last) HIP_OR_FAIL(h, hipEventRecord(r.ev_mom, S));
     }
   }
   HIP_OR_FAIL(h, topo_update(r, true));
@@ -617,7 +628,7 @@ int one_step(vlb_run* h, bool first, bool last) {
     std::swap(r.ub, r.ub_next);
     std::swap(r.Vs, r.Vs_next);
   }
-  if (last) {
+  if (two && last) {
     HIP_OR_FAIL(h, hipEventRecord(r.ev_join, S));
     HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_join, 0));
   }

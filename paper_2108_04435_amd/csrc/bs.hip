@@ -20,7 +20,7 @@
 //    image and a relative (not absolute) rounding error for near pairs;
 //  * each chunk writes one partial sum per target; the finalize kernel adds
 //    the chunks in a fixed order (no atomics, bitwise reproducible).
-#include "vlb_internal.h"
+#include "bs_pair.h"
 
 #include <cmath>
 
@@ -43,53 +43,12 @@ constexpr long long kWideTargets = 16384;
 // level from 8e3 on.
 constexpr long long kDirectPoints = 4096;
 
-// Points of a sum: component a of point j at Y[a sa + j sj], links (entries
-// of nxt are clamped into the points; prv is read with image copies only).
-struct BsPts {
-  const double* Y;
-  long long sa, sj;
-  const int32_t* nxt;
-  const int32_t* prv;
-};
-
 // Quarter of a staged tile of cnt sources walked by wave w: [lo, hi) (empty
 // when lo >= hi), at most 64 of a tile of 256.
 __device__ inline void wave_range(int cnt, int w, int& lo, int& hi) {
   const int q = (cnt + 3) >> 2;
   lo = w * q;
   hi = __builtin_amdgcn_readfirstlane(min(cnt, lo + q));
-}
-
-// A coordinate mirrored for an image copy: 0 itself, 1 in the wall plane
-// -1/2, 2 in the plane L - 1/2.
-__device__ inline double bs_mirror(double y, int m, double L) {
-  return m == 0 ? y : (m == 1 ? 2.0 * (-0.5) - y : 2.0 * (L - 0.5) - y);
-}
-
-// The image copy mirrored in the wall that the end of an open line at y is
-// bound to (the lowest closed axis whose wall plane it lies on; nothing else
-// reflected), 0 if none: in that copy the images of the end's two segments
-// meet it and are excluded, as the real ones are in copy 0.
-__device__ inline int bs_own_copy(const double* y, const BsAxes& ax) {
-  int ea = -1, es = 0, oc = 0;
-  for (int a = 2; a >= 0; --a)
-    if (!ax.periodic[a] && (y[a] == -0.5 || y[a] == ax.L[a] - 0.5)) {
-      ea = a;
-      es = y[a] == -0.5 ? 1 : 2;
-    }
-  if (ea >= 0)
-    for (int c = 1; c < ax.copies; ++c) {
-      bool only = true;
-      for (int a = 0; a < 3; ++a) only = only && ax.refl[c][a] == (a == ea ? es : 0);
-      if (only) oc = c;
-    }
-  return oc;
-}
-
-// FP32 grid coordinate of a coordinate on axis a.
-__device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
-  const double s = floor((y + ax.off[a]) * ax.q[a]);
-  return ax.periodic[a] ? (uint32_t)(long long)s : (uint32_t)(int)(long long)s;
 }
 
 // FP32: grid coordinates X (stride nc) of the points (copy 0) and of their
@@ -108,33 +67,6 @@ __global__ void k_prep(BsPts in, const int32_t* __restrict__ cntp, int n_arg, lo
       X[((long long)c * 3 + a) * nc + j] = bs_grid_f32(bs_mirror(y[a], ax.refl[c][a], ax.L[a]), ax, a);
   }
 }
-
-// FP32 pair sum.  Per pair, with R1 = s_k - r (from the grid difference),
-// d = s_next(k) - s_k, q = |d|^2 and R2 = R1 + d:
-//   R1 x R2 = R1 x d,  |R2|^2 = |R1|^2 + (2 R1.d + q),
-//   (|R1| + |R2|)^2 - q = 2 (|R1||R2| + R1.R2),
-// so the closed form (R1 x R2) (|R1| + |R2|) / (|R1||R2| (|R1||R2| + R1.R2))
-// becomes (R1 x 2d) (i1 + i2) / (s^2 - q) with i_m = 1/|R_m| and
-// s = |R1| + |R2| = |R1|^2 i1 + |R2|^2 i2: 27 ordinary and 3 transcendental
-// instructions per pair (sources are staged as 2d and q).  Uniform grid: R1
-// stays in grid units and the result is rescaled once per target (v is
-// homogeneous of degree -1 in R).
-//
-// What bounds it: VALU issue.  Ordinary FP32 and integer instructions of two
-// waves issue together (1.45 to 1.73 wave instructions per CU and cycle with
-// 8 waves per SIMD; 0.89 when an operand is a scalar register, so the source
-// data must come from vector registers), a transcendental one takes two
-// cycles alone; the loop's mix takes 23.5 cycles per pair of wave and source
-// by those rates, 25.7 measured.  Against the form with
-// 1 + (R1.R2) i1 i2 in the denominator (29.5 ordinary): 1.45 -> 1.52 Tpairs/s
-// at 1.0e5 points, the error against FP64 6.0e-7 -> 5.5e-7.  Two or four
-// targets per lane measured 3% and 13% slower (fewer waves in flight).
-struct __align__(16) BsSrc {
-  uint32_t x, y, z;  // grid coordinates of the segment's start
-  float q;           // |d|^2
-  float dx, dy, dz;  // 2 d
-  int32_t kn;        // index of the segment's end
-};
 
 // Does one of the wave's sources [t0 + lo, t0 + hi) (at most 64, staged at
 // src) start or end at one of the nt targets from j0 on?  Uniform per wave.
@@ -156,26 +88,8 @@ __device__ inline void bs_tile_f32(const BsSrc* src, int cnt, int t0, uint32_t x
 #pragma unroll 2
   for (int s = 0; s < cnt; ++s) {
     const BsSrc g = src[s];
-    float r1x = (float)(int)(g.x - xt);
-    float r1y = (float)(int)(g.y - yt);
-    float r1z = (float)(int)(g.z - zt);
-    if (!kUniform) {
-      r1x *= iqx;
-      r1y *= iqy;
-      r1z *= iqz;
-    }
-    const float ex = g.dx, ey = g.dy, ez = g.dz;
-    const float t = fmaf(r1x, ex, fmaf(r1y, ey, fmaf(r1z, ez, g.q)));
-    const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
-    const float n2 = n1 + t;
-    const float i1 = __builtin_amdgcn_rsqf(n1);
-    const float i2 = __builtin_amdgcn_rsqf(n2);
-    const float sum = fmaf(n1, i1, n2 * i2);
-    float f = (i1 + i2) * __builtin_amdgcn_rcpf(fmaf(sum, sum, -g.q));
-    if (kCheck) f = (t0 + s == jj || g.kn == jj) ? 0.0f : f;
-    ax = fmaf(f, fmaf(r1y, ez, -(r1z * ey)), ax);
-    ay = fmaf(f, fmaf(r1z, ex, -(r1x * ez)), ay);
-    az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
+    bs_pair_f32<kUniform>(g, xt, yt, zt, iqx, iqy, iqz,
+                          kCheck && (t0 + s == jj || g.kn == jj), ax, ay, az);
   }
 }
 
@@ -230,39 +144,8 @@ __global__ __launch_bounds__(256) void k_bs_f32(BsPts in, const uint32_t* __rest
   float ax = 0.f, ay = 0.f, az = 0.f;
   for (int t0 = kb; t0 < ke; t0 += kTile) {
     const int k = t0 + threadIdx.x;
-    if (k < ke) {
-      // segment vector: wrapped grid difference to the successor
-      const int kn = min(max(in.nxt[k], 0), n - 1);
-      uint32_t x0[3], x1[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        if (kDirect) {
-          x0[a] = bs_grid_f32(in.Y[a * in.sa + k * in.sj], bx, a);
-          x1[a] = bs_grid_f32(in.Y[a * in.sa + kn * in.sj], bx, a);
-        } else {
-          x0[a] = Xs[a * nc + k];
-          x1[a] = Xs[a * nc + kn];
-        }
-      }
-      float ex = (float)(int)(x1[0] - x0[0]);
-      float ey = (float)(int)(x1[1] - x0[1]);
-      float ez = (float)(int)(x1[2] - x0[2]);
-      if (!kUniform) {
-        ex *= iqx;
-        ey *= iqy;
-        ez *= iqz;
-      }
-      BsSrc g;
-      g.x = x0[0];
-      g.y = x0[1];
-      g.z = x0[2];
-      g.q = ex * ex + ey * ey + ez * ez;
-      g.dx = 2.0f * ex;
-      g.dy = 2.0f * ey;
-      g.dz = 2.0f * ez;
-      g.kn = kn;
-      src[threadIdx.x] = g;
-    }
+    if (k < ke)
+      src[threadIdx.x] = bs_stage_f32<kUniform, kDirect>(in, Xs, nc, k, n, 0, iqx, iqy, iqz, bx);
     __syncthreads();
     int lo, hi;
     wave_range(min(kTile, ke - t0), w, lo, hi);
@@ -291,48 +174,6 @@ __global__ __launch_bounds__(256) void k_bs_f32(BsPts in, const uint32_t* __rest
   }
 }
 
-// FP64 pair sum (plain path), with the FP32 sum's q, R2 and s^2:
-//   s^2 = |R1|^2 + |R2|^2 + 2 p,  p = |R1||R2| = sqrt(|R1|^2 |R2|^2),
-//   (|R1| + |R2|) / (p (p + R1.R2)) = 2 s / (p (s^2 - q))
-//                                   = 2 s^2 / sqrt(s^2 p^2 (s^2 - q)^2),
-// two inverse roots instead of two and a reciprocal.  Each is the hardware
-// approximation (relative error up to about 5e-8) refined by one Newton step
-// (which squares it), the first inside s^2, the second inside the factor:
-// f = s^2 z (3 - arg z^2) with z ~ 1/sqrt(arg).  Sources are staged as 2 d;
-// the partial sums take the 1/2.
-//
-// The separation R1: on a closed axis the difference of the positions; on a
-// periodic axis (X_s - X_t) / q + (rho_s - rho_t), where the wrapped grid
-// difference picks the image (the same decision as the FP32 sum) and the
-// residuals rho = y - X / q restore the FP64 separation of that image to
-// rounding.  The set of periodic axes is a template argument.
-//
-// What bounds it: VALU issue.  FP64 and conversions take one cycle per wave
-// instruction and CU (no two waves issue together), an FP64 transcendental
-// four; 62.5 cycles per pair with three of them and four instructions per
-// axis of R1, 50 now (41 with two closed axes).  2e4 points, two closed axes:
-// 0.61 -> 0.76 Tpairs/s with the error against 64 bits 5.9e-15 -> 1.3e-15.
-struct __align__(16) BsSrcD {
-  double rx, ry, rz;  // the segment's start: residual (periodic axis) or position (closed axis)
-  double q;           // |d|^2
-  double dx, dy, dz;  // 2 d
-  uint32_t x, y, z;   // grid coordinates (periodic axes)
-  int32_t kn;         // index of the segment's end
-};
-
-template <bool kPeriodic>
-__device__ inline double bs_sep(uint32_t xs, uint32_t xt, double rs, double rt, double g) {
-  return kPeriodic ? fma((double)(int)(xs - xt), g, rs - rt) : rs - rt;
-}
-
-// Targets per lane of the FP64 sum: index, exclusion index (-1: none),
-// position data and the sums.
-struct BsTgtD {
-  uint32_t x, y, z;
-  int jj;
-  double rx, ry, rz, ax, ay, az;
-};
-
 template <int kPer, int NT, bool kCheck>
 __device__ inline void bs_tile_f64(const BsSrcD* src, int cnt, int t0, BsTgtD* tg, double gx,
                                    double gy, double gz) {
@@ -340,34 +181,9 @@ __device__ inline void bs_tile_f64(const BsSrcD* src, int cnt, int t0, BsTgtD* t
   for (int s = 0; s < cnt; ++s) {
     const BsSrcD g = src[s];
 #pragma unroll
-    for (int m = 0; m < NT; ++m) {
-      BsTgtD& t = tg[m];
-      const double r1x = bs_sep<(kPer & 1) != 0>(g.x, t.x, g.rx, t.rx, gx);
-      const double r1y = bs_sep<(kPer & 2) != 0>(g.y, t.y, g.ry, t.ry, gy);
-      const double r1z = bs_sep<(kPer & 4) != 0>(g.z, t.z, g.rz, t.rz, gz);
-      const double n1 = fma(r1x, r1x, fma(r1y, r1y, r1z * r1z));
-      const double n2 = n1 + fma(r1x, g.dx, fma(r1y, g.dy, fma(r1z, g.dz, g.q)));
-      const double n12 = n1 * n2;
-      const double y = __builtin_amdgcn_rsq(n12);
-      const double p = n12 * y;
-      const double s2 = fma(p, fma(-p, y, 1.0), fma(2.0, p, n1 + n2));
-      const double w = s2 - g.q;
-      const double arg = (s2 * n12) * (w * w);
-      const double z = __builtin_amdgcn_rsq(arg);
-      double f = (s2 * z) * fma(-(arg * z), z, 3.0);
-      if (kCheck) f = (t0 + s == t.jj || g.kn == t.jj) ? 0.0 : f;
-      t.ax = fma(f, fma(r1y, g.dz, -(r1z * g.dy)), t.ax);
-      t.ay = fma(f, fma(r1z, g.dx, -(r1x * g.dz)), t.ay);
-      t.az = fma(f, fma(r1x, g.dy, -(r1y * g.dx)), t.az);
-    }
+    for (int m = 0; m < NT; ++m)
+      bs_pair_f64<kPer>(g, tg[m], kCheck && (t0 + s == tg[m].jj || g.kn == tg[m].jj), gx, gy, gz);
   }
-}
-
-// Grid coordinate and residual of a coordinate on a periodic axis.
-__device__ inline void bs_grid_f64(double y, double q, double invq, uint32_t& x, double& r) {
-  const double s = floor(y * q);
-  x = (uint32_t)(long long)s;
-  r = y - s * invq;
 }
 
 template <int kPer, int NT>
@@ -396,14 +212,7 @@ __global__ __launch_bounds__(256) void k_bs_f64(BsPts in, int32_t* __restrict__ 
 #pragma unroll
     for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
     BsTgtD& t = tg[m];
-    t.x = t.y = t.z = 0u;
-    t.rx = y[0];
-    t.ry = y[1];
-    t.rz = y[2];
-    if (kPer & 1) bs_grid_f64(y[0], bx.q[0], bx.invq_d[0], t.x, t.rx);
-    if (kPer & 2) bs_grid_f64(y[1], bx.q[1], bx.invq_d[1], t.y, t.ry);
-    if (kPer & 4) bs_grid_f64(y[2], bx.q[2], bx.invq_d[2], t.z, t.rz);
-    t.ax = t.ay = t.az = 0.0;
+    bs_target_f64<kPer>(y, bx, t);
     // the target's own two segments are excluded in copy 0 and, for the end
     // of an open line, in the copy mirrored in its wall
     bool ex = j < n && copy == 0;
@@ -417,39 +226,7 @@ __global__ __launch_bounds__(256) void k_bs_f64(BsPts in, int32_t* __restrict__ 
   static_assert(sizeof(src) >= 9 * kT * sizeof(double), "the wave sums reuse the tile");
   for (int t0 = kb; t0 < ke; t0 += kTile) {
     const int k = t0 + threadIdx.x;
-    if (k < ke) {
-      BsSrcD g;
-      g.kn = min(max(in.nxt[k], 0), n - 1);
-      double r[3], d[3];
-      uint32_t x[3] = {0u, 0u, 0u};
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const double y = in.Y[a * in.sa + k * in.sj];
-        d[a] = in.Y[a * in.sa + g.kn * in.sj] - y;
-        if ((kPer >> a) & 1) {
-          if (d[a] > 0.5 * bx.L[a])
-            d[a] = d[a] - bx.L[a];
-          else if (d[a] < -0.5 * bx.L[a])
-            d[a] = d[a] + bx.L[a];
-          bs_grid_f64(y, bx.q[a], bx.invq_d[a], x[a], r[a]);
-        } else {
-          const int rm = bx.refl[copy][a];
-          r[a] = bs_mirror(y, rm, bx.L[a]);
-          d[a] = rm ? -d[a] : d[a];
-        }
-      }
-      g.rx = r[0];
-      g.ry = r[1];
-      g.rz = r[2];
-      g.x = x[0];
-      g.y = x[1];
-      g.z = x[2];
-      g.q = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-      g.dx = 2.0 * d[0];
-      g.dy = 2.0 * d[1];
-      g.dz = 2.0 * d[2];
-      src[threadIdx.x] = g;
-    }
+    if (k < ke) src[threadIdx.x] = bs_stage_f64<kPer>(in, k, n, copy, bx);
     __syncthreads();
     int lo, hi;
     wave_range(min(kTile, ke - t0), w, lo, hi);

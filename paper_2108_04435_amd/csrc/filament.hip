@@ -8,7 +8,9 @@
 //    cell of its stencil's lower corner (its bin); each touched node is then
 //    owned by exactly one bin and gathers the contributions of the (at most
 //    8) bins around it, each bin's points in ascending order.
-#include "vlb_internal.h"
+#include "bs_pair.h"
+
+#include <type_traits>
 
 namespace vlb {
 
@@ -165,58 +167,32 @@ __device__ void interp_vn(const UT* __restrict__ ub, const Geom& g, double px, d
   }
 }
 
-// 64 points per block of kFinWaves waves.  The waves add the Biot-Savart
-// chunk partials of the block's points (wave g takes chunks g, g + kFinWaves,
-// ..., eight chunks' loads in flight at a time); before its share, wave 1
-// interpolates the normal-fluid velocity, wave 2 evaluates the local
-// geometry and the LIA term and wave 3 loads the RK4 state, so that these
-// load chains overlap.  Wave 0 then combines the parts in a fixed order and
-// does the rest per point.
-constexpr int kFinPts = 64;
-constexpr int kFinWaves = 4;
+// What waves 1 to 3 of a block find for its N points, one lane per point.
+template <int N>
+struct FinShared {
+  double vn[3][N];   // wave 1: normal-fluid velocity
+  double geo[8][N];  // wave 2: s' (3), LIA (3), real l+, l-
+  int end[N];        // wave 2: wall axis of an open line's end, or -1
+  double rk[9][N];   // wave 3: s^n (3), ksum (3), superflow, alpha, alpha'
+};
 
-template <class UT, class PT>
-__global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
-  __shared__ double red[kFinWaves - 1][3][kFinPts];  // chunk sums of waves 1..kFinWaves-1
-  __shared__ double s_vn[3][kFinPts];    // wave 1: normal-fluid velocity
-  __shared__ double s_geo[8][kFinPts];   // wave 2: s' (3), LIA (3), real l+, l-
-  __shared__ int s_end[kFinPts];         // wave 2: wall axis of an open line's end, or -1
-  __shared__ double s_rk[9][kFinPts];    // wave 3: s^n (3), ksum (3), superflow, alpha, alpha'
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int j = blockIdx.x * kFinPts + lane;
-  const int n = A.cnt[0];
-  const bool live = j < n;
+// Wave 1 interpolates the normal-fluid velocity (and, at the step's first
+// stage, pushes the point on its spreading bin), wave 2 evaluates the local
+// geometry and the LIA term, wave 3 loads the RK4 state, so that these load
+// chains overlap.  slot: j is below the capacity (every load is in bounds,
+// non-finite values are harmless); live: j is a point.
+template <class UT, int N>
+__device__ __forceinline__ void fin_roles(const FinArgs& A, int grp, int lane, int j, bool slot,
+                                          bool live, FinShared<N>& sh) {
   const long long nc = A.ncap;
-  // The loads do not wait for the point count: every slot below the
-  // capacity is read (indices clamped into the arrays, non-finite values
-  // harmless), and only live points write.
-  const bool slot = j < nc;
-  // the first batch of this wave's Biot-Savart chunk partials (chunks grp,
-  // grp + kFinWaves, ..., up to 8 of them; beyond S they read as zero, which
-  // adds nothing), loaded before the wave's own work so that the latencies
-  // overlap
-  const PT* __restrict__ P = (const PT*)A.P;
-  const long long jc = slot ? j : 0;  // in-bounds index for the unconditional loads
-  PT v0[8][3];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const bool ok = slot && grp + kFinWaves * u < A.S;
-    const long long c = ok ? grp + kFinWaves * u : 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const PT x = P[(c * 3 + a) * nc + jc];
-      v0[u][a] = ok ? x : (PT)0;
-    }
-  }
   const Geom& g = A.g;
   const double L[3] = {(double)g.nx, (double)g.ny, (double)g.nz};
   const int per[3] = {!g.wall[0], !g.wall[1], !g.wall[2]};
-
   if (slot && grp == 1) {
     const double p[3] = {A.Y[j], A.Y[nc + j], A.Y[2 * nc + j]};
     double vn[3];
     interp_vn<UT>((const UT*)A.ub, g, p[0], p[1], p[2], vn);
-    for (int a = 0; a < 3; ++a) s_vn[a][lane] = vn[a];
+    for (int a = 0; a < 3; ++a) sh.vn[a][lane] = vn[a];
     if (live && A.skeys) {
       int b[3];
       const uint32_t key = base_key(A.sg, p, b);
@@ -225,7 +201,6 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
       for (int a = 0; a < 3; ++a) A.sfrac[a * nc + j] = p[a] - floor(p[a]);
     }
   }
-  if (A.skeys && blockIdx.x == 0 && threadIdx.x == 0) A.cnt[11] = n;
   if (slot && grp == 2) {
     // local geometry (three-point derivatives on a non-uniform arc length)
     const int jn = min(max(A.nxt[j], 0), (int)nc - 1), jp = min(max(A.prv[j], 0), (int)nc - 1);
@@ -254,7 +229,7 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
         for (int a = 0; a < 3; ++a) dm[a] = a == ea ? dp[a] : -dp[a];
       }
     }
-    s_end[lane] = ea;
+    sh.end[lane] = ea;
     const double lp = sqrt(dp[0] * dp[0] + dp[1] * dp[1] + dp[2] * dp[2]);
     const double lm = sqrt(dm[0] * dm[0] + dm[1] * dm[1] + dm[2] * dm[2]);
     const double iden = 1.0 / (lp * lm * (lp + lm));
@@ -268,18 +243,18 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
     // LIA: beta s' x s'', beta = kappa/(4 pi) ln(2 sqrt(l+ l-) / (e^C a))
     //                          = kappa/(4 pi) (ln(l+ l-) / 2 + ln(2 / (e^C a)))
     const double beta = A.bs_scale * fma(0.5, log(lp * lm), A.ln2_ea);
-    s_geo[3][lane] = beta * (sp[1] * spp[2] - sp[2] * spp[1]);
-    s_geo[4][lane] = beta * (sp[2] * spp[0] - sp[0] * spp[2]);
-    s_geo[5][lane] = beta * (sp[0] * spp[1] - sp[1] * spp[0]);
-    for (int a = 0; a < 3; ++a) s_geo[a][lane] = sp[a];
-    s_geo[6][lane] = lp_real;
-    s_geo[7][lane] = lm_real;
+    sh.geo[3][lane] = beta * (sp[1] * spp[2] - sp[2] * spp[1]);
+    sh.geo[4][lane] = beta * (sp[2] * spp[0] - sp[0] * spp[2]);
+    sh.geo[5][lane] = beta * (sp[0] * spp[1] - sp[1] * spp[0]);
+    for (int a = 0; a < 3; ++a) sh.geo[a][lane] = sp[a];
+    sh.geo[6][lane] = lp_real;
+    sh.geo[7][lane] = lm_real;
   }
   if (slot && grp == 3) {
     if (!A.eval_only)
       for (int a = 0; a < 3; ++a) {
-        s_rk[a][lane] = A.pos[a * nc + j];
-        s_rk[3 + a][lane] = A.stage > 1 ? A.ksum[a * nc + j] : 0.0;
+        sh.rk[a][lane] = A.pos[a * nc + j];
+        sh.rk[3 + a][lane] = A.stage > 1 ? A.ksum[a * nc + j] : 0.0;
       }
     if (A.mass_balance) {
       const int ma = A.mb_axis;
@@ -290,7 +265,7 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
       int i0 = ifloor_safe(pz), i1 = i0 + 1;
       i0 = ((i0 % nm) + nm) % nm;
       i1 = ((i1 % nm) + nm) % nm;
-      s_rk[6][lane] = (1.0 - t) * A.Vs[i0] + t * A.Vs[i1];
+      sh.rk[6][lane] = (1.0 - t) * A.Vs[i0] + t * A.Vs[i1];
     }
     // mutual-friction coefficients at the point's height: the constants,
     // or the slice profiles linear between floor(z) and floor(z) + 1
@@ -310,9 +285,147 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
       al = (1.0 - t) * A.fric[i0] + t * A.fric[i1];
       alp = (1.0 - t) * A.fric[g.nz + i0] + t * A.fric[g.nz + i1];
     }
-    s_rk[7][lane] = al;
-    s_rk[8][lane] = alp;
+    sh.rk[7][lane] = al;
+    sh.rk[8][lane] = alp;
   }
+}
+
+// The rest of a stage for live point j from its non-local velocity vs.
+template <int N>
+__device__ __forceinline__ void fin_combine(const FinArgs& A, int lane, int j, double vs[3],
+                                            const FinShared<N>& sh) {
+  const long long nc = A.ncap;
+  const Geom& g = A.g;
+  const double L[3] = {(double)g.nx, (double)g.ny, (double)g.nz};
+  const int per[3] = {!g.wall[0], !g.wall[1], !g.wall[2]};
+  double sp[3];
+  for (int a = 0; a < 3; ++a) {
+    sp[a] = sh.geo[a][lane];
+    vs[a] += sh.geo[3 + a][lane];
+  }
+  const double lp = sh.geo[6][lane], lm = sh.geo[7][lane];
+  for (int a = 0; a < 3; ++a) vs[a] += A.vs_app[a];
+  if (A.mass_balance) vs[A.mb_axis] += sh.rk[6][lane];
+
+  // normal-fluid velocity at the point
+  const double vn[3] = {sh.vn[0][lane], sh.vn[1][lane], sh.vn[2][lane]};
+
+  // Schwarz equation of motion (Sec. II.A, Eq. E of M)
+  const double w[3] = {vn[0] - vs[0], vn[1] - vs[1], vn[2] - vs[2]};
+  const double sxw[3] = {sp[1] * w[2] - sp[2] * w[1], sp[2] * w[0] - sp[0] * w[2],
+                         sp[0] * w[1] - sp[1] * w[0]};
+  const double ssw[3] = {sp[1] * sxw[2] - sp[2] * sxw[1], sp[2] * sxw[0] - sp[0] * sxw[2],
+                         sp[0] * sxw[1] - sp[1] * sxw[0]};
+  const double al = sh.rk[7][lane], alp = sh.rk[8][lane];
+  double sd[3];
+  for (int a = 0; a < 3; ++a) sd[a] = vs[a] + al * sxw[a] - alp * ssw[a];
+  // an open line's end slides on its wall: no velocity normal to it
+  const int ea = sh.end[lane];
+  if (ea >= 0) sd[ea] = 0.0;
+  if (!(isfinite(sd[0]) && isfinite(sd[1]) && isfinite(sd[2])))
+    atomicOr(&A.cnt[7], kFlagNumeric);
+
+  if (A.first) {
+    for (int a = 0; a < 3; ++a) {
+      A.vs1[a * nc + j] = vs[a];
+      A.vn1[a * nc + j] = vn[a];
+      A.sd1[a * nc + j] = sd[a];
+    }
+    // reaction on the normal fluid (Magnus balance), per point, with the
+    // line length (l+ + l-)/2 carried by the point (the real segments)
+    const double r[3] = {sd[0] - vs[0], sd[1] - vs[1], sd[2] - vs[2]};
+    const double sxr[3] = {sp[1] * r[2] - sp[2] * r[1], sp[2] * r[0] - sp[0] * r[2],
+                           sp[0] * r[1] - sp[1] * r[0]};
+    const double dxi = 0.5 * (lp + lm);
+    for (int a = 0; a < 3; ++a) {
+      const double w = A.force_model ? r[a] : sxr[a];  // literal reading: for ablation
+      A.gpt[a * nc + j] = A.coupling ? A.rs_rn * A.kappa * w * dxi : 0.0;
+    }
+  }
+  if (A.eval_only) return;
+
+  // Runge-Kutta over a substep of length h from s0 (the substep's start):
+  // classical (4 stages): ksum = k1 + 2 k2 + 2 k3 + k4, stage positions
+  // s0 + (h/2) k1, s0 + (h/2) k2, s0 + h k3, result s0 + h ksum / 6;
+  // midpoint (2): s0 + (h/2) k1, result s0 + h k2; Euler (1): s0 + h k1
+  for (int a = 0; a < 3; ++a) {
+    const double s0 = sh.rk[a][lane];
+    const double kp = sh.rk[3 + a][lane];
+    double ks = sd[a];
+    double y;
+    if (A.rk == 4) {
+      switch (A.stage) {
+        case 1:
+          y = s0 + A.hh * sd[a];
+          break;
+        case 2:
+          ks = kp + 2.0 * sd[a];
+          y = s0 + A.hh * sd[a];
+          break;
+        case 3:
+          ks = kp + 2.0 * sd[a];
+          y = s0 + A.h * sd[a];
+          break;
+        default:
+          ks = kp + sd[a];
+          y = s0 + A.h * (ks / 6.0);
+          break;
+      }
+    } else if (A.rk == 2 && A.stage == 1) {
+      y = s0 + A.hh * sd[a];
+    } else {
+      y = s0 + A.h * sd[a];
+    }
+    A.ksum[a * nc + j] = ks;
+    const double yw = wrap_coord(y, L[a], per[a]);
+    A.Ynext[a * nc + j] = yw;
+    if (A.X) {
+      const double sgrid = floor((yw + A.ax.off[a]) * A.ax.q[a]);
+      A.X[a * nc + j] = A.ax.periodic[a] ? (uint32_t)(long long)sgrid : (uint32_t)(int)(long long)sgrid;
+    }
+  }
+}
+
+// 64 points per block of kFinWaves waves.  The waves add the Biot-Savart
+// chunk partials of the block's points (wave g takes chunks g, g + kFinWaves,
+// ..., eight chunks' loads in flight at a time); before its share, each wave
+// but the first has its own role (fin_roles).  Wave 0 then combines the parts
+// in a fixed order and does the rest per point.
+constexpr int kFinPts = 64;
+constexpr int kFinWaves = 4;
+
+template <class UT, class PT>
+__global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
+  __shared__ double red[kFinWaves - 1][3][kFinPts];  // chunk sums of waves 1..kFinWaves-1
+  __shared__ FinShared<kFinPts> sh;
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int j = blockIdx.x * kFinPts + lane;
+  const int n = A.cnt[0];
+  const bool live = j < n;
+  const long long nc = A.ncap;
+  // The loads do not wait for the point count: every slot below the
+  // capacity is read (indices clamped into the arrays, non-finite values
+  // harmless), and only live points write.
+  const bool slot = j < nc;
+  // the first batch of this wave's Biot-Savart chunk partials (chunks grp,
+  // grp + kFinWaves, ..., up to 8 of them; beyond S they read as zero, which
+  // adds nothing), loaded before the wave's own work so that the latencies
+  // overlap
+  const PT* __restrict__ P = (const PT*)A.P;
+  const long long jc = slot ? j : 0;  // in-bounds index for the unconditional loads
+  PT v0[8][3];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const bool ok = slot && grp + kFinWaves * u < A.S;
+    const long long c = ok ? grp + kFinWaves * u : 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const PT x = P[(c * 3 + a) * nc + jc];
+      v0[u][a] = ok ? x : (PT)0;
+    }
+  }
+  if (A.skeys && blockIdx.x == 0 && threadIdx.x == 0) A.cnt[11] = n;
+  fin_roles<UT>(A, grp, lane, j, slot, live, sh);
 
   // non-local Biot-Savart: chunk partials added in a fixed order
   double vs[3] = {0.0, 0.0, 0.0};
@@ -349,93 +462,114 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
     for (int w = 0; w < kFinWaves - 1; ++w) t += red[w][a][lane];
     vs[a] = t * A.nl_scale;
   }
+  fin_combine(A, lane, j, vs, sh);
+}
 
-  double sp[3];
-  for (int a = 0; a < 3; ++a) {
-    sp[a] = s_geo[a][lane];
-    vs[a] += s_geo[3 + a][lane];
+// One stage of a small run in one launch: the pair sum and the finalize of 8
+// points per block.  Waves 0 to 3: thread (slice, target) adds every 32nd
+// segment of the staged tiles for its target; the 32 slices are added in
+// FP64 in a fixed tree.  Waves 5 to 7 meanwhile take the roles of the
+// finalize (fin_roles; wave 4 has none).  Source records come from the
+// positions Y (other blocks may already write the next stage's), in FP32
+// too.
+//
+// What bounds it: latency.  A ring of 64 points spent 4.4 us in the sum, 7.9
+// in the finalize and about 4 between them per stage; with the roles before
+// the sum on the same waves this kernel took 10.4.  It pays while the chip
+// is not filled by the sum (kStagePoints).
+constexpr int kStTargets = 8;
+constexpr int kStThreads = 256;  // threads of the sum
+constexpr int kStSlices = kStThreads / kStTargets;
+
+template <bool kF32, int kVar, class UT>
+__global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx) {
+  using Src = std::conditional_t<kF32, BsSrc, BsSrcD>;
+  __shared__ Src src[kStThreads];
+  __shared__ FinShared<kStTargets> sh;
+  __shared__ double red[4][3][kStTargets];
+  const int n = A.cnt[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (A.skeys) A.cnt[11] = n;
+    if (n > 2)
+      *(long long*)(A.cnt + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
   }
-  const double lp = s_geo[6][lane], lm = s_geo[7][lane];
-  for (int a = 0; a < 3; ++a) vs[a] += A.vs_app[a];
-  if (A.mass_balance) vs[A.mb_axis] += s_rk[6][lane];
-
-  // normal-fluid velocity at the point
-  const double vn[3] = {s_vn[0][lane], s_vn[1][lane], s_vn[2][lane]};
-
-  // Schwarz equation of motion (Sec. II.A, Eq. E of M)
-  const double w[3] = {vn[0] - vs[0], vn[1] - vs[1], vn[2] - vs[2]};
-  const double sxw[3] = {sp[1] * w[2] - sp[2] * w[1], sp[2] * w[0] - sp[0] * w[2],
-                         sp[0] * w[1] - sp[1] * w[0]};
-  const double ssw[3] = {sp[1] * sxw[2] - sp[2] * sxw[1], sp[2] * sxw[0] - sp[0] * sxw[2],
-                         sp[0] * sxw[1] - sp[1] * sxw[0]};
-  const double al = s_rk[7][lane], alp = s_rk[8][lane];
-  double sd[3];
-  for (int a = 0; a < 3; ++a) sd[a] = vs[a] + al * sxw[a] - alp * ssw[a];
-  // an open line's end slides on its wall: no velocity normal to it
-  const int ea = s_end[lane];
-  if (ea >= 0) sd[ea] = 0.0;
-  if (!(isfinite(sd[0]) && isfinite(sd[1]) && isfinite(sd[2])))
-    atomicOr(&A.cnt[7], kFlagNumeric);
-
-  if (A.first) {
-    for (int a = 0; a < 3; ++a) {
-      A.vs1[a * nc + j] = vs[a];
-      A.vn1[a * nc + j] = vn[a];
-      A.sd1[a * nc + j] = sd[a];
-    }
-    // reaction on the normal fluid (Magnus balance), per point, with the
-    // line length (l+ + l-)/2 carried by the point (the real segments)
-    const double r[3] = {sd[0] - vs[0], sd[1] - vs[1], sd[2] - vs[2]};
-    const double sxr[3] = {sp[1] * r[2] - sp[2] * r[1], sp[2] * r[0] - sp[0] * r[2],
-                           sp[0] * r[1] - sp[1] * r[0]};
-    const double dxi = 0.5 * (lp + lm);
-    for (int a = 0; a < 3; ++a) {
-      const double w = A.force_model ? r[a] : sxr[a];  // literal reading: for ablation
-      A.gpt[a * nc + j] = A.coupling ? A.rs_rn * A.kappa * w * dxi : 0.0;
-    }
-  }
-  if (A.eval_only) return;
-
-  // Runge-Kutta over a substep of length h from s0 (the substep's start):
-  // classical (4 stages): ksum = k1 + 2 k2 + 2 k3 + k4, stage positions
-  // s0 + (h/2) k1, s0 + (h/2) k2, s0 + h k3, result s0 + h ksum / 6;
-  // midpoint (2): s0 + (h/2) k1, result s0 + h k2; Euler (1): s0 + h k1
-  for (int a = 0; a < 3; ++a) {
-    const double s0 = s_rk[a][lane];
-    const double kp = s_rk[3 + a][lane];
-    double ks = sd[a];
-    double y;
-    if (A.rk == 4) {
-      switch (A.stage) {
-        case 1:
-          y = s0 + A.hh * sd[a];
-          break;
-        case 2:
-          ks = kp + 2.0 * sd[a];
-          y = s0 + A.hh * sd[a];
-          break;
-        case 3:
-          ks = kp + 2.0 * sd[a];
-          y = s0 + A.h * sd[a];
-          break;
-        default:
-          ks = kp + sd[a];
-          y = s0 + A.h * (ks / 6.0);
-          break;
+  const int j0 = blockIdx.x * kStTargets;
+  if (j0 >= n) return;
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  if (grp >= 4) {
+    if (lane < kStTargets)
+      fin_roles<UT>(A, grp - 4, lane, j0 + lane, j0 + lane < A.ncap, j0 + lane < n, sh);
+    // the barriers of the sum
+    for (int copy = 0; copy < bx.copies; ++copy)
+      for (int t0 = 0; t0 < n; t0 += kStThreads) {
+        __syncthreads();
+        __syncthreads();
       }
-    } else if (A.rk == 2 && A.stage == 1) {
-      y = s0 + A.hh * sd[a];
-    } else {
-      y = s0 + A.h * sd[a];
-    }
-    A.ksum[a * nc + j] = ks;
-    const double yw = wrap_coord(y, L[a], per[a]);
-    A.Ynext[a * nc + j] = yw;
-    if (A.X) {
-      const double sgrid = floor((yw + A.ax.off[a]) * A.ax.q[a]);
-      A.X[a * nc + j] = A.ax.periodic[a] ? (uint32_t)(long long)sgrid : (uint32_t)(int)(long long)sgrid;
-    }
+    __syncthreads();
+    return;
   }
+
+  const int tl = threadIdx.x % kStTargets, sl = threadIdx.x / kStTargets;
+  const int j = j0 + tl;
+  const int jc = min(j, n - 1);  // lanes beyond the points repeat the last one, unwritten
+  double y[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
+  int oc = 0;  // the image copy whose own segments are excluded too
+  if (bx.copies > 1 && (in.nxt[jc] == jc || in.prv[jc] == jc)) oc = bs_own_copy(y, bx);
+  uint32_t xt[3] = {0u, 0u, 0u};
+  BsTgtD td;
+  if constexpr (kF32) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) xt[a] = bs_grid_f32(y[a], bx, a);
+  } else {
+    bs_target_f64<kVar>(y, bx, td);
+  }
+  double v[3] = {0.0, 0.0, 0.0};
+  for (int copy = 0; copy < bx.copies; ++copy) {
+    const int jj = copy == 0 || copy == oc ? jc : -1;
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    td.ax = td.ay = td.az = 0.0;
+    for (int t0 = 0; t0 < n; t0 += kStThreads) {
+      const int k = t0 + threadIdx.x;
+      if (k < n) {
+        if constexpr (kF32)
+          src[threadIdx.x] = bs_stage_f32<kVar != 0, true>(
+              in, nullptr, 0, k, n, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
+        else
+          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, n, copy, bx);
+      }
+      __syncthreads();
+      const int cnt = min(kStThreads, n - t0);
+#pragma unroll 2
+      for (int s = sl; s < cnt; s += kStSlices) {
+        const Src g = src[s];
+        const bool ex = t0 + s == jj || g.kn == jj;
+        if constexpr (kF32)
+          bs_pair_f32<kVar != 0>(g, xt[0], xt[1], xt[2], bx.invq_f[0], bx.invq_f[1], bx.invq_f[2],
+                                 ex, fx, fy, fz);
+        else
+          bs_pair_f64<kVar>(g, td, ex, bx.invq_d[0], bx.invq_d[1], bx.invq_d[2]);
+      }
+      __syncthreads();
+    }
+    const double sg = (kF32 ? 1.0 : 0.5) * (double)bx.sign[copy];
+    v[0] += sg * (kF32 ? (double)fx : td.ax);
+    v[1] += sg * (kF32 ? (double)fy : td.ay);
+    v[2] += sg * (kF32 ? (double)fz : td.az);
+  }
+#pragma unroll
+  for (int off = kStTargets; off < 64; off <<= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] += __shfl_xor(v[a], off);
+  if (lane < kStTargets)
+    for (int a = 0; a < 3; ++a) red[grp][a][lane] = v[a];
+  __syncthreads();
+  if (threadIdx.x >= kStTargets || j >= n) return;
+  double vs[3];
+  for (int a = 0; a < 3; ++a)
+    vs[a] = (((red[0][a][lane] + red[1][a][lane]) + red[2][a][lane]) + red[3][a][lane]) * A.nl_scale;
+  fin_combine(A, lane, j, vs, sh);
 }
 
 // ----------------------------------------------------------- spreading
@@ -464,7 +598,7 @@ struct BinPoint {
   }
 };
 
-__device__ inline void add_many(int head, int m, int n, const int32_t* __restrict__ bnext,
+__device__ __noinline__ void add_many(int head, int m, int n, const int32_t* __restrict__ bnext,
                                 const BinPoint& at, double f[3]) {
   double c[3], big[3] = {0.0, 0.0, 0.0};
   bool bad[3] = {false, false, false};
@@ -492,91 +626,72 @@ __device__ inline void add_many(int head, int m, int n, const int32_t* __restric
   for (int a = 0; a < 3; ++a) f[a] += bad[a] ? __builtin_nan("") : ldexp((double)s[a], -e[a]);
 }
 
-// One thread per (point, stencil corner).  Only the point at the head of its
-// bin's list acts: the node at that corner of the bin's stencil is written
-// by the occupied bin of smallest key among the (up to 8) bins whose
-// stencils contain it, which gathers those bins' points in a fixed order.
-// The nodes written are listed; the next moments kernel zeroes them.
+// One wave per point, lane (o, q): corner o of the stencil of the point's
+// bin and, around that node, bin q of the (up to 8) whose stencils contain
+// it (the node is that bin's corner q).  Only the point at the head of its
+// bin's list acts: the node is written by the occupied bin of smallest key,
+// each lane gathering its bin's points in a fixed order and the eight lanes
+// of a node adding their sums in the order of q.  The nodes written are
+// listed; the next moments kernel zeroes them.
 //
 // What bounds it: latency (list heads, links, offsets: dependent loads).
 // With a stable sort of the points by bin in place of the lists, the
 // spreading was ten launches, 65 us of a served step (128x128x256, 2e3
-// points); this one takes 13.
+// points); with one thread per node walking the eight bins in turn 13 us.
 template <class FT>
 __global__ __launch_bounds__(256) void k_spread_gather(
     const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
     const int32_t* __restrict__ bnext, const double* __restrict__ sfrac,
     const double* __restrict__ gpt, int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
     long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
-  const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = (int)(id >> 3);
-  const int o = (int)(id & 7);
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int o = lane >> 3, q = lane & 7;
   const uint32_t me = r < ncap ? skey[r] : 0u;  // (beyond the points: unused)
   const int n = cnt[11];
-  if (id == 0) cnt[1] = 8 * n;
+  if (r == 0 && lane == 0) cnt[1] = 8 * n;
   if (r >= n) return;
   if (bins[me] != r) {
-    touched[id] = -1;
+    if (q == 0) touched[8LL * r + o] = -1;
     return;
   }
-  int b[3];
-  b[0] = (int)(me % (uint32_t)sg.ext[0]);
-  b[1] = (int)((me / (uint32_t)sg.ext[0]) % (uint32_t)sg.ext[1]);
-  b[2] = (int)(me / ((uint32_t)sg.ext[0] * (uint32_t)sg.ext[1]));
-  const int off[3] = {o & 1, (o >> 1) & 1, (o >> 2) & 1};
-  int e[3];    // node in bin coordinates
-  int lat[3];  // node in lattice coordinates
-  bool ghost = false;
+  const int b[3] = {(int)(me % (uint32_t)sg.ext[0]),
+                    (int)((me / (uint32_t)sg.ext[0]) % (uint32_t)sg.ext[1]),
+                    (int)(me / ((uint32_t)sg.ext[0] * (uint32_t)sg.ext[1]))};
+  // the node, in lattice coordinates (ghost: beyond a wall), and its bin q
+  int lat[3], c[3];
+  bool ghost = false, ok = true;
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
-    e[a] = b[a] + off[a];
+    int e = b[a] + ((o >> a) & 1);
     if (sg.wall[a]) {
-      lat[a] = e[a] - 1;
-      if (lat[a] < 0 || lat[a] >= sg.n[a]) ghost = true;
+      lat[a] = e - 1;
+      ghost = ghost || lat[a] < 0 || lat[a] >= sg.n[a];
     } else {
-      if (e[a] >= sg.n[a]) e[a] -= sg.n[a];
-      lat[a] = e[a];
+      if (e >= sg.n[a]) e -= sg.n[a];
+      lat[a] = e;
     }
-  }
-  if (ghost) {
-    touched[id] = -1;
-    return;
-  }
-  // the bins whose stencil contains this node: e - o' for o' in {0,1}^3
-  uint32_t kq[8];
-  int lo[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int oq[3] = {q & 1, (q >> 1) & 1, (q >> 2) & 1};
-    int c[3];
-    bool ok = true;
-    for (int a = 0; a < 3; ++a) {
-      c[a] = e[a] - oq[a];
-      if (sg.wall[a]) {
-        if (c[a] < 0) ok = false;
-      } else if (c[a] < 0) {
+    c[a] = e - ((q >> a) & 1);
+    if (c[a] < 0) {
+      if (sg.wall[a])
+        ok = false;
+      else
         c[a] += sg.n[a];
-      }
     }
-    kq[q] = (uint32_t)(((long long)c[2] * sg.ext[1] + c[1]) * sg.ext[0] + c[0]);
-    lo[q] = ok ? bins[kq[q]] : -1;
   }
-  bool owner = true;
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-    if (lo[q] >= 0 && kq[q] < me) owner = false;
-  if (!owner) {
-    touched[id] = -1;
-    return;
-  }
+  const uint32_t kq = (uint32_t)(((long long)c[2] * sg.ext[1] + c[1]) * sg.ext[0] + c[0]);
+  const int head = ok && !ghost ? bins[kq] : -1;
+  // the node is another bin's when one of smaller key is occupied
+  const uint64_t smaller = __ballot(head >= 0 && kq < me);
+  const bool owner = !ghost && ((smaller >> (8 * o)) & 0xffu) == 0;
   double f[3] = {0.0, 0.0, 0.0};
-  for (int q = 0; q < 8; ++q) {
-    if (lo[q] < 0) continue;
+  if (owner && head >= 0) {
     const BinPoint at{sfrac, gpt, ncap, q};
     int first[kOrdered];  // the smallest indices on the list, ascending
 #pragma unroll
     for (int s = 0; s < kOrdered; ++s) first[s] = 0x7fffffff;
     int m = 0;
-    for (int j = lo[q]; (uint32_t)j < (uint32_t)n && m < n; j = bnext[j], ++m) {
+    for (int j = head; (uint32_t)j < (uint32_t)n && m < n; j = bnext[j], ++m) {
       int v = j;
 #pragma unroll
       for (int s = 0; s < kOrdered; ++s) {
@@ -586,30 +701,41 @@ __global__ __launch_bounds__(256) void k_spread_gather(
       }
     }
     if (m > kOrdered) {
-      add_many(lo[q], m, n, bnext, at, f);
-      continue;
-    }
+      add_many(head, m, n, bnext, at, f);
+    } else {
 #pragma unroll
-    for (int s = 0; s < kOrdered; ++s)
-      if (s < m) {
-        double c[3];
-        at(first[s], c);
-        for (int a = 0; a < 3; ++a) f[a] += c[a];
-      }
+      for (int s = 0; s < kOrdered; ++s)
+        if (s < m) {
+          double w[3];
+          at(first[s], w);
+          for (int a = 0; a < 3; ++a) f[a] += w[a];
+        }
+    }
   }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double t = __shfl(f[a], lane & 56);
+#pragma unroll
+    for (int s = 1; s < 8; ++s) t += __shfl(f[a], (lane & 56) + s);
+    f[a] = t;
+  }
+  if (q != 0) return;
   const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
-  F[node] = (FT)f[0];
-  F[cells + node] = (FT)f[1];
-  F[2 * cells + node] = (FT)f[2];
-  touched[id] = (int32_t)node;
+  if (owner) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
+  }
+  touched[8LL * r + o] = owner ? (int32_t)node : -1;
 }
 
 inline int nblocks(long long n, int b) { return (int)((n + b - 1) / b); }
 
 }  // namespace
 
-hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
-                        int eval_only) {
+namespace {
+
+FinArgs fin_args(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
+                 int eval_only) {
   FinArgs A;
   A.ub = r.ub;
   A.g = r.geom;
@@ -659,6 +785,43 @@ hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y,
   A.sfrac = r.sfrac;
   A.bins = r.bins;
   A.bnext = r.bnext;
+  return A;
+}
+
+template <int... V>
+hipError_t launch_stage_f64(const FinArgs& A, const BsPts& in, const BsAxes& ax, int nb,
+                            hipStream_t stream, std::integer_sequence<int, V...>) {
+  using K = void (*)(FinArgs, BsPts, BsAxes);
+  static constexpr K kern[] = {k_stage<false, V, double>...};
+  const int per = (ax.periodic[0] ? 1 : 0) | (ax.periodic[1] ? 2 : 0) | (ax.periodic[2] ? 4 : 0);
+  hipLaunchKernelGGL(kern[per], dim3(nb), dim3(2 * kStThreads), 0, stream, A, in, ax);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext) {
+  FinArgs A = fin_args(r, stage, first, last, Y, Ynext, 0);
+  A.X = nullptr;  // the next stage reads the positions
+  const BsPts in{Y, r.ncap, 1, r.nxt, r.prv};
+  const int nb = nblocks(r.ncap, kStTargets);
+  hipEvent_t b = nullptr;
+  time_begin(r, 0, &b);  // timed with the pair sums
+  hipError_t e = hipSuccess;
+  if (r.prec == VLB_F64) {
+    e = launch_stage_f64(A, in, r.bsax, nb, r.stream, std::make_integer_sequence<int, 8>{});
+  } else {
+    auto kern = r.bsax.uniform ? k_stage<true, 1, float> : k_stage<true, 0, float>;
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(2 * kStThreads), 0, r.stream, A, in, r.bsax);
+    e = hipGetLastError();
+  }
+  time_end(r, 0, b);
+  return e;
+}
+
+hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
+                        int eval_only) {
+  const FinArgs A = fin_args(r, stage, first, last, Y, Ynext, eval_only);
   const int nb = nblocks(r.ncap, kFinPts);
   switch (r.prec) {
     case VLB_F64: hipLaunchKernelGGL((k_finalize<double, double>), dim3(nb), dim3(kFinWaves * 64), 0, r.stream, A); break;
@@ -682,13 +845,13 @@ hipError_t fil_copy_positions(Run& r, const double* src, double* dst) {
 
 hipError_t fil_spread(Run& r) {
   const SpreadGeom sg = spread_geom(r);
-  const int nb8 = nblocks(8 * r.ncap, 256);
+  const int nb4 = nblocks(r.ncap, 4);
   if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_spread_gather<double>, dim3(nb8), dim3(256), 0, r.stream, r.skeys, r.bins,
+    hipLaunchKernelGGL(k_spread_gather<double>, dim3(nb4), dim3(256), 0, r.stream, r.skeys, r.bins,
                        r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (double*)r.force,
                        r.touched);
   else
-    hipLaunchKernelGGL(k_spread_gather<float>, dim3(nb8), dim3(256), 0, r.stream, r.skeys, r.bins,
+    hipLaunchKernelGGL(k_spread_gather<float>, dim3(nb4), dim3(256), 0, r.stream, r.skeys, r.bins,
                        r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (float*)r.force,
                        r.touched);
   return hipGetLastError();

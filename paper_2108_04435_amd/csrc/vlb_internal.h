@@ -538,6 +538,8 @@ struct Run {
   int64_t step = 0;
   int parity = 0;
   int point_parity = 0;     // which of the two point-array sets is current
+  bool small = false;         // few points: fused filament launches (kStagePoints)
+  bool one_stream = false;    // and a small lattice: no side stream in a step
   bool narrow_steps = false;  // in a step, lattice kernels on a narrow grid
   bool lbm_narrow = false;    // the same, for the launches in progress
   bool has_fields = false;
@@ -552,6 +554,14 @@ struct Run {
 
   std::string err;
 };
+
+// Points (capacity) times source copies up to which a run's stages are fused
+// launches.  Twenty graph steps of a ring of 64 points (capacity 345): 1791
+// -> 1622 us; 500 points (956) level; 1300 points (2076) 8% slower.
+constexpr long long kStagePoints = 1024;
+// Lattice work per step (seconds at 5 TB/s) below which such a run keeps to
+// one stream: a dependency across streams costs 5 to 9 us, twice a step.
+constexpr double kShortLattice = 2e-5;
 
 // error flag bits in cnt[7]
 constexpr int kFlagCapacity = 1;
@@ -615,6 +625,8 @@ int bs_chunks(long long ncap, int copies);
 // grid coordinates for a next sum).
 hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
                         int eval_only);
+// A whole stage (pair sum and finalize) of a small run in one launch.
+hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext);
 hipError_t fil_copy_positions(Run& r, const double* src, double* dst);
 hipError_t fil_spread(Run& r);
 hipError_t fil_seed(Run& r, long long n);
