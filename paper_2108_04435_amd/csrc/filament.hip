@@ -598,7 +598,7 @@ struct BinPoint {
   }
 };
 
-__device__ __noinline__ void add_many(int head, int m, int n, const int32_t* __restrict__ bnext,
+__device__ inline void add_many(int head, int m, int n, const int32_t* __restrict__ bnext,
                                 const BinPoint& at, double f[3]) {
   double c[3], big[3] = {0.0, 0.0, 0.0};
   bool bad[3] = {false, false, false};
@@ -626,52 +626,63 @@ __device__ __noinline__ void add_many(int head, int m, int n, const int32_t* __r
   for (int a = 0; a < 3; ++a) f[a] += bad[a] ? __builtin_nan("") : ldexp((double)s[a], -e[a]);
 }
 
-// One wave per point, lane (o, q): corner o of the stencil of the point's
-// bin and, around that node, bin q of the (up to 8) whose stencils contain
-// it (the node is that bin's corner q).  Only the point at the head of its
-// bin's list acts: the node is written by the occupied bin of smallest key,
-// each lane gathering its bin's points in a fixed order and the eight lanes
-// of a node adding their sums in the order of q.  The nodes written are
-// listed; the next moments kernel zeroes them.
-//
-// What bounds it: latency (list heads, links, offsets: dependent loads).
-// With a stable sort of the points by bin in place of the lists, the
-// spreading was ten launches, 65 us of a served step (128x128x256, 2e3
-// points); with one thread per node walking the eight bins in turn 13 us.
-template <class FT>
-__global__ __launch_bounds__(256) void k_spread_gather(
-    const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
-    const int32_t* __restrict__ bnext, const double* __restrict__ sfrac,
-    const double* __restrict__ gpt, int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
-    long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int o = lane >> 3, q = lane & 7;
-  const uint32_t me = r < ncap ? skey[r] : 0u;  // (beyond the points: unused)
-  const int n = cnt[11];
-  if (r == 0 && lane == 0) cnt[1] = 8 * n;
-  if (r >= n) return;
-  if (bins[me] != r) {
-    if (q == 0) touched[8LL * r + o] = -1;
+// Adds to f the contributions of the points on a bin's list to the node.
+__device__ __forceinline__ void add_bin(int head, int n, const int32_t* __restrict__ bnext,
+                                        const BinPoint& at, double f[3]) {
+  int first[kOrdered];  // the smallest indices on the list, ascending
+#pragma unroll
+  for (int s = 0; s < kOrdered; ++s) first[s] = 0x7fffffff;
+  int m = 0;
+  for (int j = head; (uint32_t)j < (uint32_t)n && m < n; j = bnext[j], ++m) {
+    int v = j;
+#pragma unroll
+    for (int s = 0; s < kOrdered; ++s) {
+      const int t = min(first[s], v);
+      v = max(first[s], v);
+      first[s] = t;
+    }
+  }
+  if (m > kOrdered) {
+    add_many(head, m, n, bnext, at, f);
     return;
   }
-  const int b[3] = {(int)(me % (uint32_t)sg.ext[0]),
-                    (int)((me / (uint32_t)sg.ext[0]) % (uint32_t)sg.ext[1]),
-                    (int)(me / ((uint32_t)sg.ext[0] * (uint32_t)sg.ext[1]))};
-  // the node, in lattice coordinates (ghost: beyond a wall), and its bin q
-  int lat[3], c[3];
-  bool ghost = false, ok = true;
+#pragma unroll
+  for (int s = 0; s < kOrdered; ++s)
+    if (s < m) {
+      double c[3];
+      at(first[s], c);
+      for (int a = 0; a < 3; ++a) f[a] += c[a];
+    }
+}
+
+// Corner o of the stencil of bin `me`: the node in lattice coordinates (lat)
+// and bin coordinates (e); false beyond a wall.
+__device__ inline bool bin_corner(uint32_t me, int o, const SpreadGeom& sg, int e[3], int lat[3]) {
+  e[0] = (int)(me % (uint32_t)sg.ext[0]);
+  e[1] = (int)((me / (uint32_t)sg.ext[0]) % (uint32_t)sg.ext[1]);
+  e[2] = (int)(me / ((uint32_t)sg.ext[0] * (uint32_t)sg.ext[1]));
+  bool inside = true;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    int e = b[a] + ((o >> a) & 1);
+    e[a] += (o >> a) & 1;
     if (sg.wall[a]) {
-      lat[a] = e - 1;
-      ghost = ghost || lat[a] < 0 || lat[a] >= sg.n[a];
+      lat[a] = e[a] - 1;
+      inside = inside && lat[a] >= 0 && lat[a] < sg.n[a];
     } else {
-      if (e >= sg.n[a]) e -= sg.n[a];
-      lat[a] = e;
+      if (e[a] >= sg.n[a]) e[a] -= sg.n[a];
+      lat[a] = e[a];
     }
-    c[a] = e - ((q >> a) & 1);
+  }
+  return inside;
+}
+
+// Bin q around node e, whose corner q the node is; false if there is none.
+__device__ inline bool bin_around(const int e[3], int q, const SpreadGeom& sg, uint32_t& key) {
+  int c[3];
+  bool ok = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    c[a] = e[a] - ((q >> a) & 1);
     if (c[a] < 0) {
       if (sg.wall[a])
         ok = false;
@@ -679,53 +690,89 @@ __global__ __launch_bounds__(256) void k_spread_gather(
         c[a] += sg.n[a];
     }
   }
-  const uint32_t kq = (uint32_t)(((long long)c[2] * sg.ext[1] + c[1]) * sg.ext[0] + c[0]);
-  const int head = ok && !ghost ? bins[kq] : -1;
-  // the node is another bin's when one of smaller key is occupied
-  const uint64_t smaller = __ballot(head >= 0 && kq < me);
-  const bool owner = !ghost && ((smaller >> (8 * o)) & 0xffu) == 0;
+  key = (uint32_t)(((long long)c[2] * sg.ext[1] + c[1]) * sg.ext[0] + c[0]);
+  return ok;
+}
+
+// Threads (point, stencil corner o).  Only the point at the head of its
+// bin's list acts: the node at that corner of the bin's stencil is written
+// by the occupied bin of smallest key among the (up to 8) bins whose
+// stencils contain it, which adds those bins' points in a fixed order.  The
+// nodes written are listed; the next moments kernel zeroes them.  kWave: one
+// wave per point, lane (o, q) adding bin q, the eight lanes of a node then
+// added in the order of q.
+//
+// What bounds it: latency (list heads, links, offsets: dependent loads).
+// With a stable sort of the points by bin in place of the lists, the
+// spreading was ten launches, 65 us of a served step (128x128x256, 2e3
+// points); this is one of 13.  A ring of 64 points, alone on the chip: 12 us
+// by threads walking the eight bins in turn, 4.8 by waves; beside the pair
+// sums of a large run the eight times more waves wait for their slots (9.4e3
+// points: 27 against 33 us), so waves are for small runs (kStagePoints).
+template <class FT, bool kWave>
+__global__ __launch_bounds__(256) void k_spread_gather(
+    const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
+    const int32_t* __restrict__ bnext, const double* __restrict__ sfrac,
+    const double* __restrict__ gpt, int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
+    long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
+  const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = (int)(id >> (kWave ? 6 : 3));
+  const int o = (int)(id >> (kWave ? 3 : 0)) & 7;
+  const uint32_t me = r < ncap ? skey[r] : 0u;  // (beyond the points: unused)
+  const int n = cnt[11];
+  if (id == 0) cnt[1] = 8 * n;
+  if (r >= n) return;
+  int32_t* const mine = touched + 8LL * r + o;
+  int e[3], lat[3];
   double f[3] = {0.0, 0.0, 0.0};
-  if (owner && head >= 0) {
-    const BinPoint at{sfrac, gpt, ncap, q};
-    int first[kOrdered];  // the smallest indices on the list, ascending
-#pragma unroll
-    for (int s = 0; s < kOrdered; ++s) first[s] = 0x7fffffff;
-    int m = 0;
-    for (int j = head; (uint32_t)j < (uint32_t)n && m < n; j = bnext[j], ++m) {
-      int v = j;
-#pragma unroll
-      for (int s = 0; s < kOrdered; ++s) {
-        const int t = min(first[s], v);
-        v = max(first[s], v);
-        first[s] = t;
-      }
+  if constexpr (kWave) {
+    const int q = threadIdx.x & 7;
+    if (bins[me] != r) {  // uniform over the wave
+      if (q == 0) *mine = -1;
+      return;
     }
-    if (m > kOrdered) {
-      add_many(head, m, n, bnext, at, f);
-    } else {
+    const bool inside = bin_corner(me, o, sg, e, lat);
+    uint32_t key;
+    const int head = bin_around(e, q, sg, key) && inside ? bins[key] : -1;
+    const uint64_t smaller = __ballot(head >= 0 && key < me);
+    const bool owner = inside && ((smaller >> (8 * o)) & 0xffu) == 0;
+    if (owner && head >= 0) add_bin(head, n, bnext, BinPoint{sfrac, gpt, ncap, q}, f);
 #pragma unroll
-      for (int s = 0; s < kOrdered; ++s)
-        if (s < m) {
-          double w[3];
-          at(first[s], w);
-          for (int a = 0; a < 3; ++a) f[a] += w[a];
-        }
+    for (int a = 0; a < 3; ++a) {
+      double t = __shfl(f[a], 8 * o);
+#pragma unroll
+      for (int s = 1; s < 8; ++s) t += __shfl(f[a], 8 * o + s);
+      f[a] = t;
     }
-  }
+    if (q != 0) return;
+    if (!owner) {
+      *mine = -1;
+      return;
+    }
+  } else {
+    if (bins[me] != r || !bin_corner(me, o, sg, e, lat)) {
+      *mine = -1;
+      return;
+    }
+    int head[8];
+    bool owner = true;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    double t = __shfl(f[a], lane & 56);
-#pragma unroll
-    for (int s = 1; s < 8; ++s) t += __shfl(f[a], (lane & 56) + s);
-    f[a] = t;
+    for (int q = 0; q < 8; ++q) {
+      uint32_t key;
+      head[q] = bin_around(e, q, sg, key) ? bins[key] : -1;
+      owner = owner && !(head[q] >= 0 && key < me);
+    }
+    if (!owner) {
+      *mine = -1;
+      return;
+    }
+    for (int q = 0; q < 8; ++q)
+      if (head[q] >= 0) add_bin(head[q], n, bnext, BinPoint{sfrac, gpt, ncap, q}, f);
   }
-  if (q != 0) return;
   const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
-  if (owner) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
-  }
-  touched[8LL * r + o] = owner ? (int32_t)node : -1;
+  for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
+  *mine = (int32_t)node;
 }
 
 inline int nblocks(long long n, int b) { return (int)((n + b - 1) / b); }
@@ -843,17 +890,23 @@ hipError_t fil_copy_positions(Run& r, const double* src, double* dst) {
   return hipGetLastError();
 }
 
+namespace {
+
+template <class FT>
+void launch_gather(Run& r) {
+  auto kern = r.small ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;
+  hipLaunchKernelGGL(kern, dim3(nblocks((r.small ? 64 : 8) * r.ncap, 256)), dim3(256), 0, r.stream,
+                     r.skeys, r.bins, r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, spread_geom(r),
+                     r.cells, (FT*)r.force, r.touched);
+}
+
+}  // namespace
+
 hipError_t fil_spread(Run& r) {
-  const SpreadGeom sg = spread_geom(r);
-  const int nb4 = nblocks(r.ncap, 4);
   if (r.prec == VLB_F64)
-    hipLaunchKernelGGL(k_spread_gather<double>, dim3(nb4), dim3(256), 0, r.stream, r.skeys, r.bins,
-                       r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (double*)r.force,
-                       r.touched);
+    launch_gather<double>(r);
   else
-    hipLaunchKernelGGL(k_spread_gather<float>, dim3(nb4), dim3(256), 0, r.stream, r.skeys, r.bins,
-                       r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, sg, r.cells, (float*)r.force,
-                       r.touched);
+    launch_gather<float>(r);
   return hipGetLastError();
 }
 

@@ -107,12 +107,13 @@ __device__ inline int flag_rank(const uint64_t* __restrict__ mask, const int32_t
   return pre[w] + __popcll(mask[w] & lanes_below(x & 63));
 }
 
-// Exclusive scan of a[0..n) in place by one block of kBlock threads.
+// Exclusive scan of a[0..n) in place by one block of B threads.
+template <int B>
 __device__ void block_scan_inplace(int32_t* a, int n, int32_t* total) {
-  __shared__ int32_t wsum[kBlock / 64];
+  __shared__ int32_t wsum[B / 64];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   int carry = 0;
-  for (int base = 0; base < n; base += 4 * kBlock) {
+  for (int base = 0; base < n; base += 4 * B) {
     const int k0 = base + 4 * t;
     int v[4];
 #pragma unroll
@@ -126,7 +127,7 @@ __device__ void block_scan_inplace(int32_t* a, int n, int32_t* total) {
     if (lane == 63) wsum[w] = x;
     __syncthreads();
     int before = 0, all = 0;
-    for (int u = 0; u < kBlock / 64; ++u) {
+    for (int u = 0; u < B / 64; ++u) {
       before += u < w ? wsum[u] : 0;
       all += wsum[u];
     }
@@ -164,7 +165,7 @@ __device__ void wave_scan_commit(bool flag, uint64_t* __restrict__ mask, int32_t
   __syncthreads();
   if (!s_last) return;
   __threadfence();
-  block_scan_inplace(pre, gridDim.x * (kBlock / 64), total);
+  block_scan_inplace<kBlock>(pre, gridDim.x * (kBlock / 64), total);
   if (t == 0) *ticket = 0;
 }
 
@@ -188,13 +189,9 @@ __global__ void k_reset_stats(int32_t* cnt) {
 // points long unless the input is over-resolved, and each pass halves
 // them).  Block 0 also clears the step's statistics counters.
 
-__global__ __launch_bounds__(kBlock) void k_rm_mark(const double* __restrict__ pos,
-                                                    const int32_t* __restrict__ nxt,
-                                                    const int32_t* __restrict__ prv,
-                                                    int32_t* __restrict__ cnt, long long nc,
-                                                    TopoGeom tg, double mn2, double mx2,
-                                                    int32_t* __restrict__ del) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
+__device__ void rm_mark_point(int j, const double* __restrict__ pos, const int32_t* __restrict__ nxt, const int32_t* __restrict__ prv,
+                              const int32_t* __restrict__ cnt, long long nc, const TopoGeom& tg, double mn2,
+                              double mx2, int32_t* __restrict__ del) {
   // the point's links and the three positions of its candidacy test are
   // loaded before the point count arrives
   const int jc = clamp_index(j, nc);
@@ -204,7 +201,6 @@ __global__ __launch_bounds__(kBlock) void k_rm_mark(const double* __restrict__ p
   load3(pos, nc, p0, yp);
   load3(pos, nc, q0, yq);
   const int n = cnt[0];
-  if (blockIdx.x == 0 && threadIdx.x == 0) cnt[2] = cnt[3] = cnt[4] = cnt[5] = cnt[6] = 0;
   if (j >= n) return;
   int dd = 0;
   double d[3], c3[3];
@@ -257,21 +253,23 @@ __global__ __launch_bounds__(kBlock) void k_rm_mark(const double* __restrict__ p
   del[j] = dd;
 }
 
+__global__ __launch_bounds__(kBlock) void k_rm_mark(const double* __restrict__ pos,
+                                                    const int32_t* __restrict__ nxt,
+                                                    const int32_t* __restrict__ prv,
+                                                    int32_t* __restrict__ cnt, long long nc,
+                                                    TopoGeom tg, double mn2, double mx2,
+                                                    int32_t* __restrict__ del) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) cnt[2] = cnt[3] = cnt[4] = cnt[5] = cnt[6] = 0;
+  rm_mark_point(blockIdx.x * kBlock + threadIdx.x, pos, nxt, prv, cnt, nc, tg, mn2, mx2, del);
+}
+
 // Deleted points are unlinked; every kept point whose segment (to its
 // successor after the unlinking) is longer than dxi_max is flagged for a
 // midpoint, and the flags are ranked.  A kept point may read its successor
 // link before or after the deleted successor rewrote it: both lead to the
 // same new successor, since deleted points have kept neighbours.
-__global__ __launch_bounds__(kBlock) void k_rm_link(const double* __restrict__ pos,
-                                                    int32_t* __restrict__ nxt,
-                                                    int32_t* __restrict__ prv,
-                                                    int32_t* __restrict__ cnt, long long nc,
-                                                    TopoGeom tg, double mx2,
-                                                    const int32_t* __restrict__ del,
-                                                    uint64_t* __restrict__ imask,
-                                                    int32_t* __restrict__ ipre,
-                                                    int32_t* ticket) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
+__device__ bool rm_link_point(int j, const double* __restrict__ pos, int32_t* __restrict__ nxt, int32_t* __restrict__ prv, int32_t* __restrict__ cnt,
+                              long long nc, const TopoGeom& tg, double mx2, const int32_t* __restrict__ del) {
   // loads before the point count arrives.  A deleted point's own links are
   // not rewritten here (its neighbours are kept); a kept point's successor
   // link may be read before or after a deleted successor rewrote it, and
@@ -305,19 +303,27 @@ __global__ __launch_bounds__(kBlock) void k_rm_link(const double* __restrict__ p
   }
   const uint64_t dm = __ballot(dj != 0);
   if ((threadIdx.x & 63) == 0 && dm) atomicAdd(&cnt[3], (int)__popcll(dm));
+  return ins;
+}
+
+__global__ __launch_bounds__(kBlock) void k_rm_link(const double* __restrict__ pos,
+                                                    int32_t* __restrict__ nxt,
+                                                    int32_t* __restrict__ prv,
+                                                    int32_t* __restrict__ cnt, long long nc,
+                                                    TopoGeom tg, double mx2,
+                                                    const int32_t* __restrict__ del,
+                                                    uint64_t* __restrict__ imask,
+                                                    int32_t* __restrict__ ipre,
+                                                    int32_t* ticket) {
+  const bool ins = rm_link_point(blockIdx.x * kBlock + threadIdx.x, pos, nxt, prv, cnt, nc, tg, mx2, del);
   wave_scan_commit(ins, imask, ipre, ticket, cnt + 2);
 }
 
 // Midpoints of the flagged segments, appended at n + rank in ascending
 // segment order; all or none (capacity).
-__global__ __launch_bounds__(kBlock) void k_rm_insert(double* __restrict__ pos,
-                                                      int32_t* __restrict__ nxt,
-                                                      int32_t* __restrict__ prv,
-                                                      int32_t* __restrict__ cnt, long long nc,
-                                                      TopoGeom tg, int32_t* __restrict__ del,
-                                                      const uint64_t* __restrict__ imask,
-                                                      const int32_t* __restrict__ ipre) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
+__device__ void rm_insert_point(int j, double* __restrict__ pos, int32_t* __restrict__ nxt, int32_t* __restrict__ prv, int32_t* __restrict__ cnt,
+                                long long nc, const TopoGeom& tg, int32_t* __restrict__ del,
+                                const uint64_t* __restrict__ imask, const int32_t* __restrict__ ipre) {
   // loads before the point count arrives (only this thread rewrites the
   // successor link of point j here)
   const int jc = clamp_index(j, nc);
@@ -346,6 +352,16 @@ __global__ __launch_bounds__(kBlock) void k_rm_insert(double* __restrict__ pos,
   nxt[q] = k;
   prv[k] = q;
   del[q] = 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_rm_insert(double* __restrict__ pos,
+                                                      int32_t* __restrict__ nxt,
+                                                      int32_t* __restrict__ prv,
+                                                      int32_t* __restrict__ cnt, long long nc,
+                                                      TopoGeom tg, int32_t* __restrict__ del,
+                                                      const uint64_t* __restrict__ imask,
+                                                      const int32_t* __restrict__ ipre) {
+  rm_insert_point(blockIdx.x * kBlock + threadIdx.x, pos, nxt, prv, cnt, nc, tg, del, imask, ipre);
 }
 
 // ---- reconnection bins
@@ -394,8 +410,7 @@ struct SmallArgs {
   int32_t* ticket;
 };
 
-__global__ __launch_bounds__(kBlock) void k_small_pass(SmallArgs A) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
+__device__ bool small_pass_point(int j, const SmallArgs& A) {
   const long long nc = A.nc;
   // the flags and the first links are loaded before the bound arrives
   const int jc = clamp_index(j, nc);
@@ -451,6 +466,11 @@ __global__ __launch_bounds__(kBlock) void k_small_pass(SmallArgs A) {
     A.rc_next[j] = atomicExch(&A.rc_head[key], j);
   }
   if (A.rc_mode == 2 && in) A.rc_head[key0] = -1;
+  return alive;
+}
+
+__global__ __launch_bounds__(kBlock) void k_small_pass(SmallArgs A) {
+  const bool alive = small_pass_point(blockIdx.x * kBlock + threadIdx.x, A);
   if (A.mask) wave_scan_commit(alive, A.mask, A.pre, A.ticket, A.cnt + 8);
 }
 
@@ -465,19 +485,10 @@ __device__ inline uint32_t grid_coord(double y, const BsAxes& ax, int a) {
   return ax.periodic[a] ? (uint32_t)(long long)g : (uint32_t)(int)(long long)g;
 }
 
-__global__ __launch_bounds__(kBlock) void k_compact_scatter(const double* __restrict__ pos,
-                                                            const int32_t* __restrict__ nxt,
-                                                            const int32_t* __restrict__ prv,
-                                                            int32_t* __restrict__ cnt,
-                                                            long long nc,
-                                                            const uint64_t* __restrict__ mask,
-                                                            const int32_t* __restrict__ pre,
-                                                            double* __restrict__ pos_t,
-                                                            int32_t* __restrict__ nxt_t,
-                                                            int32_t* __restrict__ prv_t,
-                                                            int set_count,
-                                                            uint32_t* __restrict__ X, BsAxes ax) {
-  const int j = blockIdx.x * kBlock + threadIdx.x;
+__device__ void compact_point(int j, const double* __restrict__ pos, const int32_t* __restrict__ nxt, const int32_t* __restrict__ prv,
+                              int32_t* __restrict__ cnt, long long nc, const uint64_t* __restrict__ mask, const int32_t* __restrict__ pre,
+                              double* __restrict__ pos_t, int32_t* __restrict__ nxt_t, int32_t* __restrict__ prv_t, int set_count,
+                              uint32_t* __restrict__ X, const BsAxes& ax) {
   // loads before the bound arrives
   const int jc = clamp_index(j, nc);
   const uint64_t mw = mask[jc >> 6];
@@ -495,6 +506,22 @@ __global__ __launch_bounds__(kBlock) void k_compact_scatter(const double* __rest
   }
   nxt_t[q] = flag_rank(mask, pre, nj);
   prv_t[q] = flag_rank(mask, pre, pj);
+}
+
+__global__ __launch_bounds__(kBlock) void k_compact_scatter(const double* __restrict__ pos,
+                                                            const int32_t* __restrict__ nxt,
+                                                            const int32_t* __restrict__ prv,
+                                                            int32_t* __restrict__ cnt,
+                                                            long long nc,
+                                                            const uint64_t* __restrict__ mask,
+                                                            const int32_t* __restrict__ pre,
+                                                            double* __restrict__ pos_t,
+                                                            int32_t* __restrict__ nxt_t,
+                                                            int32_t* __restrict__ prv_t,
+                                                            int set_count,
+                                                            uint32_t* __restrict__ X, BsAxes ax) {
+  compact_point(blockIdx.x * kBlock + threadIdx.x, pos, nxt, prv, cnt, nc, mask, pre, pos_t, nxt_t,
+                prv_t, set_count, X, ax);
 }
 
 // The copy also writes the 32-bit grid coordinates of the new positions
@@ -629,19 +656,30 @@ __global__ __launch_bounds__(kBlock) void k_rc_find(const double* __restrict__ p
 // written with device-scope atomics.
 constexpr int kMatchPer = 16;  // points per thread in the slot gather of k_rc_match
 
-__global__ __launch_bounds__(1024) void k_rc_match(int32_t* __restrict__ nxt,
-                                                   int32_t* __restrict__ prv,
-                                                   int32_t* __restrict__ cnt, long long rcap,
-                                                   const int32_t* __restrict__ count,
-                                                   const int32_t* __restrict__ slot_j,
-                                                   const uint64_t* __restrict__ slot_k,
-                                                   int32_t* __restrict__ ci,
-                                                   int32_t* __restrict__ cj,
-                                                   uint64_t* __restrict__ ckey,
-                                                   int32_t* __restrict__ live,
-                                                   uint64_t* __restrict__ bkey,
-                                                   int32_t* __restrict__ bidx,
-                                                   int32_t* __restrict__ used) {
+struct MatchArgs {
+  int32_t* nxt;
+  int32_t* prv;
+  int32_t* cnt;
+  long long rcap;
+  const int32_t* count;
+  const int32_t* slot_j;
+  const uint64_t* slot_k;
+  int32_t* ci;
+  int32_t* cj;
+  uint64_t* ckey;
+  int32_t* live;
+  uint64_t* bkey;
+  int32_t* bidx;
+  int32_t* used;
+};
+
+__device__ void rc_match(const MatchArgs& A) {
+  int32_t *nxt = A.nxt, *prv = A.prv, *cnt = A.cnt, *ci = A.ci, *cj = A.cj, *live = A.live,
+          *bidx = A.bidx, *used = A.used;
+  const int32_t *count = A.count, *slot_j = A.slot_j;
+  const uint64_t* slot_k = A.slot_k;
+  uint64_t *ckey = A.ckey, *bkey = A.bkey;
+  const long long rcap = A.rcap;
   __shared__ int32_t wsum[16];
   __shared__ int s_live;
   __shared__ int s_taken;
@@ -778,6 +816,86 @@ __global__ __launch_bounds__(1024) void k_rc_match(int32_t* __restrict__ nxt,
   }
 }
 
+__global__ __launch_bounds__(1024) void k_rc_match(MatchArgs A) { rc_match(A); }
+
+// ---- the same phases for few points (kTopoPoints) by one workgroup: its
+// barriers stand in for the kernels' ends, and the flags are ranked by the
+// block itself.  Rounds of kTopoThreads points per phase.
+constexpr int kTopoThreads = 1024;
+
+struct TopoArgs {
+  TopoGeom tg;
+  double mn2, mx2;
+  double* pos;
+  int32_t* nxt;
+  int32_t* prv;
+  int32_t* cnt;
+  long long nc;
+  int32_t* del;
+  int remesh, match, finish;  // phases of this launch
+  uint64_t* mask;
+  int32_t* pre;
+  SmallArgs small;   // the small-loop pass of this launch
+  MatchArgs m;
+  double* pos_t;
+  int32_t* nxt_t;
+  int32_t* prv_t;
+  uint32_t* X;
+  BsAxes ax;
+};
+
+// Ballots of a round's flags (point j of every thread, n points) for the
+// ranks.
+__device__ inline void block_flags(int j, int n, bool flag, uint64_t* mask, int32_t* pre) {
+  const uint64_t m = __ballot(flag);
+  if ((threadIdx.x & 63) == 0 && j < n) {
+    mask[j >> 6] = m;
+    pre[j >> 6] = __popcll(m);
+  }
+}
+
+__global__ __launch_bounds__(kTopoThreads) void k_topo_block(TopoArgs A) {
+  const int t = threadIdx.x;
+  int32_t* cnt = A.cnt;
+  const int n = cnt[0];
+  if (!A.match && t == 0) cnt[2] = cnt[3] = cnt[4] = cnt[5] = cnt[6] = 0;
+  __syncthreads();
+  if (A.remesh) {
+    for (int b = 0; b < n; b += kTopoThreads)
+      rm_mark_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.mn2, A.mx2, A.del);
+    __syncthreads();
+    for (int b = 0; b < n; b += kTopoThreads) {
+      const bool ins = rm_link_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.mx2, A.del);
+      block_flags(b + t, n, ins, A.mask, A.pre);
+    }
+    __syncthreads();
+    block_scan_inplace<kTopoThreads>(A.pre, (n + 63) / 64, cnt + 2);
+    __syncthreads();
+    if (n == 0 && t == 0) cnt[9] = 0;
+    for (int b = 0; b < n; b += kTopoThreads)
+      rm_insert_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.del, A.mask, A.pre);
+    __syncthreads();
+  }
+  if (A.match) {
+    rc_match(A.m);
+    __syncthreads();
+  }
+  const int bound = A.small.bound9 ? cnt[9] : n;
+  if (!A.small.bound9 && bound == 0 && t == 0) cnt[9] = 0;
+  for (int b = 0; b < bound; b += kTopoThreads) {
+    const bool alive = small_pass_point(b + t, A.small);
+    if (A.finish) block_flags(b + t, bound, alive, A.mask, A.pre);
+  }
+  if (!A.finish) return;
+  __syncthreads();
+  block_scan_inplace<kTopoThreads>(A.pre, (bound + 63) / 64, cnt + 8);
+  __syncthreads();
+  if (bound == 0 && t == 0) cnt[0] = cnt[8];
+  for (int b = 0; b < bound; b += kTopoThreads)
+    compact_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.mask, A.pre, A.pos_t, A.nxt_t, A.prv_t,
+                  1, A.X, A.ax);
+}
+
 inline int nb_of(long long n, int b) { return (int)((n + b - 1) / b); }
 
 TopoGeom topo_geom(const Run& r) {
@@ -815,9 +933,13 @@ hipError_t topo_update(Run& r, bool swap) {
   const int nb = nb_of(r.ncap, kBlock);
   int32_t* del = r.flag_b;
   int32_t* ticket = r.cnt + 12;
-  if (r.vor.remesh) {
-    const double mn2 = r.vor.dxi_min * r.vor.dxi_min;
-    const double mx2 = r.vor.dxi_max * r.vor.dxi_max;
+  const double mn2 = r.vor.dxi_min * r.vor.dxi_min;
+  const double mx2 = r.vor.dxi_max * r.vor.dxi_max;
+  // few points (a step's update, which swaps the point arrays): one workgroup
+  const bool block = swap && r.ncap <= kTopoPoints;
+  if (block) {
+    // the phases follow below, with the small-loop pass they end in
+  } else if (r.vor.remesh) {
     hipLaunchKernelGGL(k_rm_mark, dim3(nb), dim3(kBlock), 0, r.stream, r.pos, r.nxt, r.prv, r.cnt,
                        r.ncap, tg, mn2, mx2, del);
     hipLaunchKernelGGL(k_rm_link, dim3(nb), dim3(kBlock), 0, r.stream, r.pos, r.nxt, r.prv, r.cnt,
@@ -837,6 +959,25 @@ hipError_t topo_update(Run& r, bool swap) {
   A.dead_in = r.vor.remesh ? del : nullptr;
   A.min_pts = r.vor.min_loop_pts;
   A.ticket = ticket;
+  uint32_t* X = r.prec == VLB_F64 ? nullptr : r.bsX;
+  TopoArgs T{};
+  T.tg = tg;
+  T.mn2 = mn2;
+  T.mx2 = mx2;
+  T.pos = r.pos;
+  T.nxt = r.nxt;
+  T.prv = r.prv;
+  T.cnt = r.cnt;
+  T.nc = r.ncap;
+  T.del = del;
+  T.remesh = r.vor.remesh;
+  T.mask = r.wmask;
+  T.pre = r.wpre;
+  T.pos_t = r.pos_t;
+  T.nxt_t = r.nxt_t;
+  T.prv_t = r.prv_t;
+  T.X = X;
+  T.ax = r.bsax;
   if (r.vor.reconnect) {
     const BinGeom bg = bin_geom(r);
     A.bg = bg;
@@ -846,14 +987,18 @@ hipError_t topo_update(Run& r, bool swap) {
     A.rc_count = r.scan_a;
     A.alive_out = r.flag_a;
     A.rc_mode = 1;
-    hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, A);
+    T.small = A;
+    if (block)
+      hipLaunchKernelGGL(k_topo_block, dim3(1), dim3(kTopoThreads), 0, r.stream, T);
+    else
+      hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, A);
     const double d2max = r.vor.reconnect_dist * r.vor.reconnect_dist;
     hipLaunchKernelGGL(k_rc_find, dim3(nb_of(27 * r.ncap, kBlock)), dim3(kBlock), 0, r.stream, r.pos, r.nxt, r.prv,
                        r.rc_head, r.rc_next, r.flag_a, r.cnt, r.ncap, tg, bg, d2max, r.scan_a,
                        r.rc_slot_j, r.rc_slot_k, r.used);
-    hipLaunchKernelGGL(k_rc_match, dim3(1), dim3(1024), 0, r.stream, r.nxt, r.prv, r.cnt, r.rcap,
-                       r.scan_a, r.rc_slot_j, r.rc_slot_k, r.rc_i, r.rc_j, r.rc_key_a,
-                       r.rc_idx_a, r.rc_best, r.rc_bidx, r.used);
+    const MatchArgs m{r.nxt,    r.prv,  r.cnt,      r.rcap,     r.scan_a,  r.rc_slot_j, r.rc_slot_k,
+                      r.rc_i,   r.rc_j, r.rc_key_a, r.rc_idx_a, r.rc_best, r.rc_bidx,   r.used};
+    if (!block) hipLaunchKernelGGL(k_rc_match, dim3(1), dim3(1024), 0, r.stream, m);
     SmallArgs B = A;
     B.bound9 = 1;
     B.dead_in = nullptr;
@@ -862,16 +1007,25 @@ hipError_t topo_update(Run& r, bool swap) {
     B.rc_mode = 2;
     B.mask = r.wmask;
     B.pre = r.wpre;
-    hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, B);
+    T.remesh = 0;
+    T.match = 1;
+    T.m = m;
+    T.small = B;
+    if (!block) hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, B);
   } else {
     A.mask = r.wmask;
     A.pre = r.wpre;
-    hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, A);
+    T.small = A;
+    if (!block) hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, A);
   }
-  uint32_t* X = r.prec == VLB_F64 ? nullptr : r.bsX;
   if (swap) {
-    hipLaunchKernelGGL(k_compact_scatter, dim3(nb), dim3(kBlock), 0, r.stream, r.pos, r.nxt, r.prv,
-                       r.cnt, r.ncap, r.wmask, r.wpre, r.pos_t, r.nxt_t, r.prv_t, 1, X, r.bsax);
+    T.finish = 1;
+    if (block)
+      hipLaunchKernelGGL(k_topo_block, dim3(1), dim3(kTopoThreads), 0, r.stream, T);
+    else
+      hipLaunchKernelGGL(k_compact_scatter, dim3(nb), dim3(kBlock), 0, r.stream, r.pos, r.nxt,
+                         r.prv, r.cnt, r.ncap, r.wmask, r.wpre, r.pos_t, r.nxt_t, r.prv_t, 1, X,
+                         r.bsax);
     std::swap(r.pos, r.pos_t);
     std::swap(r.nxt, r.nxt_t);
     std::swap(r.prv, r.prv_t);

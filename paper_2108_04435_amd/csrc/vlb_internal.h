@@ -559,6 +559,10 @@ struct Run {
 // launches.  Twenty graph steps of a ring of 64 points (capacity 345): 1791
 // -> 1622 us; 500 points (956) level; 1300 points (2076) 8% slower.
 constexpr long long kStagePoints = 1024;
+// Points (capacity) up to which a step's topology runs in one workgroup: a
+// ring of 64 points 1442 -> 1360 us per twenty steps, 500 points 1262 ->
+// 1225 per ten; 2700 points (capacity 4036) 1837 -> 1955.
+constexpr long long kTopoPoints = 1024;
 // Lattice work per step (seconds at 5 TB/s) below which such a run keeps to
 // one stream: a dependency across streams costs 5 to 9 us, twice a step.
 constexpr double kShortLattice = 2e-5;

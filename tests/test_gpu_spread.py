@@ -35,8 +35,9 @@ def _crowded(per_cell):
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
 @pytest.mark.parametrize("walls", [(False, False, False), (True, False, True)])
-@pytest.mark.parametrize("per_cell", [2, 8, 9, 40, 300])
-def test_crowded_cells(per_cell, walls, precision):
+@pytest.mark.parametrize("per_cell", [2, 8, 9, 40, 220])
+@pytest.mark.parametrize("cap", [1000, 1400])   # a wave per point, a thread per node
+def test_crowded_cells(per_cell, walls, precision, cap):
     dims = (30, 26, 28)
     lat = Lattice(*dims, walls=walls)
     pos, nxt = _crowded(per_cell)
@@ -44,7 +45,7 @@ def test_crowded_cells(per_cell, walls, precision):
     n = pos.shape[0]
     say("spread", per_cell, walls, precision, n, "points")
     run = vlb.Run(wl.lattice_preset(*dims, walls=walls, precision=precision),
-                  wl.vortex_preset(remesh=False), n_cap=n + 7)
+                  wl.vortex_preset(remesh=False), n_cap=cap)
     rho, u = wl.velocity_field(5, dims, (0.01, 0.0, 0.02), 1e-3)
     run.write_fields(rho, u)
     run.seed(pos, nxt)
