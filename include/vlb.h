@@ -435,8 +435,9 @@ int vlb_biot_savart_noalloc(const vlb_bs_desc* d, int64_t n_pts, const double* x
  *    (which keeps each target's own segments in cells it sums directly).
  *  - xyz_dev, next_dev, v_dev, dev_workspace, hip_stream: as
  *    vlb_biot_savart, the workspace sized by
- *    vlb_biot_savart_farfield_workspace (about 620 bytes per point, 700
- *    per cell and 12 per point per cell chunk, up to 64 chunks).
+ *    vlb_biot_savart_farfield_workspace (about 1040 bytes per point, 1570
+ *    with two levels, 760 per cell and 12 per point per cell chunk, up to
+ *    64 chunks).
  *  - VLB_EINVAL for a bad descriptor or parameters, n_pts outside
  *    [0, 2^26] or a NULL pointer (n_pts > 0); VLB_ENOSPACE for a small
  *    workspace; VLB_EDEVICE if a launch fails.                             */

@@ -33,16 +33,15 @@
 //    coarse cell's children are consecutive), one 32-byte record each for
 //    the direct loop;
 //  * one 256-byte record per cell (range, rad^2, centre, grid centre,
-//    delta extremes, 36 moments), read with scalar loads;
+//    delta extremes, 42 moments), read with scalar loads;
 //  * per axis: each cell's deltas in ascending order and the prefix sums of
-//    the 36 moment components over that order (cnt + 1 rows per cell);
-//  * the evaluation grid: blockIdx.x picks 64 targets (consecutive in the
-//    cell order, so a wave's targets are close), blockIdx.y one of S cell
-//    chunks; the 4 waves of a block take interleaved cells of the coarsest
-//    level (c = 4 y + w modulo 4 S) and add their sums in LDS in a fixed
-//    order; the chunk partials are added in FP64 in chunk order (bitwise
+//    the 42 moment components over that order (cnt + 1 rows per cell);
+//  * the evaluation grid: blockIdx.x picks 256 targets, 64 per wave
+//    (consecutive in the cell order, so a wave's targets are close),
+//    blockIdx.y one of S cell chunks (cells y modulo S of the coarsest level);
+//    the chunk partials are added in FP64 in chunk order (bitwise
 //    reproducible).
-#include "vlb_internal.h"
+#include "bs_pair.h"
 
 #include <cmath>
 
@@ -50,35 +49,43 @@ namespace vlb {
 
 namespace {
 
-constexpr int kMom = 36;       // moment components per cell or class
-constexpr int kFfTargets = 64;
+constexpr int kMom = 42;       // moment components per cell or class
+constexpr int kFfTargets = 256;  // targets per block, 64 per wave
 
-// Moment components (no kappa: the caller scales the sum): 0..2 M0_n = d_n;
-// 3..5 A = d x y (the antisymmetric part of M1, eps_mnp M1_np); 6..14
-// M1_np = d_n y_p; 15..32 M2_njk = d_n (y_j y_k + d_j d_k / 12) for
-// jk = 00 01 02 11 12 22; 33..35 tr_n = d_n (|y|^2 + |d|^2 / 12).
+// Moment components (no kappa: the caller scales the sum), each linear in
+// the segments and combined so that the expansion takes them as they are.
+// With A = d x y and Q_n,jk = d_n (y_j y_k + d_j d_k / 12), tr_n its trace:
+//   0..2    M0_n = d_n;
+//   3..5    -A_m (the antisymmetric part of the dipole);
+//   6..14   3 d_n y_p (the dipole);
+//   15..32  7.5 (Q_n,jk - delta_jk tr_n / 5) for jk = 00 01 02 11 12 22, the
+//           off-diagonal ones doubled (both orders of a symmetric pair);
+//   33..41  -3 A_m y_k (what the curl of the quadrupole leaves beside Q).
 __device__ inline double comp_value(int comp, const double* y, const double* d) {
 #pragma clang fp contract(off)
   if (comp < 3) return d[comp];
-  if (comp < 6) {
-    const int m = comp - 3;
+  const auto cross = [&](int m) {
     const int a = (m + 1) % 3, b = (m + 2) % 3;
     return d[a] * y[b] - d[b] * y[a];
-  }
+  };
+  if (comp < 6) return -cross(comp - 3);
   if (comp < 15) {
     const int i = comp - 6;
-    return d[i / 3] * y[i % 3];
+    return 3.0 * (d[i / 3] * y[i % 3]);
   }
   if (comp < 33) {
     const int i = comp - 15;
     const int nn = i / 6, jk = i % 6;
     const int j = jk < 3 ? 0 : (jk < 5 ? 1 : 2);
     const int k = jk < 3 ? jk : (jk < 5 ? jk - 2 : 2);
-    return d[nn] * (y[j] * y[k] + d[j] * d[k] / 12.0);
+    const double q = y[j] * y[k] + d[j] * d[k] / 12.0;
+    if (j != k) return 15.0 * (d[nn] * q);
+    const double tr = (y[0] * y[0] + y[1] * y[1] + y[2] * y[2]) +
+                      (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) / 12.0;
+    return 7.5 * (d[nn] * (q - tr / 5.0));
   }
-  const int nn = comp - 33;
-  return d[nn] * ((y[0] * y[0] + y[1] * y[1] + y[2] * y[2]) +
-                  (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) / 12.0);
+  const int i = comp - 33;
+  return -3.0 * (cross(i / 3) * y[i % 3]);
 }
 
 struct FfAxes {
@@ -129,8 +136,8 @@ struct __align__(256) FfCell {
 
 struct __align__(32) FfSeg {
   uint32_t x[3];  // start on the grid
-  float d[3];     // segment vector: wrapped grid difference (uniform) or lattice units
-  float dq;       // |d|^2
+  float d[3];     // twice the segment vector: wrapped grid difference (uniform) or lattice units
+  float dq;       // |d|^2 of the vector itself
   int32_t idx;    // segment (point) index
 };
 
@@ -261,7 +268,6 @@ __global__ void k_ff_seg(const int32_t* __restrict__ so, const uint32_t* __restr
   const int k = so[p];
   const int kn = nxt[k];
   FfSeg r;
-  float dq = 0.f;
   for (int a = 0; a < 3; ++a) {
     const uint32_t x0 = X[(long long)a * nc + k];
     float e = (float)(int)(X[(long long)a * nc + kn] - x0);
@@ -269,8 +275,8 @@ __global__ void k_ff_seg(const int32_t* __restrict__ so, const uint32_t* __restr
     r.x[a] = x0;
     r.d[a] = e;
   }
-  dq = r.d[0] * r.d[0] + r.d[1] * r.d[1] + r.d[2] * r.d[2];
-  r.dq = dq;
+  r.dq = r.d[0] * r.d[0] + r.d[1] * r.d[1] + r.d[2] * r.d[2];
+  for (int a = 0; a < 3; ++a) r.d[a] *= 2.0f;
   r.idx = k;
   recs[p] = r;
 }
@@ -281,7 +287,7 @@ __device__ inline double ff_lane_d(double x, int k) {
   return __hiloint2double(hi, lo);
 }
 
-// Per segment, at one level: the 36 moment components about its cell's
+// Per segment, at one level: the 42 moment components about its cell's
 // centre (FP64, row k of comps) and |y| + |d| / 2 (srad).
 __global__ void k_ff_comps(const double* __restrict__ M, const double* __restrict__ D,
                            const int32_t* __restrict__ kidx, const int32_t* __restrict__ cntp,
@@ -305,29 +311,35 @@ __global__ void k_ff_comps(const double* __restrict__ M, const double* __restric
   srad[k] = ny + 0.5 * nd;
 }
 
-// One wave (a block of 64) per (cell of a level, axis): the cell's start
+// One block of kOrder threads per (cell of a level, axis): the cell's start
 // offsets on the axis in ascending order (ties by sorted position) with
-// their segment indices (sdel, sidx), the prefix sums of the 36 moment
+// their segment indices (sdel, sidx), the prefix sums of the 42 moment
 // components over that order (FP64 sums stored FP32, rows
 // a (nc + C) + start + c + i for i = 0 .. count, row 0 zero; nc the
 // capacity of the point arrays), and the
 // record's fields for the axis (centre, grid centre, offset extremes); the
-// axis-0 wave also writes the radius and the moments (its prefix totals).
-// The ranks compare offsets held in registers (64 at a time, broadcast
-// with readlane); the prefix sums add the components of k_ff_comps, one
-// lane per component.
-__global__ __launch_bounds__(64) void k_ff_order(const int32_t* __restrict__ so,
-                                                 const double* __restrict__ comps,
-                                                 const double* __restrict__ srad,
-                                                 const uint32_t* __restrict__ X, long long nc,
-                                                 FfAxes ax,
-                                                 int level, FfCell* __restrict__ cells,
-                                                 int32_t* __restrict__ sdel,
-                                                 int32_t* __restrict__ sidx,
-                                                 float* __restrict__ pre) {
+// axis-0 block also writes the radius and the moments (its prefix totals).
+// The ranks compare offsets staged in LDS; the prefix sums add the components
+// of k_ff_comps, one lane per component, each wave over its share of the
+// order: the shares' sums first, then the rows from the sum of the shares
+// before.  What bounds it is the latency of the dependent loads and of the
+// sums' chain: one wave per cell took 240 us for 512 cells of 195 points,
+// four waves take 84 us.
+template <int kOrder>
+__global__ __launch_bounds__(kOrder) void k_ff_order(const int32_t* __restrict__ so,
+                                                     const double* __restrict__ comps,
+                                                     const double* __restrict__ srad,
+                                                     const uint32_t* __restrict__ X, long long nc,
+                                                     FfAxes ax, int level,
+                                                     FfCell* __restrict__ cells,
+                                                     int32_t* __restrict__ sdel,
+                                                     int32_t* __restrict__ sidx,
+                                                     float* __restrict__ pre) {
 #pragma clang fp contract(off)
+  constexpr int kWaves = kOrder / 64;
   const int c = blockIdx.x / 3, a = blockIdx.x - 3 * (blockIdx.x / 3);
-  const int lane = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int C = ax.C[level];
   const int s = cells[c].start, cnt = cells[c].count;
   int ci[3];
@@ -338,23 +350,31 @@ __global__ __launch_bounds__(64) void k_ff_order(const int32_t* __restrict__ so,
   const uint32_t* Xa = X + (long long)a * nc;
   int32_t* sd = sdel + (long long)a * nc + s;
   int32_t* si = sidx + (long long)a * nc + s;
+  __shared__ int32_t off[kOrder];
+  __shared__ double part[kWaves][kMom];
+  __shared__ int32_t lo[kWaves], hi[kWaves];
+  __shared__ double far[kWaves];
   int dmn = 0x7fffffff, dmx = -0x7fffffff - 1;
-  for (int b0 = 0; b0 < cnt; b0 += 64) {
-    const int i = b0 + lane;
+  double rad = 0.0;
+  for (int b0 = 0; b0 < cnt; b0 += kOrder) {
+    const int i = b0 + t;
     const bool vi = i < cnt;
     const int ki = vi ? so[s + i] : 0;
     const int di = vi ? (int)(Xa[ki] - xc) : 0;
     if (vi) {
       dmn = min(dmn, di);
       dmx = max(dmx, di);
+      if (a == 0) rad = fmax(rad, srad[ki]);
     }
     int rank = 0;
-    for (int j0 = 0; j0 < cnt; j0 += 64) {
-      const int jj = j0 + lane;
-      const int dj = jj < cnt ? (int)(Xa[so[s + jj]] - xc) : 0;
-      const int m = min(64, cnt - j0);
+    for (int j0 = 0; j0 < cnt; j0 += kOrder) {
+      __syncthreads();  // the offsets of the previous round have been read
+      off[t] = j0 == b0 ? di : (j0 + t < cnt ? (int)(Xa[so[s + j0 + t]] - xc) : 0);
+      __syncthreads();
+      const int m = min(kOrder, cnt - j0);
+#pragma unroll 4
       for (int k = 0; k < m; ++k) {
-        const int dk = __builtin_amdgcn_readlane(dj, k);
+        const int dk = off[k];
         rank += (dk < di || (dk == di && j0 + k < i)) ? 1 : 0;
       }
     }
@@ -363,25 +383,47 @@ __global__ __launch_bounds__(64) void k_ff_order(const int32_t* __restrict__ so,
       si[rank] = ki;
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    dmn = min(dmn, __shfl_xor(dmn, off));
-    dmx = max(dmx, __shfl_xor(dmx, off));
+  for (int o = 32; o > 0; o >>= 1) {
+    dmn = min(dmn, __shfl_xor(dmn, o));
+    dmx = max(dmx, __shfl_xor(dmx, o));
+    rad = fmax(rad, __shfl_xor(rad, o));
+  }
+  if (lane == 0) {
+    lo[w] = dmn;
+    hi[w] = dmx;
+    far[w] = rad;
   }
   __syncthreads();  // the sorted order, written above, is read below
   float* row = pre + ((long long)a * (nc + C) + s + c) * kMom;
-  double acc = 0.0, rad = 0.0;
-  for (int i = lane; i < cnt; i += 64) rad = fmax(rad, srad[so[s + i]]);
-  if (lane < kMom) {
-    row[lane] = 0.f;
+  const int per = (cnt + kWaves - 1) / kWaves;
+  const int i0 = min(w * per, cnt), i1 = min(i0 + per, cnt);
+  double acc = 0.0;
+  if (kWaves > 1) {
+    if (lane < kMom && w + 1 < kWaves) {
 #pragma unroll 8
-    for (int i = 0; i < cnt; ++i) {
+      for (int i = i0; i < i1; ++i) acc = acc + comps[(long long)si[i] * kMom + lane];
+      part[w][lane] = acc;
+    }
+    __syncthreads();
+    acc = 0.0;
+    if (lane < kMom)
+      for (int u = 0; u < w; ++u) acc = acc + part[u][lane];
+  }
+  if (lane < kMom) {
+    if (w == 0) row[lane] = 0.f;
+#pragma unroll 8
+    for (int i = i0; i < i1; ++i) {
       acc = acc + comps[(long long)si[i] * kMom + lane];
       row[(long long)(i + 1) * kMom + lane] = (float)acc;
     }
   }
-  for (int off = 32; off > 0; off >>= 1) rad = fmax(rad, __shfl_xor(rad, off));
   FfCell& o = cells[c];
-  if (lane == 0) {
+  if (t == 0) {
+    for (int u = 1; u < kWaves; ++u) {
+      dmn = min(dmn, lo[u]);
+      dmx = max(dmx, hi[u]);
+      rad = fmax(rad, far[u]);
+    }
     o.c[a] = cen[a];
     o.xc[a] = xc;
     o.dmin[a] = cnt > 0 ? dmn : 0;
@@ -391,7 +433,7 @@ __global__ __launch_bounds__(64) void k_ff_order(const int32_t* __restrict__ so,
       o.pad = 0;
     }
   }
-  if (a == 0 && lane < kMom) o.m[lane] = (float)acc;
+  if (a == 0 && w == kWaves - 1 && lane < kMom) o.m[lane] = (float)acc;
 }
 
 // Moments: one array, or the difference of two (the upper class of a split
@@ -406,93 +448,43 @@ struct MomD {
   __device__ float operator()(int i) const { return t[i] - p[i]; }
 };
 
+// The expansion of a cell (or class) of moments m at separation R (target
+// less centre): 69 ordinary instructions.
 template <class M>
-__device__ inline void m2p_f32(float Rx, float Ry, float Rz, const M& m, float& vx, float& vy,
-                               float& vz) {
+__device__ __forceinline__ void m2p_f32(float Rx, float Ry, float Rz, const M& m, float& vx,
+                                        float& vy, float& vz) {
   const float r2 = fmaf(Rx, Rx, fmaf(Ry, Ry, Rz * Rz));
   const float ir = __builtin_amdgcn_rsqf(r2);
   const float i2 = ir * ir;
   const float r3 = ir * i2;
   const float r5 = r3 * i2;
-  const float r7h = 7.5f * (r5 * i2);
-  float S[3][3], W[3];
+  const float xx = Rx * Rx, xy = Rx * Ry, xz = Rx * Rz, yy = Ry * Ry, yz = Ry * Rz, zz = Rz * Rz;
+  float W[3], B[3];  // both to be scaled by r5
 #pragma unroll
-  for (int nn = 0; nn < 3; ++nn) {
-    const int q = 15 + 6 * nn;
-    const float q0 = m(q), q1 = m(q + 1), q2 = m(q + 2), q3 = m(q + 3), q4 = m(q + 4),
-                q5 = m(q + 5);
-    S[nn][0] = fmaf(q0, Rx, fmaf(q1, Ry, q2 * Rz));
-    S[nn][1] = fmaf(q1, Rx, fmaf(q3, Ry, q4 * Rz));
-    S[nn][2] = fmaf(q2, Rx, fmaf(q4, Ry, q5 * Rz));
-    const float Q = fmaf(Rx, S[nn][0], fmaf(Ry, S[nn][1], Rz * S[nn][2]));
-    const float a = fmaf(m(6 + 3 * nn), Rx, fmaf(m(7 + 3 * nn), Ry, m(8 + 3 * nn) * Rz));
-    W[nn] = fmaf(r5, fmaf(3.0f, a, -1.5f * m(33 + nn)), r7h * Q);
+  for (int n = 0; n < 3; ++n) {
+    const int q = 15 + 6 * n;
+    const float Q = fmaf(m(q), xx, fmaf(m(q + 1), xy, fmaf(m(q + 2), xz, fmaf(m(q + 3), yy,
+                    fmaf(m(q + 4), yz, m(q + 5) * zz)))));
+    const float a = fmaf(m(6 + 3 * n), Rx, fmaf(m(7 + 3 * n), Ry, m(8 + 3 * n) * Rz));
+    W[n] = fmaf(i2, Q, a);
+    B[n] = fmaf(m(33 + 3 * n), Rx, fmaf(m(34 + 3 * n), Ry, m(35 + 3 * n) * Rz));
   }
-  const float B0 = S[1][2] - S[2][1];
-  const float B1 = S[2][0] - S[0][2];
-  const float B2 = S[0][1] - S[1][0];
-  const float m0 = m(0), m1 = m(1), m2 = m(2);
-  const float V0 = fmaf(m1, Rz, -fmaf(m2, Ry, m(3)));
-  const float V1 = fmaf(m2, Rx, -fmaf(m0, Rz, m(4)));
-  const float V2 = fmaf(m0, Ry, -fmaf(m1, Rx, m(5)));
-  const float t5 = 3.0f * r5;
-  vx = fmaf(r3, V0, vx + fmaf(W[1], Rz, -fmaf(W[2], Ry, t5 * B0)));
-  vy = fmaf(r3, V1, vy + fmaf(W[2], Rx, -fmaf(W[0], Rz, t5 * B1)));
-  vz = fmaf(r3, V2, vz + fmaf(W[0], Ry, -fmaf(W[1], Rx, t5 * B2)));
+  const float V0 = fmaf(m(1), Rz, fmaf(-m(2), Ry, m(3)));
+  const float V1 = fmaf(m(2), Rx, fmaf(-m(0), Rz, m(4)));
+  const float V2 = fmaf(m(0), Ry, fmaf(-m(1), Rx, m(5)));
+  vx = fmaf(r3, V0, fmaf(r5, fmaf(W[1], Rz, fmaf(-W[2], Ry, B[0])), vx));
+  vy = fmaf(r3, V1, fmaf(r5, fmaf(W[2], Rx, fmaf(-W[0], Rz, B[1])), vy));
+  vz = fmaf(r3, V2, fmaf(r5, fmaf(W[0], Ry, fmaf(-W[1], Rx, B[2])), vz));
 }
 
-// One (target, segment) pair of the exact straight-segment integral, as in
-// the direct FP32 sum: R1 = s - r from the wrapped grid difference, R2 =
-// R1 + d, v += (R1 x d) (i1 + i2) i1 i2 / (1 + (R1.R2) i1 i2).
+// One (target, segment) pair of the exact straight-segment integral, in the
+// direct FP32 sum's form (bs_pair_f32): d is staged doubled.
 template <bool kUniform>
-__device__ inline void ff_pair(const FfSeg& g, uint32_t xt, uint32_t yt, uint32_t zt,
-                               const FfAxes& ax, float& vx, float& vy, float& vz, bool zero) {
-  float r1x = (float)(int)(g.x[0] - xt);
-  float r1y = (float)(int)(g.x[1] - yt);
-  float r1z = (float)(int)(g.x[2] - zt);
-  if (!kUniform) {
-    r1x *= ax.iqf[0];
-    r1y *= ax.iqf[1];
-    r1z *= ax.iqf[2];
-  }
-  const float ex = g.d[0], ey = g.d[1], ez = g.d[2];
-  const float t = fmaf(r1x, ex, fmaf(r1y, ey, r1z * ez));
-  const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
-  const float n2 = fmaf(2.0f, t, n1 + g.dq);
-  const float i1 = __builtin_amdgcn_rsqf(n1);
-  const float i2 = __builtin_amdgcn_rsqf(n2);
-  const float crx = fmaf(r1y, ez, -r1z * ey);
-  const float cry = fmaf(r1z, ex, -r1x * ez);
-  const float crz = fmaf(r1x, ey, -r1y * ex);
-  const float a = i1 * i2;
-  const float den = fmaf(n1 + t, a, 1.0f);
-  float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(den);
-  f = zero ? 0.0f : f;
-  vx = fmaf(f, crx, vx);
-  vy = fmaf(f, cry, vy);
-  vz = fmaf(f, crz, vz);
-}
-
-// The decision fields of a cell record, loaded one cell ahead.
-struct FfHead {
-  int32_t start, count;
-  double rad2;
-  double c[3];
-  uint32_t xc[3];
-  int32_t dmin[3], dmax[3];
-};
-
-__device__ inline void ff_head(const FfCell* __restrict__ cm, FfHead& h) {
-  h.start = cm->start;
-  h.count = cm->count;
-  h.rad2 = cm->rad2;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    h.c[a] = cm->c[a];
-    h.xc[a] = cm->xc[a];
-    h.dmin[a] = cm->dmin[a];
-    h.dmax[a] = cm->dmax[a];
-  }
+__device__ __forceinline__ void ff_pair(const FfSeg& g, uint32_t xt, uint32_t yt, uint32_t zt,
+                                        const FfAxes& ax, float& vx, float& vy, float& vz,
+                                        bool zero) {
+  const BsSrc s{g.x[0], g.x[1], g.x[2], g.dq, g.d[0], g.d[1], g.d[2], 0};
+  bs_pair_f32<kUniform>(s, xt, yt, zt, ax.iqf[0], ax.iqf[1], ax.iqf[2], zero, vx, vy, vz);
 }
 
 // Per-lane decision for one cell (FP64 and integers, no contraction).
@@ -504,7 +496,7 @@ struct FfDecision {
   bool ok0;      // R0 passes the opening test
 };
 
-__device__ inline void ff_decide(const FfHead* cm, const double* r, const uint32_t* xt,
+__device__ inline void ff_decide(const FfCell* __restrict__ cm, const double* r, const uint32_t* xt,
                                  const FfAxes& ax, FfDecision& o) {
 #pragma clang fp contract(off)
   o.ncross = 0;
@@ -532,7 +524,7 @@ __device__ inline void ff_decide(const FfHead* cm, const double* r, const uint32
 // The class of the largest offset on the crossed axis: its wrapped offset
 // dropped by 2^32 at the crossing, so its K there is one less.  Returns
 // whether that image passes the opening test.
-__device__ inline bool ff_other(const FfHead* cm, const FfDecision& o, const double* r,
+__device__ inline bool ff_other(const FfCell* __restrict__ cm, const FfDecision& o, const double* r,
                                 const FfAxes& ax, double* R1) {
 #pragma clang fp contract(off)
 #pragma unroll
@@ -544,18 +536,18 @@ __device__ inline bool ff_other(const FfHead* cm, const FfDecision& o, const dou
 
 // Far and split contributions of one cell for the active lanes; returns
 // whether this lane opens the cell (active, neither far nor split).
-__device__ inline bool ff_cell_eval(const FfHead& hc, const FfCell* __restrict__ cm, int c,
+__device__ inline bool ff_cell_eval(const FfCell* __restrict__ cm, int c,
                                     const int32_t* __restrict__ sdel,
                                     const float* __restrict__ pre, long long nc, int C,
                                     bool active,
                                     const double* r, const uint32_t* xt, const FfAxes& ax,
                                     float& fx, float& fy, float& fz) {
   FfDecision dc;
-  ff_decide(&hc, r, xt, ax, dc);
+  ff_decide(cm, r, xt, ax, dc);
   const bool far = active && dc.ncross == 0 && dc.ok0;
   bool split = false;
   double R1[3] = {0.0, 0.0, 0.0};
-  if (active && dc.ncross == 1 && dc.ok0) split = ff_other(&hc, dc, r, ax, R1);
+  if (active && dc.ncross == 1 && dc.ok0) split = ff_other(cm, dc, r, ax, R1);
   if (__any(far)) {
     if (far)
       m2p_f32((float)-dc.R0[0], (float)-dc.R0[1], (float)-dc.R0[2], MomA{cm->m}, fx, fy, fz);
@@ -564,10 +556,10 @@ __device__ inline bool ff_cell_eval(const FfHead& hc, const FfCell* __restrict__
     if (split) {
       // offsets below the crossing: u + delta < 2^31
       const int a = dc.axis;
-      const uint32_t u = hc.xc[a] - xt[a];
+      const uint32_t u = cm->xc[a] - xt[a];
       const int db = (int)(0x80000000u - u);
-      const int32_t* dl = sdel + (long long)a * nc + hc.start;
-      int lo = 0, hi = hc.count;
+      const int32_t* dl = sdel + (long long)a * nc + cm->start;
+      int lo = 0, hi = cm->count;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
         if (dl[mid] < db)
@@ -575,7 +567,7 @@ __device__ inline bool ff_cell_eval(const FfHead& hc, const FfCell* __restrict__
         else
           hi = mid;
       }
-      const float* pr = pre + ((long long)a * (nc + C) + hc.start + c + lo) * kMom;
+      const float* pr = pre + ((long long)a * (nc + C) + cm->start + c + lo) * kMom;
       m2p_f32((float)-dc.R0[0], (float)-dc.R0[1], (float)-dc.R0[2], MomA{pr}, fx, fy, fz);
       m2p_f32((float)-R1[0], (float)-R1[1], (float)-R1[2], MomD{cm->m, pr}, fx, fy, fz);
     }
@@ -597,30 +589,144 @@ __device__ inline void ff_direct_loop(int s0, int e, const FfSeg* __restrict__ r
     const int m = min(64, e - c0);
     if (lane < m) lds[lane] = recs[c0 + lane];
     __builtin_amdgcn_wave_barrier();
-    for (int k = 0; k < m; ++k) {
-      const FfSeg g = lds[k];
-      if (near)
+    if (near) {
+#pragma unroll 2
+      for (int k = 0; k < m; ++k) {
+        const FfSeg g = lds[k];
         ff_pair<kUniform>(g, xt[0], xt[1], xt[2], ax, dx, dy, dz,
                           kCheck && (g.idx == jj || g.idx == pj));
+      }
     }
     __builtin_amdgcn_wave_barrier();
   }
 }
 
 template <bool kUniform>
-__device__ inline void ff_direct(const FfHead& hc, int c, const FfSeg* __restrict__ recs,
+__device__ inline void ff_direct(int s0, int count, int c, const FfSeg* __restrict__ recs,
                                  FfSeg* lds, bool near, int kj, int kp, int jj, int pj,
                                  const uint32_t* xt, const FfAxes& ax, float& dx, float& dy,
                                  float& dz) {
-  const int s0 = hc.start, e = hc.start + hc.count;
+  const int e = s0 + count;
   if (__any(kj == c || kp == c))
     ff_direct_loop<kUniform, true>(s0, e, recs, lds, near, jj, pj, xt, ax, dx, dy, dz);
   else
     ff_direct_loop<kUniform, false>(s0, e, recs, lds, near, jj, pj, xt, ax, dx, dy, dz);
 }
 
+// The wave's targets: grid coordinates of lane 0 and the extremes of the
+// targets' offsets from it; one: no target lies beyond the box boundary from
+// lane 0 on any axis, so that a cell's image is the same grid distance for
+// all of them.
+struct FfBox {
+  uint32_t x0[3];
+  int emin[3], emax[3];
+  bool one;
+};
+
+__device__ inline void ff_box(const uint32_t* xt, bool valid, FfBox& b) {
+  b.one = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    b.x0[a] = (uint32_t)__builtin_amdgcn_readfirstlane((int)xt[a]);
+    const int e = valid ? (int)(xt[a] - b.x0[a]) : 0;
+    int lo = e, hi = e;
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = min(lo, __shfl_xor(lo, off));
+      hi = max(hi, __shfl_xor(hi, off));
+    }
+    b.emin[a] = __builtin_amdgcn_readfirstlane(lo);
+    b.emax[a] = __builtin_amdgcn_readfirstlane(hi);
+    b.one = b.one && (long long)b.x0[a] + b.emin[a] >= 0 &&
+            (long long)b.x0[a] + b.emax[a] < (1LL << 32);
+  }
+}
+
+// What the per-lane decision (ff_decide) comes to for all of the wave's
+// targets at once, one cell per lane: far for all of them at the image K, or
+// opened by all, or one of the two at that image with no crossing (each lane
+// tests its distance), or mixed (each lane decides).  A target at offset e has
+// wmin = a - e and wmax = b - e where that neither wraps (no crossing), and
+// the image of the centre lies a - dmin - e grid steps away (one more at most
+// for the positions' parts below the grid); the bounds on its distance over
+// the box decide with a margin of 1e-9.
+enum FfClass { kEmpty = 0, kFar = 1, kRing = 2, kOpen = 3, kMixed = 4 };
+
+__device__ inline int ff_class(const FfCell* __restrict__ cm, const FfBox& b, const FfAxes& ax,
+                               int K[3]) {
+  K[0] = K[1] = K[2] = 0;
+  if (cm->count == 0) return kEmpty;
+  bool ok = b.one;
+  double near2 = 0.0, far2 = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int dmin = cm->dmin[a], dmax = cm->dmax[a];
+    const uint32_t xc = cm->xc[a];
+    const long long lo = (int)(xc - b.x0[a] + (uint32_t)dmin);
+    const long long hi = lo + ((long long)dmax - dmin);
+    ok = ok && lo - b.emax[a] >= -(1LL << 31) && hi - b.emin[a] < (1LL << 31);
+    const long long at = lo - dmin;
+    K[a] = (int)((at - ((long long)xc - (long long)b.x0[a])) >> 32);
+    const double iq = ax.L[a] / 4294967296.0;
+    const double rlo = (double)(at - b.emax[a] - 1) * iq, rhi = (double)(at - b.emin[a] + 1) * iq;
+    const double m = fmax(0.0, fmax(rlo, -rhi)), M = fmax(fabs(rlo), fabs(rhi));
+    near2 += m * m;
+    far2 += M * M;
+  }
+  const double rad2 = cm->rad2;
+  if (!ok) return kMixed;
+  if (near2 * ax.th2 > rad2 * (1.0 + 1e-9)) return kFar;
+  return far2 * ax.th2 < rad2 * (1.0 - 1e-9) ? kOpen : kRing;
+}
+
+// A cell at the image K for all lanes: the expansion for the active lanes it
+// is far for (kTest: those that pass the opening test of ff_decide; else all).
+// Returns whether this lane opens the cell.
+template <bool kTest>
+__device__ __forceinline__ bool ff_far(const FfCell* __restrict__ cm, const int K[3], bool active,
+                                       const double* r, const FfAxes& ax, float& fx, float& fy,
+                                       float& fz) {
+#pragma clang fp contract(off)
+  double R[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) R[a] = (cm->c[a] - r[a]) + (double)K[a] * ax.L[a];
+  bool far = active;
+  if (kTest) {
+    const double d2 = (R[0] * R[0] + R[1] * R[1]) + R[2] * R[2];
+    far = active && d2 * ax.th2 >= cm->rad2;
+  }
+  if (far) m2p_f32((float)-R[0], (float)-R[1], (float)-R[2], MomA{cm->m}, fx, fy, fz);
+  return active && !far;
+}
+
+// Cell c of a level, of class cls (ff_class; its K in lane i): the far and
+// split contributions for the active lanes; returns whether this lane opens
+// the cell.
+__device__ __forceinline__ bool ff_take(const FfCell* __restrict__ cells, int c, int cls,
+                                        const int K[3], int i, const int32_t* __restrict__ sdel,
+                                        const float* __restrict__ pre, long long nc, int C,
+                                        bool active, const double* r, const uint32_t* xt,
+                                        const FfAxes& ax, float& fx, float& fy, float& fz) {
+  const FfCell* __restrict__ cm = cells + c;
+  if (cls == kOpen) return active;
+  if (cls == kMixed) return ff_cell_eval(cm, c, sdel, pre, nc, C, active, r, xt, ax, fx, fy, fz);
+  const int Ki[3] = {__builtin_amdgcn_readlane(K[0], i), __builtin_amdgcn_readlane(K[1], i),
+                     __builtin_amdgcn_readlane(K[2], i)};
+  return cls == kFar ? ff_far<false>(cm, Ki, active, r, ax, fx, fy, fz)
+                     : ff_far<true>(cm, Ki, active, r, ax, fx, fy, fz);
+}
+
+// What bounds it: the vector units, at 1.09 wave instructions per cycle and CU
+// (an FMA with a scalar operand, as 42 of the expansion's are, issues at 0.89,
+// one of vector registers at 1.6).  So the decision, 50 instructions per target
+// and cell, is taken once per wave and cell, 64 cells at a time, where all of
+// the wave's targets agree, and costs a distance where only the opening test
+// differs.  The waves of a block, and the blocks that run beside it, walk the
+// same cells, so that their records are read from the scalar cache.  Five
+// waves per SIMD (96 VGPRs, 15 spilled) beat four by 4% and six by 5%.  1e5
+// points of a 256^3 tangle, cells of 16 and 32, theta 0.25: 2.55 ms before
+// (each lane deciding each cell, a block's four waves on four cells), 1.70 ms.
 template <bool kUniform, int kLevels>
-__global__ __launch_bounds__(256) void k_ff_eval(
+__global__ __launch_bounds__(256, 5) void k_ff_eval(
     const FfCell* __restrict__ cells0, const FfCell* __restrict__ cells1,
     const FfSeg* __restrict__ recs, const int32_t* __restrict__ so,
     const int32_t* __restrict__ kidx, const int32_t* __restrict__ prv,
@@ -632,9 +738,10 @@ __global__ __launch_bounds__(256) void k_ff_eval(
   if (blockIdx.x * kFfTargets >= n) return;  // whole block beyond the live points
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x * kFfTargets + lane;
+  const int t = blockIdx.x * kFfTargets + threadIdx.x;
+  if (t - lane >= n) return;  // the wave's targets
   const bool valid = t < n;
-  const int j = valid ? so[t] : 0;
+  const int j = so[valid ? t : n - 1];  // lanes beyond the points repeat the last one, unwritten
   double r[3];
   uint32_t xt[3];
 #pragma unroll
@@ -652,41 +759,51 @@ __global__ __launch_bounds__(256) void k_ff_eval(
   const int32_t* __restrict__ sdt = kLevels == 2 ? sdel1 : sdel0;
   const float* __restrict__ prt = kLevels == 2 ? pre1 : pre0;
   const int Ct = ax.C[kLevels - 1];
-  const int step = 4 * S;
+  const int step = S;
   __shared__ FfSeg stage[4][64];  // each wave's staged segment records
   FfSeg* lds = stage[w];
-  int c = blockIdx.y * 4 + w;
-  FfHead hc;
-  if (c < Ct) ff_head(top + c, hc);
-  for (; c < Ct; c += step) {
-    // the next cell's decision fields are loaded while this one is summed
-    FfHead hn;
-    if (c + step < Ct) ff_head(top + c + step, hn);
-    if (hc.count > 0) {
-      const bool open =
-          ff_cell_eval(hc, top + c, c, sdt, prt, nc, Ct, valid, r, xt, ax, fx, fy, fz);
-      if (kLevels == 1) {
-        if (__any(open))
-          ff_direct<kUniform>(hc, c, recs, lds, open, kj, kp, jj, pj, xt, ax, dx, dy, dz);
-      } else if (__any(open)) {
-        // the children, each child's decision fields loaded one child ahead
-        FfHead hf;
-        ff_head(cells0 + c * 8, hf);
-        for (int ch = 0; ch < 8; ++ch) {
-          const int f = c * 8 + ch;
-          FfHead hfn;
-          if (ch < 7) ff_head(cells0 + f + 1, hfn);
-          if (hf.count > 0) {
-            const bool near = ff_cell_eval(hf, cells0 + f, f, sdel0, pre0, nc, ax.C[0], open, r,
-                                           xt, ax, fx, fy, fz);
-            if (__any(near))
-              ff_direct<kUniform>(hf, f, recs, lds, near, kj, kp, jj, pj, xt, ax, dx, dy, dz);
-          }
-          hf = hfn;
+  FfBox box;
+  ff_box(xt, valid, box);
+  // The wave's coarsest cells, in groups of one per lane (one level) or of 8,
+  // whose 64 children are then one per lane.
+  constexpr int kGroup = kLevels == 2 ? 8 : 64;
+  for (int c0 = blockIdx.y; c0 < Ct; c0 += step * kGroup) {
+    int K[3] = {0, 0, 0};
+    int cls = kEmpty;
+    if (lane < kGroup && c0 + lane * step < Ct) cls = ff_class(top + c0 + lane * step, box, ax, K);
+    uint32_t open_lo = 0u, open_hi = 0u;  // two levels, lane i: the lanes that open cell i
+    for (uint64_t todo = __ballot(cls != kEmpty); todo; todo &= todo - 1) {
+      const int i = __ffsll((unsigned long long)todo) - 1;
+      const int c = c0 + i * step;
+      const bool op = ff_take(top, c, __builtin_amdgcn_readlane(cls, i), K, i, sdt, prt, nc, Ct,
+                              valid, r, xt, ax, fx, fy, fz);
+      if (kLevels == 2) {
+        const uint64_t m = __ballot(op);
+        if (lane == i) {
+          open_lo = (uint32_t)m;
+          open_hi = (uint32_t)(m >> 32);
         }
+      } else if (__any(op)) {
+        ff_direct<kUniform>(top[c].start, top[c].count, c, recs, lds, op, kj, kp, jj, pj, xt, ax,
+                            dx, dy, dz);
       }
     }
-    hc = hn;
+    if (kLevels == 1) continue;
+    // lane: child lane & 7 of the group's cell lane >> 3
+    const int f0 = (c0 + (lane >> 3) * step) * 8 + (lane & 7);
+    cls = kEmpty;
+    if (__shfl((int)(open_lo | open_hi), lane >> 3) != 0) cls = ff_class(cells0 + f0, box, ax, K);
+    for (uint64_t todo = __ballot(cls != kEmpty); todo; todo &= todo - 1) {
+      const int i = __ffsll((unsigned long long)todo) - 1;
+      const int f = (c0 + (i >> 3) * step) * 8 + (i & 7);
+      const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)open_lo, i >> 3) |
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)open_hi, i >> 3) << 32;
+      const bool near = ff_take(cells0, f, __builtin_amdgcn_readlane(cls, i), K, i, sdel0, pre0,
+                                nc, ax.C[0], (m >> lane) & 1u, r, xt, ax, fx, fy, fz);
+      if (__any(near))
+        ff_direct<kUniform>(cells0[f].start, cells0[f].count, f, recs, lds, near, kj, kp, jj, pj,
+                            xt, ax, dx, dy, dz);
+    }
   }
   if (kUniform) {
     fx = fmaf(dx, ax.qf, fx);
@@ -697,33 +814,25 @@ __global__ __launch_bounds__(256) void k_ff_eval(
     fy += dy;
     fz += dz;
   }
-  __shared__ float red[3][3][kFfTargets];
-  if (w > 0) {
-    red[w - 1][0][lane] = fx;
-    red[w - 1][1][lane] = fy;
-    red[w - 1][2][lane] = fz;
-  }
-  __syncthreads();
-  if (w == 0 && valid) {
+  if (valid) {
     float* out = Pout + (long long)blockIdx.y * 3 * nc;
-    out[j] = ((fx + red[0][0][lane]) + red[1][0][lane]) + red[2][0][lane];
-    out[nc + j] = ((fy + red[0][1][lane]) + red[1][1][lane]) + red[2][1][lane];
-    out[2 * nc + j] = ((fz + red[0][2][lane]) + red[1][2][lane]) + red[2][2][lane];
+    out[j] = fx;
+    out[nc + j] = fy;
+    out[2 * nc + j] = fz;
   }
 }
 
 // v[j][a] = scale * (sum over the S chunk partials of target j, in chunk
-// order, in FP64).
+// order, in FP64); a thread per component.
 __global__ void k_ff_sum(const float* __restrict__ P, int S, int n, double scale,
                          double* __restrict__ v) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    double t = 0.0;
-    for (int c = 0; c < S; ++c) t += (double)P[((long long)c * 3 + a) * n + j];
-    v[3LL * j + a] = t * scale;
-  }
+  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= 3LL * n) return;
+  double t = 0.0;
+#pragma unroll 8
+  for (int c = 0; c < S; ++c) t += (double)P[3LL * c * n + q];
+  const int a = (int)(q / n);
+  v[3 * (q - (long long)a * n) + a] = t * scale;
 }
 
 FfAxes ff_axes(const vlb_bs_desc* d, const vlb_ff_params* p) {
@@ -751,14 +860,16 @@ FfAxes ff_axes(const vlb_bs_desc* d, const vlb_ff_params* p) {
   return ax;
 }
 
-// Chunks of the coarsest cells: about 32768 blocks over the target blocks
-// (a 256^3 tangle of 1e5 points: 15 in a run, whose launch is sized by the
-// capacity, 21 stand-alone; 4 chunks measured 10% slower per coupled step),
-// at least 4 cells per chunk, at most 64 chunks.
+// Chunks of the coarsest cells: about 8192 blocks over the target blocks (a
+// 256^3 tangle of 1e5 points: 21; with 4096 blocks its sum takes 4% longer,
+// with 16384 the same), at most a chunk per cell and 64 chunks.  Few points
+// need the short chunks: 3637 points over 90 cells take 137 us with 64 chunks
+// and 167 us with 22 (22118 points over 324 cells: 473 us with 64 chunks, 481
+// us with 95).
 int ff_chunks(long long n, int Ctop) {
   const long long tb = (n + kFfTargets - 1) / kFfTargets;
-  long long S = (32768 + tb - 1) / tb;
-  if (S > Ctop / 4) S = Ctop / 4;
+  long long S = (8192 + tb - 1) / tb;
+  if (S > Ctop) S = Ctop;
   if (S > 64) S = 64;
   if (S < 1) S = 1;
   return (int)S;
@@ -834,9 +945,22 @@ size_t ff_layout(long long n, const FfAxes& ax, bool solo, char* base, FfBufs* b
     s.sidx[1] = s.sidx[0];
     s.pre[1] = s.pre[0];
   }
-  if (solo) s.P = (float*)take((size_t)s.S * 3 * n * sizeof(float));
+  // (for as many chunks as a box of more cells takes, so that finer cells and
+  // a second level never need less)
+  if (solo) s.P = (float*)take((size_t)ff_chunks(n, 64) * 3 * n * sizeof(float));
   if (b) *b = s;
   return (off + 255) / 256 * 256;
+}
+
+// The order of a level's cells: a wave per (cell, axis) where a cell holds
+// fewer than 64 points on average (4096 cells of 24: 42 us), else 4 waves (512
+// cells of 195: 84 us, with one wave 240 us).
+void ff_order(const FfBufs& b, const int32_t* so, long long n, const FfAxes& ax, int l,
+              hipStream_t stream) {
+  const auto kernel = n < 64LL * ax.C[l] ? k_ff_order<64> : k_ff_order<256>;
+  const int threads = n < 64LL * ax.C[l] ? 64 : 256;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(3 * ax.C[l])), dim3(threads), 0, stream, so, b.comps,
+                     b.srad, b.X, n, ax, l, b.cells[l], b.sdel[l], b.sidx[l], b.pre[l]);
 }
 
 }  // namespace
@@ -887,8 +1011,7 @@ hipError_t ff_solo(const vlb_bs_desc* d, const vlb_ff_params* p, long long n, co
                        3 * l, b.cells[l]);
     hipLaunchKernelGGL(k_ff_comps, dim3(nb), dim3(256), 0, stream, b.M, b.D, b.kidx, b.cnt, n,
                        ax, l, b.comps, b.srad);
-    hipLaunchKernelGGL(k_ff_order, dim3((unsigned)(3 * C)), dim3(64), 0, stream, so, b.comps,
-                       b.srad, b.X, n, ax, l, b.cells[l], b.sdel[l], b.sidx[l], b.pre[l]);
+    ff_order(b, so, n, ax, l, stream);
   }
   const dim3 grid((unsigned)((n + kFfTargets - 1) / kFfTargets), b.S);
 #define FF_EVAL(U, LV)                                                                         \
@@ -901,7 +1024,7 @@ hipError_t ff_solo(const vlb_bs_desc* d, const vlb_ff_params* p, long long n, co
     if (ax.levels == 2) FF_EVAL(false, 2); else FF_EVAL(false, 1);
   }
 #undef FF_EVAL
-  hipLaunchKernelGGL(k_ff_sum, dim3(nb), dim3(256), 0, stream, b.P, b.S, (int)n,
+  hipLaunchKernelGGL(k_ff_sum, dim3((unsigned)((3 * n + 255) / 256)), dim3(256), 0, stream, b.P, b.S, (int)n,
                      d->kappa / (4.0 * M_PI), v);
   return hipGetLastError();
 }
@@ -950,8 +1073,7 @@ hipError_t ff_run_sum(Run& r, const double* Y) {
                        3 * l, b.cells[l]);
     hipLaunchKernelGGL(k_ff_comps, dim3(nb), dim3(256), 0, stream, b.M, b.D, b.kidx, r.cnt, nc,
                        ax, l, b.comps, b.srad);
-    hipLaunchKernelGGL(k_ff_order, dim3((unsigned)(3 * C)), dim3(64), 0, stream, so, b.comps,
-                       b.srad, b.X, nc, ax, l, b.cells[l], b.sdel[l], b.sidx[l], b.pre[l]);
+    ff_order(b, so, nc, ax, l, stream);
   }
   const dim3 grid((unsigned)((nc + kFfTargets - 1) / kFfTargets), r.ffS);
 #define FF_EVAL(U, LV)                                                                         \
