@@ -892,6 +892,70 @@ hipError_t fil_copy_positions(Run& r, const double* src, double* dst) {
 
 namespace {
 
+struct HostArrays {
+  const double* p[4];
+};
+
+// Threads walk the values in the order of the host's arrays, so that a wave
+// writes (or reads) whole lines across the bus.
+__global__ __launch_bounds__(256) void k_export(HostArrays src, int k,
+                                                const int32_t* __restrict__ nxt,
+                                                const int32_t* __restrict__ cnt, long long nc,
+                                                char* __restrict__ host, size_t bytes) {
+  const int n = cnt[0];
+  const uint32_t t0 = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
+  if (t0 == 0) {
+    ((int32_t*)host)[0] = n;
+    ((int32_t*)host)[1] = cnt[7];
+  }
+  if (host_io_need(n, k, nxt ? 1 : 0) > bytes) return;
+  double* out = (double*)(host + kHostIoHeader);
+  const uint32_t per = 3u * (uint32_t)n;
+  for (uint32_t q = t0; q < per * k; q += step) {
+    const uint32_t m = q / per, i = q - m * per;
+    const double* s = m == 0 ? src.p[0] : (m == 1 ? src.p[1] : (m == 2 ? src.p[2] : src.p[3]));
+    out[q] = s[(long long)(i % 3u) * nc + i / 3u];
+  }
+  if (nxt)
+    for (uint32_t j = t0; j < (uint32_t)n; j += step) ((int32_t*)(out + (size_t)per * k))[j] = nxt[j];
+}
+
+__global__ __launch_bounds__(256) void k_import(const char* __restrict__ host, int n, long long nc,
+                                                double* __restrict__ pos,
+                                                int32_t* __restrict__ nxt,
+                                                int32_t* __restrict__ prv,
+                                                int32_t* __restrict__ cnt) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j == 0) cnt[0] = n;
+  if (j >= n) return;
+  const double* xyz = (const double*)(host + kHostIoHeader);
+  const int32_t* links = (const int32_t*)(xyz + 3 * (size_t)n);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) pos[a * nc + j] = xyz[(size_t)a * n + j];
+  nxt[j] = links[j];
+  prv[j] = links[n + j];
+}
+
+}  // namespace
+
+hipError_t fil_export(Run& r, const double* const* src, int k, bool links) {
+  HostArrays a{};
+  for (int m = 0; m < k; ++m) a.p[m] = src[m];
+  long long work = k > 0 ? 3 * k * r.ncap : (links ? r.ncap : 1);
+  if (work > 65536) work = 65536;
+  hipLaunchKernelGGL(k_export, dim3(nblocks(work, 256)), dim3(256), 0, r.stream, a, k,
+                     links ? r.nxt : nullptr, r.cnt, r.ncap, r.host, r.host_bytes);
+  return hipGetLastError();
+}
+
+hipError_t fil_import(Run& r, int n) {
+  hipLaunchKernelGGL(k_import, dim3(nblocks(n > 0 ? n : 1, 256)), dim3(256), 0, r.stream, r.host, n,
+                     r.ncap, r.pos, r.nxt, r.prv, r.cnt);
+  return hipGetLastError();
+}
+
+namespace {
+
 template <class FT>
 void launch_gather(Run& r) {
   auto kern = r.small ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;

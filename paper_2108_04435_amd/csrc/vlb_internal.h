@@ -443,6 +443,8 @@ struct Run {
   hipStream_t stream = nullptr;  // the caller's stream: every call's work joins it
   hipStream_t side = nullptr;    // library stream for the lattice part of a step
   hipEvent_t ev_fork = nullptr, ev_mom = nullptr, ev_fin1 = nullptr, ev_join = nullptr;
+  char* host = nullptr;  // host_bytes of pinned memory for transfers, one at a time
+  size_t host_bytes = 0;
   int device = 0;
   char* ws = nullptr;
   uint64_t ws_bytes = 0;
@@ -632,6 +634,17 @@ hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y,
 // A whole stage (pair sum and finalize) of a small run in one launch.
 hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext);
 hipError_t fil_copy_positions(Run& r, const double* src, double* dst);
+// Point data through the run's pinned memory, in one launch each way: a header
+// of 16 ints, then the data.  export: header n and the latched flags, then k
+// arrays as [n][3] and the links, if the live points' fit (else the header
+// alone).  import: n points, positions 3 x n, links and predecessors.
+constexpr size_t kHostIoBytes = 1 << 20;  // at most, per run
+constexpr size_t kHostIoHeader = 64;
+__host__ __device__ inline size_t host_io_need(long long n, int arrays, int links) {
+  return kHostIoHeader + (size_t)n * (24 * arrays + 4 * links);
+}
+hipError_t fil_export(Run& r, const double* const* src, int k, bool links);
+hipError_t fil_import(Run& r, int n);
 hipError_t fil_spread(Run& r);
 hipError_t fil_seed(Run& r, long long n);
 
