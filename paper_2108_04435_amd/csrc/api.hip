@@ -651,7 +651,7 @@ int one_step(vlb_run* h, bool first, bool last) {
     if (gs == gside) {
       if (two) HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fin1, 0));
       OnStream on(r, S);
-      if (spread) HIP_OR_FAIL(h, fil_spread(r));
+      if (spread) HIP_OR_FAIL(h, fil_spread(r, false));
       // the LBM update (on a narrow grid where the filament part is the
       // longer one), then the moments of f^(n+1) into the next step's field
       // (the stages of this step still read the current one)
@@ -782,7 +782,7 @@ int vlb_eval_line_velocity(vlb_run* h, double* vs, double* vn, double* sdot, dou
     HIP_OR_FAIL(h, bs_sum(r, r.pos));
   }
   HIP_OR_FAIL(h, fil_finalize(r, 1, 1, 1, r.pos, r.ya, 1));
-  if (r.vor.coupling) HIP_OR_FAIL(h, fil_spread(r));
+  if (r.vor.coupling) HIP_OR_FAIL(h, fil_spread(r, true));
   const double* src[4];
   double* dst[4];
   int k = 0;

@@ -135,35 +135,45 @@ __device__ inline double wrap_coord(double x, double L, int periodic) {
 
 // Normal-fluid velocity at a point: delta_2pt weights on the 8 surrounding
 // nodes of the step's bare-velocity field; nodes beyond a wall carry zero.
+// All 24 loads are in flight together (a node beyond a wall reads another and
+// adds nothing): with a branch around each node's loads they followed one
+// another, and 20 steps of a ring of 64 points took 1220 us instead of 1140.
 template <class UT>
 __device__ void interp_vn(const UT* __restrict__ ub, const Geom& g, double px, double py,
                           double pz, double v[3]) {
-  const double b[3] = {floor(px), floor(py), floor(pz)};
-  const double fr[3] = {px - b[0], py - b[1], pz - b[2]};
+  const double fr[3] = {px - floor(px), py - floor(py), pz - floor(pz)};
   const int ib[3] = {ifloor_safe(px), ifloor_safe(py), ifloor_safe(pz)};
   const int n[3] = {g.nx, g.ny, g.nz};
-  v[0] = v[1] = v[2] = 0.0;
-  for (int o = 0; o < 8; ++o) {
-    const int off[3] = {o & 1, (o >> 1) & 1, (o >> 2) & 1};
-    int node[3];
-    double w = 1.0;
-    bool ghost = false;
-    for (int a = 0; a < 3; ++a) {
-      int c = ib[a] + off[a];
-      w *= off[a] ? fr[a] : 1.0 - fr[a];
-      if (c < 0 || c >= n[a]) {
-        if (g.wall[a])
-          ghost = true;
-        else
-          c = ((c % n[a]) + n[a]) % n[a];
-      }
-      node[a] = c;
+  int node[3][2];
+  bool ghost[3][2];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      int c = ib[a] + s;
+      const bool out = c < 0 || c >= n[a];
+      ghost[a][s] = out && g.wall[a];
+      if (out) c = g.wall[a] ? 0 : ((c % n[a]) + n[a]) % n[a];
+      node[a][s] = c;
     }
-    if (ghost) continue;
-    const long long c = ((long long)node[2] * g.ny + node[1]) * g.nx + node[0];
-    v[0] += w * (double)ub[c];
-    v[1] += w * (double)ub[g.cells + c];
-    v[2] += w * (double)ub[2 * g.cells + c];
+  UT u[8][3];
+#pragma unroll
+  for (int o = 0; o < 8; ++o) {
+    const long long c =
+        ((long long)node[2][o >> 2] * g.ny + node[1][(o >> 1) & 1]) * g.nx + node[0][o & 1];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) u[o][a] = ub[a * g.cells + c];
+  }
+  v[0] = v[1] = v[2] = 0.0;
+#pragma unroll
+  for (int o = 0; o < 8; ++o) {
+    const int off[3] = {o & 1, (o >> 1) & 1, o >> 2};
+    double w = 1.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) w *= off[a] ? fr[a] : 1.0 - fr[a];
+    const bool in = !(ghost[0][off[0]] || ghost[1][off[1]] || ghost[2][off[2]]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] = in ? v[a] + w * (double)u[o][a] : v[a];
   }
 }
 
@@ -191,15 +201,18 @@ __device__ __forceinline__ void fin_roles(const FinArgs& A, int grp, int lane, i
   if (slot && grp == 1) {
     const double p[3] = {A.Y[j], A.Y[nc + j], A.Y[2 * nc + j]};
     double vn[3];
-    interp_vn<UT>((const UT*)A.ub, g, p[0], p[1], p[2], vn);
-    for (int a = 0; a < 3; ++a) sh.vn[a][lane] = vn[a];
-    if (live && A.skeys) {
+    int below = 0;  // the point pushed upon
+    const bool push = live && A.skeys;
+    if (push) {
       int b[3];
       const uint32_t key = base_key(A.sg, p, b);
       A.skeys[j] = key;
-      A.bnext[j] = atomicExch(&A.bins[key], j);
+      below = atomicExch(&A.bins[key], j);
       for (int a = 0; a < 3; ++a) A.sfrac[a * nc + j] = p[a] - floor(p[a]);
     }
+    interp_vn<UT>((const UT*)A.ub, g, p[0], p[1], p[2], vn);
+    for (int a = 0; a < 3; ++a) sh.vn[a][lane] = vn[a];
+    if (push) A.bnext[j] = below;
   }
   if (slot && grp == 2) {
     // local geometry (three-point derivatives on a non-uniform arc length)
@@ -222,16 +235,17 @@ __device__ __forceinline__ void fin_roles(const FinArgs& A, int grp, int lane, i
     if (jn == j || jp == j)
       for (int a = 2; a >= 0; --a)
         if (!per[a] && (pj[a] == -0.5 || pj[a] == L[a] - 0.5)) ea = a;
+    double lp = lp_real, lm = lm_real;
     if (ea >= 0) {
       if (jn == j) {
         for (int a = 0; a < 3; ++a) dp[a] = a == ea ? dm[a] : -dm[a];
       } else {
         for (int a = 0; a < 3; ++a) dm[a] = a == ea ? dp[a] : -dp[a];
       }
+      lp = sqrt(dp[0] * dp[0] + dp[1] * dp[1] + dp[2] * dp[2]);
+      lm = sqrt(dm[0] * dm[0] + dm[1] * dm[1] + dm[2] * dm[2]);
     }
     sh.end[lane] = ea;
-    const double lp = sqrt(dp[0] * dp[0] + dp[1] * dp[1] + dp[2] * dp[2]);
-    const double lm = sqrt(dm[0] * dm[0] + dm[1] * dm[1] + dm[2] * dm[2]);
     const double iden = 1.0 / (lp * lm * (lp + lm));
     double sp[3], spp[3];
     for (int a = 0; a < 3; ++a) {
@@ -475,8 +489,10 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
 //
 // What bounds it: latency.  A ring of 64 points spent 4.4 us in the sum, 7.9
 // in the finalize and about 4 between them per stage; with the roles before
-// the sum on the same waves this kernel took 10.4.  It pays while the chip
-// is not filled by the sum (kStagePoints).
+// the sum on the same waves this kernel took 10.4, this way 8.6, and 7.2 with
+// no load waiting for the point count and the loads of the velocity field in
+// flight together.  It pays while the chip is not filled by the sum
+// (kStagePoints).
 constexpr int kStTargets = 8;
 constexpr int kStThreads = 256;  // threads of the sum
 constexpr int kStSlices = kStThreads / kStTargets;
@@ -493,25 +509,28 @@ __global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx) {
     if (n > 2)
       *(long long*)(A.cnt + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
   }
+  // The loads of the first tile and of the roles do not wait for the point
+  // count: slots below the capacity are read (links clamped, values beyond the
+  // points unused), and a block beyond the points writes nothing.
+  const int nc = (int)A.ncap;
+  const int tiles = max(1, (n + kStThreads - 1) / kStThreads);
   const int j0 = blockIdx.x * kStTargets;
-  if (j0 >= n) return;
   const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
   if (grp >= 4) {
     if (lane < kStTargets)
-      fin_roles<UT>(A, grp - 4, lane, j0 + lane, j0 + lane < A.ncap, j0 + lane < n, sh);
+      fin_roles<UT>(A, grp - 4, lane, j0 + lane, j0 + lane < nc, j0 + lane < n, sh);
     // the barriers of the sum
-    for (int copy = 0; copy < bx.copies; ++copy)
-      for (int t0 = 0; t0 < n; t0 += kStThreads) {
-        __syncthreads();
-        __syncthreads();
-      }
+    for (int t = 0; t < bx.copies * tiles; ++t) {
+      __syncthreads();
+      __syncthreads();
+    }
     __syncthreads();
     return;
   }
 
   const int tl = threadIdx.x % kStTargets, sl = threadIdx.x / kStTargets;
   const int j = j0 + tl;
-  const int jc = min(j, n - 1);  // lanes beyond the points repeat the last one, unwritten
+  const int jc = min(j, nc - 1);  // (lanes beyond the points write nothing)
   double y[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
@@ -530,14 +549,15 @@ __global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx) {
     const int jj = copy == 0 || copy == oc ? jc : -1;
     float fx = 0.f, fy = 0.f, fz = 0.f;
     td.ax = td.ay = td.az = 0.0;
-    for (int t0 = 0; t0 < n; t0 += kStThreads) {
+    for (int tile = 0; tile == 0 || tile < tiles; ++tile) {
+      const int t0 = tile * kStThreads;
       const int k = t0 + threadIdx.x;
-      if (k < n) {
+      if (k < nc) {
         if constexpr (kF32)
           src[threadIdx.x] = bs_stage_f32<kVar != 0, true>(
-              in, nullptr, 0, k, n, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
+              in, nullptr, 0, k, nc, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
         else
-          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, n, copy, bx);
+          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, nc, copy, bx);
       }
       __syncthreads();
       const int cnt = min(kStThreads, n - t0);
@@ -708,7 +728,9 @@ __device__ inline bool bin_around(const int e[3], int q, const SpreadGeom& sg, u
 // points); this is one of 13.  A ring of 64 points, alone on the chip: 12 us
 // by threads walking the eight bins in turn, 4.8 by waves; beside the pair
 // sums of a large run the eight times more waves wait for their slots (9.4e3
-// points: 27 against 33 us), so waves are for small runs (kStagePoints).
+// points: 27 against 33 us), so waves are for small runs (kStagePoints) and,
+// up to kGatherWaves points, for a gather with nothing beside it (the line
+// velocity of 700 points 73 -> 65 us, of 9.4e3 196 -> 193, of 2e4 619 -> 621).
 template <class FT, bool kWave>
 __global__ __launch_bounds__(256) void k_spread_gather(
     const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
@@ -956,21 +978,24 @@ hipError_t fil_import(Run& r, int n) {
 
 namespace {
 
+constexpr long long kGatherWaves = 16384;
+
 template <class FT>
-void launch_gather(Run& r) {
-  auto kern = r.small ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;
-  hipLaunchKernelGGL(kern, dim3(nblocks((r.small ? 64 : 8) * r.ncap, 256)), dim3(256), 0, r.stream,
+void launch_gather(Run& r, bool waves) {
+  auto kern = waves ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;
+  hipLaunchKernelGGL(kern, dim3(nblocks((waves ? 64 : 8) * r.ncap, 256)), dim3(256), 0, r.stream,
                      r.skeys, r.bins, r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, spread_geom(r),
                      r.cells, (FT*)r.force, r.touched);
 }
 
 }  // namespace
 
-hipError_t fil_spread(Run& r) {
+hipError_t fil_spread(Run& r, bool alone) {
+  const bool waves = r.small || (alone && r.ncap <= kGatherWaves);
   if (r.prec == VLB_F64)
-    launch_gather<double>(r);
+    launch_gather<double>(r, waves);
   else
-    launch_gather<float>(r);
+    launch_gather<float>(r, waves);
   return hipGetLastError();
 }
 

@@ -645,7 +645,8 @@ __host__ __device__ inline size_t host_io_need(long long n, int arrays, int link
 }
 hipError_t fil_export(Run& r, const double* const* src, int k, bool links);
 hipError_t fil_import(Run& r, int n);
-hipError_t fil_spread(Run& r);
+// alone: nothing else of the run is in flight.
+hipError_t fil_spread(Run& r, bool alone);
 hipError_t fil_seed(Run& r, long long n);
 
 // swap: compact into the other point arrays and swap them (steps); else

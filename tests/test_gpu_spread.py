@@ -36,7 +36,7 @@ def _crowded(per_cell):
 @pytest.mark.parametrize("precision", ["f64", "f32"])
 @pytest.mark.parametrize("walls", [(False, False, False), (True, False, True)])
 @pytest.mark.parametrize("per_cell", [2, 8, 9, 40, 220])
-@pytest.mark.parametrize("cap", [1000, 1400])   # a wave per point, a thread per node
+@pytest.mark.parametrize("cap", [1000, 17000])   # a wave per point, a thread per node
 def test_crowded_cells(per_cell, walls, precision, cap):
     dims = (30, 26, 28)
     lat = Lattice(*dims, walls=walls)
