@@ -219,7 +219,7 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   r.small = r.vor.ff_cell == 0 && r.ncap * r.bsax.copies <= kStagePoints;
   // Which part of a step is the longer one, by its work at the rates they
   // reach: pairs of the Biot-Savart sums (1.5e12 per second in FP32, half of
-  // that in FP64; with the far field 28 ns per point and sum) against the
+  // that in FP64; with the far field 20 ns per point and sum) against the
   // bytes of the update and the moments at 5 TB/s.  128x128x256 FP32 with
   // 2e3 points (30 us of pairs, 210 us of lattice): see the moments kernel;
   // counterflow (64x64x256, 9.4e3 points: 480 against 53 us) keeps the narrow
@@ -228,7 +228,7 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
     const double sums = (double)r.vor.rk_stages * r.vor.vfm_substeps;
     const double nn = (double)r.ncap;
     const double fil = r.vor.ff_cell > 0
-                           ? sums * nn * 28e-9
+                           ? sums * nn * 20e-9
                            : sums * nn * nn * r.bsax.copies / (r.prec == VLB_F64 ? 0.75e12 : 1.5e12);
     const double latt = (double)r.cells * (57.0 * elt_size(r.prec) + (r.prec == VLB_F64 ? 48 : 24)) / 5e12;
     r.narrow_steps = fil > latt;
@@ -585,6 +585,12 @@ struct OnStream {
 // the side stream from main and computes its own moments; the last one
 // joins the side stream back, so a call's work is ordered on the caller's
 // stream.
+//
+// A run whose kernels are all short keeps to the caller's stream.  Its second,
+// third and fourth stage carry the spreading, the update and the next moments
+// in blocks of their own (a ring of 64 points in 32^3, 20 steps: 1131 us with
+// a launch for each, 901 so); what fewer stages do not carry follows them.  A
+// timed run launches each by itself.
 int one_step(vlb_run* h, bool first, bool last) {
   Run& r = h->r;
   if (!r.has_points) {  // never seeded: the normal fluid alone
@@ -623,6 +629,15 @@ int one_step(vlb_run* h, bool first, bool last) {
   // the side stream's work follows the second stage (the first if there is
   // only one)
   const int gside = G > 1 ? 1 : 0;
+  // one stream: the stages after the first carry the gather, the update and
+  // the moments of f^(n+1), one each
+  const bool ride = r.one_stream && !r.timing && lbm_can_ride(r);
+  int task = !ride ? 3 : (spread ? 0 : 1);
+  const int tasks = last ? 2 : 3;
+  const auto swap_next = [&r] {
+    std::swap(r.ub, r.ub_next);
+    std::swap(r.Vs, r.Vs_next);
+  };
   for (int gs = 0; gs < G; ++gs) {
     const int s = gs % K;
     // FP32: the grid coordinates of every stage's positions were written by
@@ -630,7 +645,22 @@ int one_step(vlb_run* h, bool first, bool last) {
     // for the step's first stage, the previous finalize for the others)
     if (r.small) {
       if (two && gs == 0) HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_mom, 0));
-      HIP_OR_FAIL(h, fil_stage(r, s + 1, gs == 0, gs == G - 1, Ys[s], Yn[s]));
+      SideWork side;
+      const int carried = gs > 0 && task < tasks ? task++ : -1;
+      if (carried == 0) side = fil_ride_gather(r);
+      if (carried == 1) side = lbm_ride_update(r);
+      if (carried == 2) {
+        swap_next();
+        side = lbm_ride_moments(r);
+        swap_next();
+      }
+      HIP_OR_FAIL(h, fil_stage(r, s + 1, gs == 0, gs == G - 1, Ys[s], Yn[s], side));
+      if (carried == 2) {
+        swap_next();
+        const hipError_t e = lbm_moments_after(r);
+        swap_next();
+        if (e != hipSuccess) return hip_fail(h, e, "lbm_moments");
+      }
     } else if (r.vor.ff_cell > 0) {
       HIP_OR_FAIL(h, ff_run_sum(r, Ys[s]));
     } else {
@@ -648,7 +678,7 @@ int one_step(vlb_run* h, bool first, bool last) {
     if (two && gs == 0) HIP_OR_FAIL(h, hipEventRecord(r.ev_fin1, M));
     // the side stream's work is enqueued after the main stream's next
     // kernel, so that a graph keeps the main chain on one queue
-    if (gs == gside) {
+    if (gs == gside && !ride) {
       if (two) HIP_OR_FAIL(h, hipStreamWaitEvent(S, r.ev_fin1, 0));
       OnStream on(r, S);
       if (spread) HIP_OR_FAIL(h, fil_spread(r, false));
@@ -658,22 +688,28 @@ int one_step(vlb_run* h, bool first, bool last) {
       r.lbm_narrow = r.narrow_steps;
       hipError_t le = lbm_step(r);
       if (le == hipSuccess && !last) {
-        std::swap(r.ub, r.ub_next);
-        std::swap(r.Vs, r.Vs_next);
+        swap_next();
         le = lbm_moments(r);
-        std::swap(r.ub, r.ub_next);
-        std::swap(r.Vs, r.Vs_next);
+        swap_next();
       }
       r.lbm_narrow = false;
       if (le != hipSuccess) return hip_fail(h, le, "lbm_step / lbm_moments");
       if (two && !last) HIP_OR_FAIL(h, hipEventRecord(r.ev_mom, S));
     }
   }
-  HIP_OR_FAIL(h, topo_update(r, true));
-  if (!last) {
-    std::swap(r.ub, r.ub_next);
-    std::swap(r.Vs, r.Vs_next);
+  // what fewer stages did not carry
+  for (; ride && task < tasks; ++task) {
+    if (task == 0) HIP_OR_FAIL(h, fil_spread(r, true));
+    if (task == 1) HIP_OR_FAIL(h, lbm_step(r));
+    if (task == 2) {
+      swap_next();
+      const hipError_t e = lbm_moments(r);
+      swap_next();
+      if (e != hipSuccess) return hip_fail(h, e, "lbm_moments");
+    }
   }
+  HIP_OR_FAIL(h, topo_update(r, true));
+  if (!last) swap_next();
   if (two && last) {
     HIP_OR_FAIL(h, hipEventRecord(r.ev_join, S));
     HIP_OR_FAIL(h, hipStreamWaitEvent(M, r.ev_join, 0));

@@ -9,6 +9,7 @@
 //    owned by exactly one bin and gathers the contributions of the (at most
 //    8) bins around it, each bin's points in ascending order.
 #include "bs_pair.h"
+#include "lbm_node.h"
 
 #include <type_traits>
 
@@ -479,119 +480,6 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
   fin_combine(A, lane, j, vs, sh);
 }
 
-// One stage of a small run in one launch: the pair sum and the finalize of 8
-// points per block.  Waves 0 to 3: thread (slice, target) adds every 32nd
-// segment of the staged tiles for its target; the 32 slices are added in
-// FP64 in a fixed tree.  Waves 5 to 7 meanwhile take the roles of the
-// finalize (fin_roles; wave 4 has none).  Source records come from the
-// positions Y (other blocks may already write the next stage's), in FP32
-// too.
-//
-// What bounds it: latency.  A ring of 64 points spent 4.4 us in the sum, 7.9
-// in the finalize and about 4 between them per stage; with the roles before
-// the sum on the same waves this kernel took 10.4, this way 8.6, and 7.2 with
-// no load waiting for the point count and the loads of the velocity field in
-// flight together.  It pays while the chip is not filled by the sum
-// (kStagePoints).
-constexpr int kStTargets = 8;
-constexpr int kStThreads = 256;  // threads of the sum
-constexpr int kStSlices = kStThreads / kStTargets;
-
-template <bool kF32, int kVar, class UT>
-__global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx) {
-  using Src = std::conditional_t<kF32, BsSrc, BsSrcD>;
-  __shared__ Src src[kStThreads];
-  __shared__ FinShared<kStTargets> sh;
-  __shared__ double red[4][3][kStTargets];
-  const int n = A.cnt[0];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (A.skeys) A.cnt[11] = n;
-    if (n > 2)
-      *(long long*)(A.cnt + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
-  }
-  // The loads of the first tile and of the roles do not wait for the point
-  // count: slots below the capacity are read (links clamped, values beyond the
-  // points unused), and a block beyond the points writes nothing.
-  const int nc = (int)A.ncap;
-  const int tiles = max(1, (n + kStThreads - 1) / kStThreads);
-  const int j0 = blockIdx.x * kStTargets;
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  if (grp >= 4) {
-    if (lane < kStTargets)
-      fin_roles<UT>(A, grp - 4, lane, j0 + lane, j0 + lane < nc, j0 + lane < n, sh);
-    // the barriers of the sum
-    for (int t = 0; t < bx.copies * tiles; ++t) {
-      __syncthreads();
-      __syncthreads();
-    }
-    __syncthreads();
-    return;
-  }
-
-  const int tl = threadIdx.x % kStTargets, sl = threadIdx.x / kStTargets;
-  const int j = j0 + tl;
-  const int jc = min(j, nc - 1);  // (lanes beyond the points write nothing)
-  double y[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
-  int oc = 0;  // the image copy whose own segments are excluded too
-  if (bx.copies > 1 && (in.nxt[jc] == jc || in.prv[jc] == jc)) oc = bs_own_copy(y, bx);
-  uint32_t xt[3] = {0u, 0u, 0u};
-  BsTgtD td;
-  if constexpr (kF32) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) xt[a] = bs_grid_f32(y[a], bx, a);
-  } else {
-    bs_target_f64<kVar>(y, bx, td);
-  }
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int copy = 0; copy < bx.copies; ++copy) {
-    const int jj = copy == 0 || copy == oc ? jc : -1;
-    float fx = 0.f, fy = 0.f, fz = 0.f;
-    td.ax = td.ay = td.az = 0.0;
-    for (int tile = 0; tile == 0 || tile < tiles; ++tile) {
-      const int t0 = tile * kStThreads;
-      const int k = t0 + threadIdx.x;
-      if (k < nc) {
-        if constexpr (kF32)
-          src[threadIdx.x] = bs_stage_f32<kVar != 0, true>(
-              in, nullptr, 0, k, nc, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
-        else
-          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, nc, copy, bx);
-      }
-      __syncthreads();
-      const int cnt = min(kStThreads, n - t0);
-#pragma unroll 2
-      for (int s = sl; s < cnt; s += kStSlices) {
-        const Src g = src[s];
-        const bool ex = t0 + s == jj || g.kn == jj;
-        if constexpr (kF32)
-          bs_pair_f32<kVar != 0>(g, xt[0], xt[1], xt[2], bx.invq_f[0], bx.invq_f[1], bx.invq_f[2],
-                                 ex, fx, fy, fz);
-        else
-          bs_pair_f64<kVar>(g, td, ex, bx.invq_d[0], bx.invq_d[1], bx.invq_d[2]);
-      }
-      __syncthreads();
-    }
-    const double sg = (kF32 ? 1.0 : 0.5) * (double)bx.sign[copy];
-    v[0] += sg * (kF32 ? (double)fx : td.ax);
-    v[1] += sg * (kF32 ? (double)fy : td.ay);
-    v[2] += sg * (kF32 ? (double)fz : td.az);
-  }
-#pragma unroll
-  for (int off = kStTargets; off < 64; off <<= 1)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) v[a] += __shfl_xor(v[a], off);
-  if (lane < kStTargets)
-    for (int a = 0; a < 3; ++a) red[grp][a][lane] = v[a];
-  __syncthreads();
-  if (threadIdx.x >= kStTargets || j >= n) return;
-  double vs[3];
-  for (int a = 0; a < 3; ++a)
-    vs[a] = (((red[0][a][lane] + red[1][a][lane]) + red[2][a][lane]) + red[3][a][lane]) * A.nl_scale;
-  fin_combine(A, lane, j, vs, sh);
-}
-
 // ----------------------------------------------------------- spreading
 
 // Sum of the contributions to one node of the m points of a bin's list,
@@ -731,39 +619,46 @@ __device__ inline bool bin_around(const int e[3], int q, const SpreadGeom& sg, u
 // points: 27 against 33 us), so waves are for small runs (kStagePoints) and,
 // up to kGatherWaves points, for a gather with nothing beside it (the line
 // velocity of 700 points 73 -> 65 us, of 9.4e3 196 -> 193, of 2e4 619 -> 621).
+struct GatherArgs {
+  const uint32_t* skeys;
+  const int32_t* bins;
+  const int32_t* bnext;
+  const double* sfrac;
+  const double* gpt;
+  int32_t* touched;
+};
+
 template <class FT, bool kWave>
-__global__ __launch_bounds__(256) void k_spread_gather(
-    const uint32_t* __restrict__ skey, const int32_t* __restrict__ bins,
-    const int32_t* __restrict__ bnext, const double* __restrict__ sfrac,
-    const double* __restrict__ gpt, int32_t* __restrict__ cnt, long long ncap, SpreadGeom sg,
-    long long cells, FT* __restrict__ F, int32_t* __restrict__ touched) {
-  const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void spread_gather(long long id, const GatherArgs& s,
+                                              int32_t* __restrict__ cnt, long long ncap,
+                                              const SpreadGeom& sg, long long cells,
+                                              FT* __restrict__ F) {
   const int r = (int)(id >> (kWave ? 6 : 3));
   const int o = (int)(id >> (kWave ? 3 : 0)) & 7;
-  const uint32_t me = r < ncap ? skey[r] : 0u;  // (beyond the points: unused)
+  const uint32_t me = r < ncap ? s.skeys[r] : 0u;  // (beyond the points: unused)
   const int n = cnt[11];
   if (id == 0) cnt[1] = 8 * n;
   if (r >= n) return;
-  int32_t* const mine = touched + 8LL * r + o;
+  int32_t* const mine = s.touched + 8LL * r + o;
   int e[3], lat[3];
   double f[3] = {0.0, 0.0, 0.0};
   if constexpr (kWave) {
     const int q = threadIdx.x & 7;
-    if (bins[me] != r) {  // uniform over the wave
+    if (s.bins[me] != r) {  // uniform over the wave
       if (q == 0) *mine = -1;
       return;
     }
     const bool inside = bin_corner(me, o, sg, e, lat);
     uint32_t key;
-    const int head = bin_around(e, q, sg, key) && inside ? bins[key] : -1;
+    const int head = bin_around(e, q, sg, key) && inside ? s.bins[key] : -1;
     const uint64_t smaller = __ballot(head >= 0 && key < me);
     const bool owner = inside && ((smaller >> (8 * o)) & 0xffu) == 0;
-    if (owner && head >= 0) add_bin(head, n, bnext, BinPoint{sfrac, gpt, ncap, q}, f);
+    if (owner && head >= 0) add_bin(head, n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       double t = __shfl(f[a], 8 * o);
 #pragma unroll
-      for (int s = 1; s < 8; ++s) t += __shfl(f[a], 8 * o + s);
+      for (int k = 1; k < 8; ++k) t += __shfl(f[a], 8 * o + k);
       f[a] = t;
     }
     if (q != 0) return;
@@ -772,7 +667,7 @@ __global__ __launch_bounds__(256) void k_spread_gather(
       return;
     }
   } else {
-    if (bins[me] != r || !bin_corner(me, o, sg, e, lat)) {
+    if (s.bins[me] != r || !bin_corner(me, o, sg, e, lat)) {
       *mine = -1;
       return;
     }
@@ -781,7 +676,7 @@ __global__ __launch_bounds__(256) void k_spread_gather(
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       uint32_t key;
-      head[q] = bin_around(e, q, sg, key) ? bins[key] : -1;
+      head[q] = bin_around(e, q, sg, key) ? s.bins[key] : -1;
       owner = owner && !(head[q] >= 0 && key < me);
     }
     if (!owner) {
@@ -789,12 +684,185 @@ __global__ __launch_bounds__(256) void k_spread_gather(
       return;
     }
     for (int q = 0; q < 8; ++q)
-      if (head[q] >= 0) add_bin(head[q], n, bnext, BinPoint{sfrac, gpt, ncap, q}, f);
+      if (head[q] >= 0) add_bin(head[q], n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
   }
   const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
 #pragma unroll
   for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
   *mine = (int32_t)node;
+}
+
+// The work a stage carries, in blocks of kSideThreads (two items of 256
+// threads each for the moments, whose sums keep their tree).
+template <class UT, class S>
+__device__ __forceinline__ void side_work(const SideWork& w, const FinArgs& A,
+                                          const GatherArgs& ga, int block, double (*red)[256]) {
+  const Geom& g = A.g;
+  const int tid = threadIdx.x;
+  if (w.kind == SideWork::kGather) {
+    spread_gather<UT, true>((long long)block * kSideThreads + tid, ga, A.cnt, A.ncap, A.sg, g.cells,
+                            (UT*)w.force);
+  } else if (w.kind == SideWork::kUpdate) {
+    const int c = block * kSideThreads + tid;
+    if (c >= (int)g.cells) return;
+    const int t = c / g.nx, z = t / g.ny;
+    if (w.parity == 0)
+      collide_node<S, 0, false, true>((S*)w.pops, (const UT*)w.force, g, c - t * g.nx, t - z * g.ny, z);
+    else
+      collide_node<S, 1, false, true>((S*)w.pops, (const UT*)w.force, g, c - t * g.nx, t - z * g.ny, z);
+  } else {
+    const SpreadClear<UT> sc{w.clear ? A.cnt : nullptr, ga.touched, ga.skeys, (int32_t*)ga.bins,
+                             (UT*)w.force};
+    spread_clear(sc, g.cells, block * kSideThreads + tid, w.blocks * kSideThreads);
+    const int half = tid >> 8, t = tid & 255, nt = w.bx * w.by;
+    const int it = 2 * block + half;
+    double uzv = 0.0;
+    if (it < w.items && t < nt) {
+      const int ty = t / w.bx, tx = t - ty * w.bx;
+      uzv = w.parity == 0
+                ? moments_item<S, UT, 0, true, false>((const S*)w.pops, g, (UT*)w.ub, it, w.parts, tx, ty, w.bx, w.by)
+                : moments_item<S, UT, 1, true, false>((const S*)w.pops, g, (UT*)w.ub, it, w.parts, tx, ty, w.bx, w.by);
+    }
+    if (!w.Ps) return;
+    red[half][t] = uzv;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+      if (t < s && t + s < nt) red[half][t] += red[half][t + s];
+      __syncthreads();
+    }
+    if (t == 0 && it < w.items) w.Ps[it] = w.parts == 1 ? w.scale * red[half][0] : red[half][0];
+  }
+}
+
+// One stage of a small run in one launch: the pair sum and the finalize of 8
+// points per block.  Waves 0 to 3: thread (slice, target) adds every 32nd
+// segment of the staged tiles for its target; the 32 slices are added in
+// FP64 in a fixed tree.  Waves 5 to 7 meanwhile take the roles of the
+// finalize (fin_roles; wave 4 has none).  Source records come from the
+// positions Y (other blocks may already write the next stage's), in FP32
+// too.
+//
+// What bounds it: latency.  A ring of 64 points spent 4.4 us in the sum, 7.9
+// in the finalize and about 4 between them per stage; with the roles before
+// the sum on the same waves this kernel took 10.4, this way 8.6, and 7.2 with
+// no load waiting for the point count and the loads of the velocity field in
+// flight together.  It pays while the chip is not filled by the sum
+// (kStagePoints).
+//
+// Blocks from `blocks` on do the work it carries (side_work): latency bound
+// as well, it costs nothing beside the stage, where the gather, the update and
+// the moments took 15 us of a ring's 56 us step as launches of their own.
+constexpr int kStTargets = 8;
+constexpr int kStThreads = 256;  // threads of the sum
+constexpr int kStSlices = kStThreads / kStTargets;
+
+template <bool kF32, int kVar, class UT, class S>
+__global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx, SideWork side,
+                                               GatherArgs ga, int blocks) {
+  using Src = std::conditional_t<kF32, BsSrc, BsSrcD>;
+  __shared__ Src src[kStThreads];
+  __shared__ FinShared<kStTargets> sh;
+  __shared__ double red[4][3][kStTargets];
+  if ((int)blockIdx.x >= blocks) {
+    __shared__ double sums[2][256];
+    side_work<UT, S>(side, A, ga, blockIdx.x - blocks, sums);
+    return;
+  }
+  const int n = A.cnt[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (A.skeys) A.cnt[11] = n;
+    if (n > 2)
+      *(long long*)(A.cnt + 16) += (long long)n * (n - 2) + (long long)(bx.copies - 1) * n * n;
+  }
+  // The loads of the first tile and of the roles do not wait for the point
+  // count: slots below the capacity are read (links clamped, values beyond the
+  // points unused), and a block beyond the points writes nothing.
+  const int nc = (int)A.ncap;
+  const int tiles = max(1, (n + kStThreads - 1) / kStThreads);
+  const int j0 = blockIdx.x * kStTargets;
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  if (grp >= 4) {
+    if (lane < kStTargets)
+      fin_roles<UT>(A, grp - 4, lane, j0 + lane, j0 + lane < nc, j0 + lane < n, sh);
+    // the barriers of the sum
+    for (int t = 0; t < bx.copies * tiles; ++t) {
+      __syncthreads();
+      __syncthreads();
+    }
+    __syncthreads();
+    return;
+  }
+
+  const int tl = threadIdx.x % kStTargets, sl = threadIdx.x / kStTargets;
+  const int j = j0 + tl;
+  const int jc = min(j, nc - 1);  // (lanes beyond the points write nothing)
+  double y[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
+  int oc = 0;  // the image copy whose own segments are excluded too
+  if (bx.copies > 1 && (in.nxt[jc] == jc || in.prv[jc] == jc)) oc = bs_own_copy(y, bx);
+  uint32_t xt[3] = {0u, 0u, 0u};
+  BsTgtD td;
+  if constexpr (kF32) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) xt[a] = bs_grid_f32(y[a], bx, a);
+  } else {
+    bs_target_f64<kVar>(y, bx, td);
+  }
+  double v[3] = {0.0, 0.0, 0.0};
+  for (int copy = 0; copy < bx.copies; ++copy) {
+    const int jj = copy == 0 || copy == oc ? jc : -1;
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    td.ax = td.ay = td.az = 0.0;
+    for (int tile = 0; tile == 0 || tile < tiles; ++tile) {
+      const int t0 = tile * kStThreads;
+      const int k = t0 + threadIdx.x;
+      if (k < nc) {
+        if constexpr (kF32)
+          src[threadIdx.x] = bs_stage_f32<kVar != 0, true>(
+              in, nullptr, 0, k, nc, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
+        else
+          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, nc, copy, bx);
+      }
+      __syncthreads();
+      const int cnt = min(kStThreads, n - t0);
+#pragma unroll 2
+      for (int s = sl; s < cnt; s += kStSlices) {
+        const Src g = src[s];
+        const bool ex = t0 + s == jj || g.kn == jj;
+        if constexpr (kF32)
+          bs_pair_f32<kVar != 0>(g, xt[0], xt[1], xt[2], bx.invq_f[0], bx.invq_f[1], bx.invq_f[2],
+                                 ex, fx, fy, fz);
+        else
+          bs_pair_f64<kVar>(g, td, ex, bx.invq_d[0], bx.invq_d[1], bx.invq_d[2]);
+      }
+      __syncthreads();
+    }
+    const double sg = (kF32 ? 1.0 : 0.5) * (double)bx.sign[copy];
+    v[0] += sg * (kF32 ? (double)fx : td.ax);
+    v[1] += sg * (kF32 ? (double)fy : td.ay);
+    v[2] += sg * (kF32 ? (double)fz : td.az);
+  }
+#pragma unroll
+  for (int off = kStTargets; off < 64; off <<= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] += __shfl_xor(v[a], off);
+  if (lane < kStTargets)
+    for (int a = 0; a < 3; ++a) red[grp][a][lane] = v[a];
+  __syncthreads();
+  if (threadIdx.x >= kStTargets || j >= n) return;
+  double vs[3];
+  for (int a = 0; a < 3; ++a)
+    vs[a] = (((red[0][a][lane] + red[1][a][lane]) + red[2][a][lane]) + red[3][a][lane]) * A.nl_scale;
+  fin_combine(A, lane, j, vs, sh);
+}
+
+template <class FT, bool kWave>
+__global__ __launch_bounds__(256) void k_spread_gather(GatherArgs s, int32_t* __restrict__ cnt,
+                                                       long long ncap, SpreadGeom sg,
+                                                       long long cells, FT* __restrict__ F) {
+  spread_gather<FT, kWave>((long long)blockIdx.x * blockDim.x + threadIdx.x, s, cnt, ncap, sg,
+                           cells, F);
 }
 
 inline int nblocks(long long n, int b) { return (int)((n + b - 1) / b); }
@@ -857,35 +925,49 @@ FinArgs fin_args(Run& r, int stage, int first, int last, const double* Y, double
   return A;
 }
 
+GatherArgs gather_args(const Run& r) {
+  return GatherArgs{r.skeys, r.bins, r.bnext, r.sfrac, r.gpt, r.touched};
+}
+
+using StageKernel = void (*)(FinArgs, BsPts, BsAxes, SideWork, GatherArgs, int);
+
 template <int... V>
-hipError_t launch_stage_f64(const FinArgs& A, const BsPts& in, const BsAxes& ax, int nb,
-                            hipStream_t stream, std::integer_sequence<int, V...>) {
-  using K = void (*)(FinArgs, BsPts, BsAxes);
-  static constexpr K kern[] = {k_stage<false, V, double>...};
-  const int per = (ax.periodic[0] ? 1 : 0) | (ax.periodic[1] ? 2 : 0) | (ax.periodic[2] ? 4 : 0);
-  hipLaunchKernelGGL(kern[per], dim3(nb), dim3(2 * kStThreads), 0, stream, A, in, ax);
-  return hipGetLastError();
+StageKernel stage_f64(int per, std::integer_sequence<int, V...>) {
+  static constexpr StageKernel kern[] = {k_stage<false, V, double, double>...};
+  return kern[per];
 }
 
 }  // namespace
 
-hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext) {
+SideWork fil_ride_gather(const Run& r) {
+  SideWork w;
+  w.kind = SideWork::kGather;
+  w.blocks = nblocks(64 * r.ncap, kSideThreads);
+  w.force = r.force;
+  return w;
+}
+
+hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
+                     const SideWork& side) {
   FinArgs A = fin_args(r, stage, first, last, Y, Ynext, 0);
   A.X = nullptr;  // the next stage reads the positions
   const BsPts in{Y, r.ncap, 1, r.nxt, r.prv};
   const int nb = nblocks(r.ncap, kStTargets);
   hipEvent_t b = nullptr;
   time_begin(r, 0, &b);  // timed with the pair sums
-  hipError_t e = hipSuccess;
-  if (r.prec == VLB_F64) {
-    e = launch_stage_f64(A, in, r.bsax, nb, r.stream, std::make_integer_sequence<int, 8>{});
-  } else {
-    auto kern = r.bsax.uniform ? k_stage<true, 1, float> : k_stage<true, 0, float>;
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(2 * kStThreads), 0, r.stream, A, in, r.bsax);
-    e = hipGetLastError();
-  }
+  const BsAxes& ax = r.bsax;
+  const int per = (ax.periodic[0] ? 1 : 0) | (ax.periodic[1] ? 2 : 0) | (ax.periodic[2] ? 4 : 0);
+  StageKernel kern;
+  if (r.prec == VLB_F64)
+    kern = stage_f64(per, std::make_integer_sequence<int, 8>{});
+  else if (r.prec == VLB_F32)
+    kern = ax.uniform ? k_stage<true, 1, float, float> : k_stage<true, 0, float, float>;
+  else
+    kern = ax.uniform ? k_stage<true, 1, float, __half> : k_stage<true, 0, float, __half>;
+  hipLaunchKernelGGL(kern, dim3(nb + side.blocks), dim3(2 * kStThreads), 0, r.stream, A, in, ax,
+                     side, gather_args(r), nb);
   time_end(r, 0, b);
-  return e;
+  return hipGetLastError();
 }
 
 hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
@@ -984,8 +1066,7 @@ template <class FT>
 void launch_gather(Run& r, bool waves) {
   auto kern = waves ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;
   hipLaunchKernelGGL(kern, dim3(nblocks((waves ? 64 : 8) * r.ncap, 256)), dim3(256), 0, r.stream,
-                     r.skeys, r.bins, r.bnext, r.sfrac, r.gpt, r.cnt, r.ncap, spread_geom(r),
-                     r.cells, (FT*)r.force, r.touched);
+                     gather_args(r), r.cnt, r.ncap, spread_geom(r), r.cells, (FT*)r.force);
 }
 
 }  // namespace

@@ -566,8 +566,12 @@ constexpr long long kStagePoints = 1024;
 // 1225 per ten; 2700 points (capacity 4036) 1837 -> 1955.
 constexpr long long kTopoPoints = 1024;
 // Lattice work per step (seconds at 5 TB/s) below which such a run keeps to
-// one stream: a dependency across streams costs 5 to 9 us, twice a step.
-constexpr double kShortLattice = 2e-5;
+// one stream, its stages carrying the lattice work: a dependency across
+// streams costs 5 to 9 us, twice a step, and the carried update gives up
+// block order and occupancy.  Ten steps of 500 points in 96^3 FP32 (45 us):
+// 1170 us on two streams, 1097 on one; 400 points in 128x128x64 (53 us): 1115
+// against 1205; 200 points in 80^3 FP64 (52 us): 946 against 892.
+constexpr double kShortLattice = 5e-5;
 
 // error flag bits in cnt[7]
 constexpr int kFlagCapacity = 1;
@@ -631,8 +635,32 @@ int bs_chunks(long long ncap, int copies);
 // grid coordinates for a next sum).
 hipError_t fil_finalize(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
                         int eval_only);
+// Work that a small run's stage carries in blocks of its own, in place of a
+// launch of its own: the spreading gather, the lattice update or the moments.
+// Each touches nothing that the stage beside it does, and follows the one
+// before it by the order of the launches.
+constexpr int kSideThreads = 512;
+struct SideWork {
+  enum Kind { kNone, kGather, kUpdate, kMoments };
+  int kind = kNone;
+  int parity = 0;
+  int blocks = 0;          // of kSideThreads
+  void* pops = nullptr;
+  void* force = nullptr;
+  void* ub = nullptr;      // moments: the field written
+  int clear = 0;           // moments: clear what the last spreading left
+  int bx = 0, by = 0, parts = 0, items = 0;
+  double scale = 0.0;
+  double* Ps = nullptr;
+};
+bool lbm_can_ride(const Run& r);
+SideWork lbm_ride_update(Run& r);   // (advances the parity)
+SideWork lbm_ride_moments(Run& r);
+hipError_t lbm_moments_after(Run& r);  // what follows the carried moments
+SideWork fil_ride_gather(const Run& r);
 // A whole stage (pair sum and finalize) of a small run in one launch.
-hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext);
+hipError_t fil_stage(Run& r, int stage, int first, int last, const double* Y, double* Ynext,
+                     const SideWork& side);
 hipError_t fil_copy_positions(Run& r, const double* src, double* dst);
 // Point data through the run's pinned memory, in one launch each way: a header
 // of 16 ints, then the data.  export: header n and the latched flags, then k
@@ -647,7 +675,6 @@ hipError_t fil_export(Run& r, const double* const* src, int k, bool links);
 hipError_t fil_import(Run& r, int n);
 // alone: nothing else of the run is in flight.
 hipError_t fil_spread(Run& r, bool alone);
-hipError_t fil_seed(Run& r, long long n);
 
 // swap: compact into the other point arrays and swap them (steps); else
 // compact and copy back (the standalone call)
