@@ -5,6 +5,8 @@
 
 #include "vlb_internal.h"
 
+#include <type_traits>
+
 namespace vlb {
 
 // Points of a sum: component a of point j at Y[a sa + j sj], links (entries
@@ -257,6 +259,80 @@ __device__ __forceinline__ void bs_pair_f64(const BsSrcD& g, BsTgtD& t, bool exc
   t.ax = fma(f, fma(r1y, g.dz, -(r1z * g.dy)), t.ax);
   t.ay = fma(f, fma(r1z, g.dx, -(r1x * g.dz)), t.ay);
   t.az = fma(f, fma(r1x, g.dy, -(r1y * g.dx)), t.az);
+}
+
+// The whole sum for kFewTargets targets by kThreads threads: thread (slice,
+// target) adds every slice-th segment of the staged tiles (kTile records at
+// src) for its target j; the slices are added in FP64 in a fixed tree, to a
+// part per wave and target (red).  n: the points, lim >= n: what may be read;
+// the first tile's loads do not wait for n.
+constexpr int kFewTargets = 8;
+
+template <bool kF32, int kVar, int kThreads, int kTile, class Src>
+__device__ __forceinline__ void bs_few(const BsPts& in, int n, int lim, int tiles, int j,
+                                       const BsAxes& bx, Src* src,
+                                       double (*red)[3][kFewTargets]) {
+  constexpr int kSlices = kThreads / kFewTargets;
+  const int lane = threadIdx.x & 63;
+  const int sl = threadIdx.x / kFewTargets;
+  const int jc = min(j, lim - 1);  // (lanes beyond the points write nothing)
+  double y[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
+  int oc = 0;  // the image copy whose own segments are excluded too
+  if (bx.copies > 1 && (in.nxt[jc] == jc || in.prv[jc] == jc)) oc = bs_own_copy(y, bx);
+  uint32_t xt[3] = {0u, 0u, 0u};
+  BsTgtD td;
+  if constexpr (kF32) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) xt[a] = bs_grid_f32(y[a], bx, a);
+  } else {
+    bs_target_f64<kVar>(y, bx, td);
+  }
+  double v[3] = {0.0, 0.0, 0.0};
+  for (int copy = 0; copy < bx.copies; ++copy) {
+    const int jj = copy == 0 || copy == oc ? jc : -1;
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    td.ax = td.ay = td.az = 0.0;
+    for (int tile = 0; tile == 0 || tile < tiles; ++tile) {
+      const int t0 = tile * kTile;
+#pragma unroll
+      for (int u = 0; u < kTile; u += kThreads) {
+        const int k = t0 + u + threadIdx.x;
+        if (k < lim) {
+          if constexpr (kF32)
+            src[u + threadIdx.x] = bs_stage_f32<kVar != 0, true>(
+                in, nullptr, 0, k, lim, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
+          else
+            src[u + threadIdx.x] = bs_stage_f64<kVar>(in, k, lim, copy, bx);
+        }
+      }
+      __syncthreads();
+      const int cnt = min(kTile, n - t0);
+#pragma unroll 2
+      for (int s = sl; s < cnt; s += kSlices) {
+        const Src g = src[s];
+        const bool ex = t0 + s == jj || g.kn == jj;
+        if constexpr (kF32)
+          bs_pair_f32<kVar != 0>(g, xt[0], xt[1], xt[2], bx.invq_f[0], bx.invq_f[1], bx.invq_f[2],
+                                 ex, fx, fy, fz);
+        else
+          bs_pair_f64<kVar>(g, td, ex, bx.invq_d[0], bx.invq_d[1], bx.invq_d[2]);
+      }
+      __syncthreads();
+    }
+    const double sg = (kF32 ? 1.0 : 0.5) * (double)bx.sign[copy];
+    v[0] += sg * (kF32 ? (double)fx : td.ax);
+    v[1] += sg * (kF32 ? (double)fy : td.ay);
+    v[2] += sg * (kF32 ? (double)fz : td.az);
+  }
+#pragma unroll
+  for (int off = kFewTargets; off < 64; off <<= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] += __shfl_xor(v[a], off);
+  if (lane < kFewTargets)
+    for (int a = 0; a < 3; ++a) red[threadIdx.x >> 6][a][lane] = v[a];
+  __syncthreads();
 }
 
 }  // namespace vlb

@@ -752,9 +752,8 @@ __device__ __forceinline__ void side_work(const SideWork& w, const FinArgs& A,
 // Blocks from `blocks` on do the work it carries (side_work): latency bound
 // as well, it costs nothing beside the stage, where the gather, the update and
 // the moments took 15 us of a ring's 56 us step as launches of their own.
-constexpr int kStTargets = 8;
+constexpr int kStTargets = kFewTargets;
 constexpr int kStThreads = 256;  // threads of the sum
-constexpr int kStSlices = kStThreads / kStTargets;
 
 template <bool kF32, int kVar, class UT, class S>
 __global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx, SideWork side,
@@ -793,63 +792,8 @@ __global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx, S
     return;
   }
 
-  const int tl = threadIdx.x % kStTargets, sl = threadIdx.x / kStTargets;
-  const int j = j0 + tl;
-  const int jc = min(j, nc - 1);  // (lanes beyond the points write nothing)
-  double y[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) y[a] = in.Y[a * in.sa + jc * in.sj];
-  int oc = 0;  // the image copy whose own segments are excluded too
-  if (bx.copies > 1 && (in.nxt[jc] == jc || in.prv[jc] == jc)) oc = bs_own_copy(y, bx);
-  uint32_t xt[3] = {0u, 0u, 0u};
-  BsTgtD td;
-  if constexpr (kF32) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) xt[a] = bs_grid_f32(y[a], bx, a);
-  } else {
-    bs_target_f64<kVar>(y, bx, td);
-  }
-  double v[3] = {0.0, 0.0, 0.0};
-  for (int copy = 0; copy < bx.copies; ++copy) {
-    const int jj = copy == 0 || copy == oc ? jc : -1;
-    float fx = 0.f, fy = 0.f, fz = 0.f;
-    td.ax = td.ay = td.az = 0.0;
-    for (int tile = 0; tile == 0 || tile < tiles; ++tile) {
-      const int t0 = tile * kStThreads;
-      const int k = t0 + threadIdx.x;
-      if (k < nc) {
-        if constexpr (kF32)
-          src[threadIdx.x] = bs_stage_f32<kVar != 0, true>(
-              in, nullptr, 0, k, nc, copy, bx.invq_f[0], bx.invq_f[1], bx.invq_f[2], bx);
-        else
-          src[threadIdx.x] = bs_stage_f64<kVar>(in, k, nc, copy, bx);
-      }
-      __syncthreads();
-      const int cnt = min(kStThreads, n - t0);
-#pragma unroll 2
-      for (int s = sl; s < cnt; s += kStSlices) {
-        const Src g = src[s];
-        const bool ex = t0 + s == jj || g.kn == jj;
-        if constexpr (kF32)
-          bs_pair_f32<kVar != 0>(g, xt[0], xt[1], xt[2], bx.invq_f[0], bx.invq_f[1], bx.invq_f[2],
-                                 ex, fx, fy, fz);
-        else
-          bs_pair_f64<kVar>(g, td, ex, bx.invq_d[0], bx.invq_d[1], bx.invq_d[2]);
-      }
-      __syncthreads();
-    }
-    const double sg = (kF32 ? 1.0 : 0.5) * (double)bx.sign[copy];
-    v[0] += sg * (kF32 ? (double)fx : td.ax);
-    v[1] += sg * (kF32 ? (double)fy : td.ay);
-    v[2] += sg * (kF32 ? (double)fz : td.az);
-  }
-#pragma unroll
-  for (int off = kStTargets; off < 64; off <<= 1)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) v[a] += __shfl_xor(v[a], off);
-  if (lane < kStTargets)
-    for (int a = 0; a < 3; ++a) red[grp][a][lane] = v[a];
-  __syncthreads();
+  const int j = j0 + (int)threadIdx.x % kStTargets;
+  bs_few<kF32, kVar, kStThreads, kStThreads>(in, n, nc, tiles, j, bx, src, red);
   if (threadIdx.x >= kStTargets || j >= n) return;
   double vs[3];
   for (int a = 0; a < 3; ++a)

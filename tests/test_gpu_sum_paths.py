@@ -1,7 +1,8 @@
 """The stand-alone sum over every route it can take: each set of closed axes
 (the FP64 kernel is specialised on it), point counts on both sides of the
-count from which it takes two targets per lane and of the one up to which
-the FP32 sum reads positions, ragged last blocks and tiles.  Against the oracle's sum at sampled targets, in FP64."""
+count from which it takes two targets per lane, of the one up to which the
+FP32 sum reads positions and of the one up to which it is one launch, ragged
+last blocks and tiles.  Against the oracle's sum at sampled targets, in FP64."""
 
 import numpy as np
 import pytest
@@ -57,13 +58,15 @@ def _check(n, dims, walls, precision):
     assert err <= TOL[precision]
 
 
+@pytest.mark.parametrize("n", [700, 1300])   # one launch, chunks
 @pytest.mark.parametrize("mask", range(8))
-def test_every_set_of_closed_axes(mask):
+def test_every_set_of_closed_axes(mask, n):
     walls = tuple(bool((mask >> a) & 1) for a in range(3))
-    _check(700, (40, 36, 48), walls, "f64")
+    _check(n, (40, 36, 48), walls, "f64")
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-@pytest.mark.parametrize("n", [3, 63, 65, 257, 1023, 4096, 4097, 16383, 16385])
+@pytest.mark.parametrize("n", [3, 63, 65, 257, 1023, 1025, 1280, 1281, 4096, 4097, 16383,
+                               16385])
 def test_point_counts(n, precision):
     _check(n, (64, 64, 64), (False, True, False), precision)
