@@ -6,7 +6,8 @@
  * plus a set of closed vortex filaments (Sec. II.A), coupled through the
  * mutual-friction force (Sec. II.B).  All state lives in ONE caller-owned
  * block of device memory (the workspace); the library never allocates
- * device memory.  Device work is ordered on ONE caller-owned HIP stream,
+ * device memory (a run owns up to 1 MiB of pinned host memory for the
+ * transfers of its points).  Device work is ordered on ONE caller-owned HIP stream,
  * given at creation: inside vlb_step and a graph, the lattice part of a
  * step runs on a second, library-owned stream (default priority) forked
  * from the caller's stream at the start of the call and joined back to it
@@ -391,7 +392,7 @@ int vlb_biot_savart(const vlb_bs_desc* d, int64_t n_pts, const double* xyz_dev,
 /* Allocation-free vlb_biot_savart, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid it): the same sum, kernels and bits as vlb_biot_savart, with its
- * scratch (grid coordinates, links, chunk partials) in a fixed device array
+ * scratch (grid coordinates, chunk partials) in a fixed device array
  * of the library (about 4.5 MB per GPU, held until the process ends)
  * instead of a caller workspace.  Arguments as vlb_biot_savart; call with
  * the GPU of hip_stream current.  n_pts is limited to 16384 (VLB_EINVAL

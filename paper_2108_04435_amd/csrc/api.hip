@@ -64,8 +64,6 @@ struct Bump {
   }
 };
 
-size_t elt_size(int prec) { return prec == VLB_F64 ? 8 : (prec == VLB_F32 ? 4 : 2); }
-
 int check_desc(const vlb_lattice_desc* lat, const vlb_vortex_desc* vor, std::string& msg) {
   if (!lat || !vor) { msg = "null descriptor"; return VLB_EINVAL; }
   if (lat->nx < 4 || lat->ny < 4 || lat->nz < 4) { msg = "every lattice dimension must be >= 4"; return VLB_EINVAL; }
@@ -781,8 +779,7 @@ int vlb_write_state(vlb_run* h, const void* pops_dev, int64_t step) {
   if (!pops_dev) return fail(h, VLB_EINVAL, "pops is NULL");
   if (step < 0) return fail(h, VLB_EINVAL, "step must be >= 0");
   Run& r = h->r;
-  HIP_OR_FAIL(h, hipMemcpyAsync(r.pops, pops_dev, 19 * (size_t)r.cells * elt_size(r.prec),
-                                hipMemcpyDeviceToDevice, r.stream));
+  HIP_OR_FAIL(h, lbm_write_state(r, pops_dev));
   HIP_OR_FAIL(h, hipMemsetAsync(r.force, 0, 3 * r.cells * (r.prec == VLB_F64 ? 8 : 4), r.stream));
   HIP_OR_FAIL(h, hipMemsetAsync(r.cnt + 1, 0, sizeof(int32_t), r.stream));
   HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));

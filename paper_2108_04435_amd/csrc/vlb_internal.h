@@ -437,6 +437,9 @@ struct BsAxes {
 };
 
 // Workspace-resident state of a run.
+// Bytes of a stored population.
+inline size_t elt_size(int prec) { return prec == VLB_F64 ? 8 : (prec == VLB_F32 ? 4 : 2); }
+
 struct Run {
   vlb_lattice_desc lat;
   vlb_vortex_desc vor;
@@ -584,6 +587,7 @@ hipError_t lbm_step(Run& r);
 hipError_t lbm_read_fields(Run& r, double* rho, double* u);
 hipError_t lbm_read_pops(Run& r, double* f);
 hipError_t lbm_read_state(Run& r, void* out);
+hipError_t lbm_write_state(Run& r, const void* in);
 hipError_t lbm_read_force(Run& r, double* out);
 hipError_t lbm_moments(Run& r);
 size_t lbm_mb_doubles(const Run& r);  // size of mbP
