@@ -820,8 +820,11 @@ __global__ __launch_bounds__(1024) void k_rc_match(MatchArgs A) { rc_match(A); }
 
 // ---- the same phases for few points (kTopoPoints) by one workgroup: its
 // barriers stand in for the kernels' ends, and the flags are ranked by the
-// block itself.  Rounds of kTopoThreads points per phase.
-constexpr int kTopoThreads = 1024;
+// block itself.  A thread per point: the smallest of 256, 512 and 1024 threads
+// that holds the capacity (a barrier of fewer waves is shorter: 20 steps of a
+// 64-point ring 876 us with 1024, 845 with 256; ten steps of 300 points 751
+// with 1024, 736 with 512, 758 with 256), 1024 with reconnection, whose
+// matching takes them.
 
 struct TopoArgs {
   TopoGeom tg;
@@ -831,10 +834,7 @@ struct TopoArgs {
   int32_t* prv;
   int32_t* cnt;
   long long nc;
-  int32_t* del;
   int remesh, match, finish;  // phases of this launch
-  uint64_t* mask;
-  int32_t* pre;
   SmallArgs small;   // the small-loop pass of this launch
   MatchArgs m;
   double* pos_t;
@@ -854,46 +854,90 @@ __device__ inline void block_flags(int j, int n, bool flag, uint64_t* mask, int3
   }
 }
 
-__global__ __launch_bounds__(kTopoThreads) void k_topo_block(TopoArgs A) {
+// The points, links, flags, ranks and counters live in LDS from one load of
+// all slots (which waits for no count) to the compaction; what a later launch
+// reads is written back.  What bounds it: latency.  With every phase reading
+// global memory again 20 steps of a 64-point ring took 902
+// us, 876 so.
+template <int B>
+__global__ __launch_bounds__(B) void k_topo_block(TopoArgs A) {
+  __shared__ double pos[3 * kTopoPoints];
+  __shared__ int32_t nxt[kTopoPoints], prv[kTopoPoints], del[kTopoPoints];
+  __shared__ uint64_t mask[kTopoPoints / 64];
+  __shared__ int32_t pre[kTopoPoints / 64];
+  __shared__ int32_t cnt[16];
   const int t = threadIdx.x;
-  int32_t* cnt = A.cnt;
-  const int n = cnt[0];
-  if (!A.match && t == 0) cnt[2] = cnt[3] = cnt[4] = cnt[5] = cnt[6] = 0;
+  const int nc = (int)A.nc;
+  if constexpr (B == 1024)
+    if (A.match) {
+      rc_match(A.m);  // (links in global memory)
+      __syncthreads();
+    }
+  if (t < 16) cnt[t] = (!A.match && t >= 2 && t <= 6) ? 0 : A.cnt[t];
+  for (int j = t; j < nc; j += B) {
+    nxt[j] = A.nxt[j];
+    prv[j] = A.prv[j];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) pos[a * nc + j] = A.pos[(long long)a * nc + j];
+  }
   __syncthreads();
+  const int n = cnt[0];
   if (A.remesh) {
-    for (int b = 0; b < n; b += kTopoThreads)
-      rm_mark_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.mn2, A.mx2, A.del);
+    for (int b = 0; b < n; b += B)
+      rm_mark_point(b + t, pos, nxt, prv, cnt, nc, A.tg, A.mn2, A.mx2, del);
     __syncthreads();
-    for (int b = 0; b < n; b += kTopoThreads) {
-      const bool ins = rm_link_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.mx2, A.del);
-      block_flags(b + t, n, ins, A.mask, A.pre);
+    for (int b = 0; b < n; b += B) {
+      const bool ins = rm_link_point(b + t, pos, nxt, prv, cnt, nc, A.tg, A.mx2, del);
+      block_flags(b + t, n, ins, mask, pre);
     }
     __syncthreads();
-    block_scan_inplace<kTopoThreads>(A.pre, (n + 63) / 64, cnt + 2);
-    __syncthreads();
+    block_scan_inplace<B>(pre, (n + 63) / 64, cnt + 2);
     if (n == 0 && t == 0) cnt[9] = 0;
-    for (int b = 0; b < n; b += kTopoThreads)
-      rm_insert_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.tg, A.del, A.mask, A.pre);
+    __syncthreads();
+    for (int b = 0; b < n; b += B)
+      rm_insert_point(b + t, pos, nxt, prv, cnt, nc, A.tg, del, mask, pre);
     __syncthreads();
   }
-  if (A.match) {
-    rc_match(A.m);
+  SmallArgs small = A.small;
+  small.pos = pos;
+  small.nxt = nxt;
+  small.prv = prv;
+  small.cnt = cnt;
+  if (small.dead_in) small.dead_in = del;
+  const int bound = small.bound9 ? cnt[9] : n;
+  if (!small.bound9 && bound == 0 && t == 0) cnt[9] = 0;
+  for (int b = 0; b < bound; b += B) {
+    const bool alive = small_pass_point(b + t, small);
+    if (A.finish) block_flags(b + t, bound, alive, mask, pre);
+  }
+  __syncthreads();
+  if (A.finish) {
+    block_scan_inplace<B>(pre, (bound + 63) / 64, cnt + 8);
     __syncthreads();
+    if (bound == 0 && t == 0) cnt[0] = cnt[8];
+    for (int b = 0; b < bound; b += B)
+      compact_point(b + t, pos, nxt, prv, cnt, nc, mask, pre, A.pos_t, A.nxt_t, A.prv_t, 1, A.X,
+                    A.ax);
+  } else {
+    for (int j = t; j < bound; j += B) {
+      A.nxt[j] = nxt[j];
+      A.prv[j] = prv[j];
+      if (j >= n)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) A.pos[(long long)a * nc + j] = pos[a * nc + j];
+    }
   }
-  const int bound = A.small.bound9 ? cnt[9] : n;
-  if (!A.small.bound9 && bound == 0 && t == 0) cnt[9] = 0;
-  for (int b = 0; b < bound; b += kTopoThreads) {
-    const bool alive = small_pass_point(b + t, A.small);
-    if (A.finish) block_flags(b + t, bound, alive, A.mask, A.pre);
-  }
-  if (!A.finish) return;
   __syncthreads();
-  block_scan_inplace<kTopoThreads>(A.pre, (bound + 63) / 64, cnt + 8);
-  __syncthreads();
-  if (bound == 0 && t == 0) cnt[0] = cnt[8];
-  for (int b = 0; b < bound; b += kTopoThreads)
-    compact_point(b + t, A.pos, A.nxt, A.prv, cnt, A.nc, A.mask, A.pre, A.pos_t, A.nxt_t, A.prv_t,
-                  1, A.X, A.ax);
+  // the counters this kernel owns (others are written beside it)
+  if (t < 10 && t != 1 && t != 7 && !(A.match && (t == 4 || t == 6))) A.cnt[t] = cnt[t];
+  if (t == 7 && cnt[7]) atomicOr(&A.cnt[7], cnt[7]);
+}
+
+void launch_topo_block(const TopoArgs& T, const Run& r) {
+  const int threads = r.vor.reconnect || r.ncap > 512 ? 1024 : (r.ncap > 256 ? 512 : 256);
+  auto kern = threads == 1024 ? k_topo_block<1024>
+                              : (threads == 512 ? k_topo_block<512> : k_topo_block<256>);
+  hipLaunchKernelGGL(kern, dim3(1), dim3(threads), 0, r.stream, T);
 }
 
 inline int nb_of(long long n, int b) { return (int)((n + b - 1) / b); }
@@ -969,10 +1013,7 @@ hipError_t topo_update(Run& r, bool swap) {
   T.prv = r.prv;
   T.cnt = r.cnt;
   T.nc = r.ncap;
-  T.del = del;
   T.remesh = r.vor.remesh;
-  T.mask = r.wmask;
-  T.pre = r.wpre;
   T.pos_t = r.pos_t;
   T.nxt_t = r.nxt_t;
   T.prv_t = r.prv_t;
@@ -989,7 +1030,7 @@ hipError_t topo_update(Run& r, bool swap) {
     A.rc_mode = 1;
     T.small = A;
     if (block)
-      hipLaunchKernelGGL(k_topo_block, dim3(1), dim3(kTopoThreads), 0, r.stream, T);
+      launch_topo_block(T, r);
     else
       hipLaunchKernelGGL(k_small_pass, dim3(nb), dim3(kBlock), 0, r.stream, A);
     const double d2max = r.vor.reconnect_dist * r.vor.reconnect_dist;
@@ -1021,7 +1062,7 @@ hipError_t topo_update(Run& r, bool swap) {
   if (swap) {
     T.finish = 1;
     if (block)
-      hipLaunchKernelGGL(k_topo_block, dim3(1), dim3(kTopoThreads), 0, r.stream, T);
+      launch_topo_block(T, r);
     else
       hipLaunchKernelGGL(k_compact_scatter, dim3(nb), dim3(kBlock), 0, r.stream, r.pos, r.nxt,
                          r.prv, r.cnt, r.ncap, r.wmask, r.wpre, r.pos_t, r.nxt_t, r.prv_t, 1, X,

@@ -53,6 +53,29 @@ def test_block_equals_grid(n_rings, reconnect, remesh):
         np.testing.assert_array_equal(p0, p1)
 
 
+@pytest.mark.parametrize("remesh", [True, False])
+@pytest.mark.parametrize("cap", [256, 257, 512, 513])   # 256, 512, 512, 1024 threads
+def test_block_sizes(cap, remesh):
+    """Walls on two axes: nine image copies, so that no capacity here takes
+    the fused stages.  The sum's chunk count depends on the capacity (3 here, 4
+    at 1025), so that the line velocities differ in the order of their parts:
+    1e-15 of velocities of order one, and positions of up to 48 by a few ulp
+    (7e-15) per step; links are equal, positions to 1e-12 after the first step."""
+    dims, walls = (48, 40, 44), (True, True, False)
+    ring = wl.ring((24.0, 20.0, 22.0), 7.0, (0.3, 0.2, 1.0), 50)
+    a, b = wl.ring((12.0, 30.0, 12.0), 0.55, (0, 0, 1), 5), wl.ring((12.0, 10.0, 9.0), 3.0, (0, 1, 0), 70)
+    pos, nxt = wl.concat_loops([ring, a, b])
+    rho, u = wl.velocity_field(3, dims, (0.0, 0.0, 0.02), 1e-3)
+    cfg = dict(lattice=wl.lattice_preset(*dims, walls=walls, precision="f64"),
+               vortex=wl.vortex_preset(remesh=remesh, kappa=0.3, wall_images=True),
+               rho=rho, u=u, pos=pos, nxt=nxt)
+    say("topology sizes", cap, remesh, pos.shape[0], "points")
+    a, b = _steps(cfg, cap, 5), _steps(cfg, 1025, 5)
+    np.testing.assert_allclose(a[0][0], b[0][0], rtol=0, atol=1e-12)
+    for (_, k0), (_, k1) in zip(a, b):
+        np.testing.assert_array_equal(k0, k1)
+
+
 def test_block_to_no_points():
     dims = (24, 24, 24)
     pos, nxt = wl.ring((12.0, 12.0, 12.0), 0.5, (0, 0, 1), 4)   # shorter than a loop may be
