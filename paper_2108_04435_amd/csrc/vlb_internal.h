@@ -564,10 +564,11 @@ struct Run {
 // launches.  Twenty graph steps of a ring of 64 points (capacity 345): 1791
 // -> 1622 us; 500 points (956) level; 1300 points (2076) 8% slower.
 constexpr long long kStagePoints = 1024;
-// Points (capacity) up to which a step's topology runs in one workgroup: a
-// ring of 64 points 1442 -> 1360 us per twenty steps, 500 points 1262 ->
-// 1225 per ten; 2700 points (capacity 4036) 1837 -> 1955.
-constexpr long long kTopoPoints = 1024;
+// Points (capacity) up to which a step's topology runs in one workgroup, from
+// LDS: against the kernels of larger runs 1100 points (capacity 1640) 1161 ->
+// 1098 us per ten steps with reconnection, 998 -> 903 without; 2700 points
+// (capacity 4036) 1705 -> 1721 and 1524 -> 1470.
+constexpr long long kTopoPoints = 2048;
 // Lattice work per step (seconds at 5 TB/s) below which such a run keeps to
 // one stream, its stages carrying the lattice work: a dependency across
 // streams costs 5 to 9 us, twice a step, and the carried update gives up

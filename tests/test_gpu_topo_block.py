@@ -1,4 +1,4 @@
-"""The topology of a step in one workgroup (runs of at most 1024 points of
+"""The topology of a step in one workgroup (runs of at most 2048 points of
 capacity) against the kernels of larger runs: the same runs at a capacity on
 either side of the limit give the same filaments, bit for bit, over steps
 with remeshing, reconnection and small-loop removal, down to no points.  (With
@@ -48,17 +48,17 @@ def test_block_equals_grid(n_rings, reconnect, remesh):
                                        wall_images=True),
                rho=rho, u=u, pos=pos, nxt=nxt)
     say("topology", n_rings, reconnect, remesh, pos.shape[0], "points")
-    for (p0, k0), (p1, k1) in zip(_steps(cfg, 1024, 5), _steps(cfg, 1025, 5)):
+    for (p0, k0), (p1, k1) in zip(_steps(cfg, 2048, 5), _steps(cfg, 2049, 5)):
         np.testing.assert_array_equal(k0, k1)
         np.testing.assert_array_equal(p0, p1)
 
 
 @pytest.mark.parametrize("remesh", [True, False])
-@pytest.mark.parametrize("cap", [256, 257, 512, 513])   # 256, 512, 512, 1024 threads
+@pytest.mark.parametrize("cap", [256, 257, 512, 513, 1400])   # 256, 512, 512, 1024, 1024 threads
 def test_block_sizes(cap, remesh):
     """Walls on two axes: nine image copies, so that no capacity here takes
-    the fused stages.  The sum's chunk count depends on the capacity (3 here, 4
-    at 1025), so that the line velocities differ in the order of their parts:
+    the fused stages.  The sum's chunk count depends on the capacity (3 here, 8
+    at 2049), so that the line velocities differ in the order of their parts:
     1e-15 of velocities of order one, and positions of up to 48 by a few ulp
     (7e-15) per step; links are equal, positions to 1e-12 after the first step."""
     dims, walls = (48, 40, 44), (True, True, False)
@@ -70,7 +70,7 @@ def test_block_sizes(cap, remesh):
                vortex=wl.vortex_preset(remesh=remesh, kappa=0.3, wall_images=True),
                rho=rho, u=u, pos=pos, nxt=nxt)
     say("topology sizes", cap, remesh, pos.shape[0], "points")
-    a, b = _steps(cfg, cap, 5), _steps(cfg, 1025, 5)
+    a, b = _steps(cfg, cap, 5), _steps(cfg, 2049, 5)
     np.testing.assert_allclose(a[0][0], b[0][0], rtol=0, atol=1e-12)
     for (_, k0), (_, k1) in zip(a, b):
         np.testing.assert_array_equal(k0, k1)
@@ -82,6 +82,6 @@ def test_block_to_no_points():
     rho, u = wl.velocity_field(3, dims, (0.0, 0.0, 0.0), 0.0)
     cfg = dict(lattice=wl.lattice_preset(*dims, precision="f64"),
                vortex=wl.vortex_preset(reconnect=True), rho=rho, u=u, pos=pos, nxt=nxt)
-    for cap in (64, 1024, 1025):
+    for cap in (64, 512, 1024, 2048, 2049):
         out = _steps(cfg, cap, 3)
         assert [p.shape[0] for p, _ in out] == [0, 0, 0]
