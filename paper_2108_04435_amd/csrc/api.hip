@@ -214,7 +214,6 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
   // spreading bins: lower stencil corner, n (+1 on wall axes) per axis
   const unsigned long long ext = (unsigned long long)(n[0] + g.wall[0]) * (n[1] + g.wall[1]) * (n[2] + g.wall[2]);
   r.nbins_table = (long long)ext;
-  r.small = r.vor.ff_cell == 0 && r.ncap * r.bsax.copies <= kStagePoints;
   // Which part of a step is the longer one, by its work at the rates they
   // reach: pairs of the Biot-Savart sums (1.5e12 per second in FP32, half of
   // that in FP64; with the far field 20 ns per point and sum) against the
@@ -230,7 +229,10 @@ void init_run(Run& r, const vlb_lattice_desc* lat, const vlb_vortex_desc* vor) {
                            : sums * nn * nn * r.bsax.copies / (r.prec == VLB_F64 ? 0.75e12 : 1.5e12);
     const double latt = (double)r.cells * (57.0 * elt_size(r.prec) + (r.prec == VLB_F64 ? 48 : 24)) / 5e12;
     r.narrow_steps = fil > latt;
-    r.one_stream = r.small && latt < kShortLattice;
+    const bool brief = latt < kShortLattice;
+    r.small = r.vor.ff_cell == 0 &&
+              r.ncap * r.bsax.copies <= (brief ? kStagePointsOne : kStagePoints);
+    r.one_stream = r.small && brief;
   }
   // reconnection bins of edge >= reconnect distance
   if (vor->reconnect) {

@@ -564,6 +564,11 @@ struct Run {
 // launches.  Twenty graph steps of a ring of 64 points (capacity 345): 1791
 // -> 1622 us; 500 points (956) level; 1300 points (2076) 8% slower.
 constexpr long long kStagePoints = 1024;
+// The same for runs on one stream, whose stages carry the lattice work too: 750
+// points (capacity 1143) in 48^3 FP32 996 -> 947 us per ten steps, 900 in 64^3
+// FP64 973 -> 966, 1400 (capacity 2080) level; beside a longer lattice 900
+// points in 128^3 took 1772 instead of 1666.
+constexpr long long kStagePointsOne = 1536;
 // Points (capacity) up to which a step's topology runs in one workgroup, from
 // LDS: against the kernels of larger runs 1100 points (capacity 1640) 1161 ->
 // 1098 us per ten steps with reconnection, 998 -> 903 without; 2700 points

@@ -18,11 +18,11 @@ if not torch.cuda.is_available():
 import paper_2108_04435_amd as vlb  # noqa: E402
 
 
-def _end(dims, walls, precision, vortex, timed, calls):
+def _end(dims, walls, precision, vortex, timed, calls, cap):
     lattice = wl.lattice_preset(*dims, walls=walls, precision=precision)
     pos, nxt = wl.random_rings(5, 3, 2.0, 6.0, dims, walls, 0.8)
     rho, u = wl.velocity_field(3, dims, (0.0, 0.005, 0.02), 1e-3)
-    run = vlb.Run(lattice, wl.vortex_preset(**vortex), n_cap=300)
+    run = vlb.Run(lattice, wl.vortex_preset(**vortex), n_cap=cap)
     run.write_fields(rho, u)
     run.seed(pos, nxt)
     if timed:
@@ -44,12 +44,13 @@ def _end(dims, walls, precision, vortex, timed, calls):
     dict(), dict(mass_balance=True), dict(mass_balance=True, mass_balance_axis=0),
     dict(rk_stages=2, mass_balance=True), dict(rk_stages=1), dict(rk_stages=2, vfm_substeps=3),
     dict(coupling=False)])
-def test_carried_equals_launched(dims, walls, precision, vortex):
+@pytest.mark.parametrize("cap", [300, 1500])
+def test_carried_equals_launched(dims, walls, precision, vortex, cap):
     axis = vortex.get("mass_balance_axis", 2)
     if vortex.get("mass_balance") and walls[axis]:
         pytest.skip("the flow axis is periodic")
-    say("carry", dims, walls, precision, vortex)
+    say("carry", dims, walls, precision, vortex, cap)
     calls = (1, 2, 4)
-    for a, b in zip(_end(dims, walls, precision, vortex, False, calls),
-                    _end(dims, walls, precision, vortex, True, calls)):
+    for a, b in zip(_end(dims, walls, precision, vortex, False, calls, cap),
+                    _end(dims, walls, precision, vortex, True, calls, cap)):
         np.testing.assert_array_equal(a, b)
