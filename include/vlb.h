@@ -7,7 +7,7 @@
  * mutual-friction force (Sec. II.B).  All state lives in ONE caller-owned
  * block of device memory (the workspace); the library never allocates
  * device memory (a run owns up to 1 MiB of pinned host memory for the
- * transfers of its points).  Device work is ordered on ONE caller-owned HIP stream,
+ * transfers of its points, the process one page for flags).  Device work is ordered on ONE caller-owned HIP stream,
  * given at creation: inside vlb_step and a graph, the lattice part of a
  * step runs on a second, library-owned stream (default priority) forked
  * from the caller's stream at the start of the call and joined back to it

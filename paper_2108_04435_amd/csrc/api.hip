@@ -102,7 +102,45 @@ int check_desc(const vlb_lattice_desc* lat, const vlb_vortex_desc* vor, std::str
   return VLB_OK;
 }
 
+// One pinned page of the process, in slots of 64 bytes that runs take at
+// creation and give back: a flag read into it takes 14 us less than into other
+// memory, and pinning a page for each run would take 35 of its creation.  Runs
+// beyond the 64 slots read into ordinary memory.
+struct FlagPage {
+  std::mutex m;
+  char* page = nullptr;
+  uint64_t used = 0;
+};
+
+FlagPage& flag_page() {
+  static FlagPage p;
+  return p;
+}
+
+int32_t* take_flag_slot() {
+  FlagPage& p = flag_page();
+  std::lock_guard<std::mutex> lock(p.m);
+  if (!p.page && hipHostMalloc((void**)&p.page, 4096, hipHostMallocPortable) != hipSuccess) {
+    p.page = nullptr;
+    (void)hipGetLastError();  // the run does without
+    return nullptr;
+  }
+  if (p.used == ~0ull) return nullptr;
+  const int i = __builtin_ctzll(~p.used);
+  p.used |= 1ull << i;
+  return (int32_t*)(p.page + 64 * i);
+}
+
+void give_flag_slot(int32_t* s) {
+  if (!s) return;
+  FlagPage& p = flag_page();
+  std::lock_guard<std::mutex> lock(p.m);
+  p.used &= ~(1ull << (((char*)s - p.page) / 64));
+}
+
 void release_streams(Run& r) {
+  give_flag_slot(r.flag);
+  r.flag = nullptr;
   hipEvent_t* evs[] = {&r.ev_fork, &r.ev_mom, &r.ev_fin1, &r.ev_join};
   for (hipEvent_t* ev : evs)
     if (*ev) {
@@ -343,9 +381,20 @@ int report(vlb_run* h, int32_t flags) {
   return VLB_OK;
 }
 
+// The run's pinned memory for its points, from the first call that moves them.
+int pin_host(vlb_run* h) {
+  Run& r = h->r;
+  if (r.host) return VLB_OK;
+  r.host_bytes = host_io_need(r.ncap, 4, 0);
+  if (r.host_bytes > kHostIoBytes) r.host_bytes = kHostIoBytes;
+  HIP_OR_FAIL(h, hipHostMalloc((void**)&r.host, r.host_bytes));
+  return VLB_OK;
+}
+
 int latched(vlb_run* h) {
   Run& r = h->r;
-  int32_t* flags = (int32_t*)r.host;
+  int32_t own = 0;
+  int32_t* flags = r.flag ? r.flag : &own;
   HIP_OR_FAIL(h, hipMemcpyAsync(flags, r.cnt + 7, sizeof(int32_t), hipMemcpyDeviceToHost, r.stream));
   HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));
   return report(h, *flags);
@@ -371,6 +420,8 @@ int copy_soa_to_host(vlb_run* h, const double* dev_soa, int n, double* host_aos)
 int fetch(vlb_run* h, const double* const* src, double* const* dst, int k, int32_t* next,
           int64_t cap, int64_t* n_pts) {
   Run& r = h->r;
+  int c = pin_host(h);
+  if (c != VLB_OK) return c;
   HIP_OR_FAIL(h, fil_export(r, src, k, next != nullptr));
   HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));
   const int32_t* head = (const int32_t*)r.host;
@@ -383,7 +434,7 @@ int fetch(vlb_run* h, const double* const* src, double* const* dst, int k, int32
     if (next) memcpy(next, p, 4 * (size_t)n);
   } else {
     for (int m = 0; m < k; ++m) {
-      const int c = copy_soa_to_host(h, src[m], n, dst[m]);
+      c = copy_soa_to_host(h, src[m], n, dst[m]);
       if (c != VLB_OK) return c;
     }
     if (next) {
@@ -430,11 +481,8 @@ int vlb_create_lattice(const vlb_lattice_desc* lat, const vlb_vortex_desc* vor, 
   layout(r, r.ws);
   r.stream = (hipStream_t)hip_stream;
   hipError_t e = hipGetDevice(&r.device);
+  if (e == hipSuccess) r.flag = take_flag_slot();
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&r.side, hipStreamNonBlocking);
-  // (pinning a page takes time at creation: no more than the points can fill)
-  r.host_bytes = host_io_need(r.ncap, 4, 0);
-  if (r.host_bytes > kHostIoBytes) r.host_bytes = kHostIoBytes;
-  if (e == hipSuccess) e = hipHostMalloc((void**)&r.host, r.host_bytes);
   hipEvent_t* evs[] = {&r.ev_fork, &r.ev_mom, &r.ev_fin1, &r.ev_join};
   for (hipEvent_t* ev : evs)
     if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
@@ -479,6 +527,8 @@ int vlb_seed_vortices(vlb_run* h, int64_t n_pts, const double* xyz, const int32_
   if (n_pts < 0 || n_pts > r.ncap) return fail(h, VLB_EINVAL, "n_pts must be in [0, n_cap]");
   if (n_pts > 0 && (!xyz || !next)) return fail(h, VLB_EINVAL, "xyz and next are required");
   const int n = (int)n_pts;
+  const int pc = pin_host(h);
+  if (pc != VLB_OK) return pc;
   // links: at most one predecessor besides itself per point; a point that
   // links to itself is the last point of an open line, one that no other
   // point links to is the first (it keeps itself as its predecessor)

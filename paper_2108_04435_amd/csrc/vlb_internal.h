@@ -448,6 +448,7 @@ struct Run {
   hipEvent_t ev_fork = nullptr, ev_mom = nullptr, ev_fin1 = nullptr, ev_join = nullptr;
   char* host = nullptr;  // host_bytes of pinned memory for transfers, one at a time
   size_t host_bytes = 0;
+  int32_t* flag = nullptr;  // pinned slot for the latched flags (or null)
   int device = 0;
   char* ws = nullptr;
   uint64_t ws_bytes = 0;

@@ -67,3 +67,26 @@ def test_line_velocity_arrays(n):
         assert np.abs(one).max() > 0.0
         np.testing.assert_array_equal(out[k], one)
     run.close()
+
+
+def test_more_runs_than_flag_slots():
+    """Seventy runs at once (the process keeps 64 pinned slots for flags), a
+    non-finite velocity latched by the last of them, and slots given back."""
+    dims = (8, 8, 8)
+    for _ in range(2):
+        runs = [vlb.Run(wl.lattice_preset(*dims, precision="f32"), wl.vortex_preset(), 16)
+                for _ in range(70)]
+        for run in runs:
+            run.step(1)
+            run.sync()
+        pos = np.array([[2.0, 2.0, 2.0], [3.0, 2.0, 2.0], [3.0, 3.0, 2.0], [2.0, 3.0, 2.0]])
+        run = runs[-1]
+        run.write_fields(np.full(dims, np.nan), np.full((3,) + dims, np.nan))
+        run.seed(pos, np.array([1, 2, 3, 0]))
+        with pytest.raises(RuntimeError, match="non-finite"):
+            run.step(1)
+            run.sync()
+        run.seed(pos, np.array([1, 2, 3, 0]))
+        assert run.n_points() == 4
+        for run in runs:
+            run.close()
