@@ -176,10 +176,10 @@ size_t layout(Run& r, char* base) {
   r.seg = (double*)B.take(3 * (size_t)nc * sizeof(double));
   r.fric = (double*)B.take((2 * (size_t)r.geom.nz + 1) * sizeof(double));
   r.touched = (int32_t*)B.take(8 * nc * sizeof(int32_t));
-  double** dbufs[] = {&r.pos, &r.ya, &r.yb, &r.ksum, &r.vs1, &r.vn1, &r.sd1, &r.gpt, &r.pos_t, &r.stage, &r.sfrac};
+  double** dbufs[] = {&r.pos, &r.ya, &r.yb, &r.ksum, &r.vs1, &r.vn1, &r.sd1, &r.gpt, &r.pos_t, &r.sfrac};
   for (double** p : dbufs) *p = (double*)B.take(3 * nc * sizeof(double));
-  int32_t** ibufs[] = {&r.nxt, &r.prv, &r.nxt_t, &r.prv_t, &r.stage_i, &r.flag_a, &r.flag_b,
-                       &r.scan_a, &r.scan_b, &r.used};
+  int32_t** ibufs[] = {&r.nxt, &r.prv, &r.nxt_t, &r.prv_t, &r.flag_a, &r.flag_b,
+                       &r.scan_a, &r.used};
   for (int32_t** p : ibufs) *p = (int32_t*)B.take((nc + 1) * sizeof(int32_t));
   const int nco = r.bsax.copies;
   // grid coordinates (the FP64 sum reads the positions)

@@ -281,12 +281,6 @@ __global__ void k_ff_seg(const int32_t* __restrict__ so, const uint32_t* __restr
   recs[p] = r;
 }
 
-__device__ inline double ff_lane_d(double x, int k) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), k);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), k);
-  return __hiloint2double(hi, lo);
-}
-
 // Per segment, at one level: the 42 moment components about its cell's
 // centre (FP64, row k of comps) and |y| + |d| / 2 (srad).
 __global__ void k_ff_comps(const double* __restrict__ M, const double* __restrict__ D,

@@ -515,7 +515,6 @@ struct Run {
   int32_t* flag_a = nullptr;  // per point int flags
   int32_t* flag_b = nullptr;
   int32_t* scan_a = nullptr;
-  int32_t* scan_b = nullptr;
   uint64_t* wmask = nullptr;  // per-wave flag ballots
   int32_t* wpre = nullptr;    // per-wave exclusive prefix counts
 
@@ -536,10 +535,6 @@ struct Run {
   uint64_t* rc_best = nullptr;   // per point: smallest live key
   int32_t* rc_bidx = nullptr;    // per point: smallest live candidate of that key
   int32_t* used = nullptr;
-
-  // staging for host <-> device filament copies
-  double* stage = nullptr;  // 3 * ncap doubles
-  int32_t* stage_i = nullptr;
 
   int64_t step = 0;
   int parity = 0;
