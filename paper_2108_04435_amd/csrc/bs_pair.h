@@ -52,28 +52,31 @@ __device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
 
 // FP32 pair sum.  Per pair, with R1 = s_k - r (from the grid difference),
 // d = s_next(k) - s_k, q = |d|^2 and R2 = R1 + d:
-//   R1 x R2 = R1 x d,  |R2|^2 = |R1|^2 + (2 R1.d + q),
-//   (|R1| + |R2|)^2 - q = 2 (|R1||R2| + R1.R2),
-// so the closed form (R1 x R2) (|R1| + |R2|) / (|R1||R2| (|R1||R2| + R1.R2))
-// becomes (R1 x 2d) (i1 + i2) / (s^2 - q) with i_m = 1/|R_m| and
-// s = |R1| + |R2| = |R1|^2 i1 + |R2|^2 i2: 27 ordinary and 3 transcendental
-// instructions per pair (sources are staged as 2d and q).  Uniform grid: R1
-// stays in grid units and the result is rescaled once per target (v is
-// homogeneous of degree -1 in R).
+//   R1 x R2 = R1 x d,  R1.R2 = |R1|^2 + R1.d,  |R2|^2 = |R1|^2 + 2 R1.d + q,
+//   v = (R1 x R2) (i1 + i2) i1 i2 / (1 + (R1.R2) i1 i2),  i_m = 1/|R_m|,
+// the closed form (|R1| + |R2|) / (|R1||R2| (|R1||R2| + R1.R2)) rewritten with
+// inverse norms.  Uniform grid: R1 stays in grid units and the result is
+// rescaled once per target (v is homogeneous of degree -1 in R).
+//
+// The denominator is 1 + cos of the angle between R1 and R2, not the
+// (|R1| + |R2|)^2 - q that it is a multiple of and that takes two instructions
+// less (1.0e5 points: 6.64 against 6.88 ms): beside the segment's start that
+// difference cancels, and a q added into 2 R1.d before |R1|^2 is rounds at the
+// size of q.
+// Error of the factor beside the start of a segment of 0.7 to 0.95, rms, at 0.3,
+// 0.1 and 0.01 from it: 9.5e-8, 8.6e-8 and 8.4e-8 so, 1.9e-7, 4.1e-7 and 3.5e-6
+// with the difference.
 //
 // What bounds it: VALU issue.  Ordinary FP32 and integer instructions of two
 // waves issue together (1.45 to 1.73 wave instructions per CU and cycle with
 // 8 waves per SIMD; 0.89 when an operand is a scalar register, so the source
 // data must come from vector registers), a transcendental one takes two
-// cycles alone; the loop's mix takes 23.5 cycles per pair of wave and source
-// by those rates, 25.7 measured.  Against the form with
-// 1 + (R1.R2) i1 i2 in the denominator (29.5 ordinary): 1.45 -> 1.52 Tpairs/s
-// at 1.0e5 points, the error against FP64 6.0e-7 -> 5.5e-7.  Two or four
-// targets per lane measured 3% and 13% slower (fewer waves in flight).
+// cycles alone: 29 ordinary and 3 transcendental per pair.  Two or four targets
+// per lane measured 3% and 13% slower (fewer waves in flight).
 struct __align__(16) BsSrc {
   uint32_t x, y, z;  // grid coordinates of the segment's start
   float q;           // |d|^2
-  float dx, dy, dz;  // 2 d
+  float dx, dy, dz;  // d
   int32_t kn;        // index of the segment's end
 };
 
@@ -110,9 +113,9 @@ __device__ inline BsSrc bs_stage_f32(const BsPts& in, const uint32_t* __restrict
   g.y = x0[1];
   g.z = x0[2];
   g.q = ex * ex + ey * ey + ez * ez;
-  g.dx = 2.0f * ex;
-  g.dy = 2.0f * ey;
-  g.dz = 2.0f * ez;
+  g.dx = ex;
+  g.dy = ey;
+  g.dz = ez;
   g.kn = kn;
   return g;
 }
@@ -130,20 +133,20 @@ __device__ __forceinline__ void bs_pair_f32(const BsSrc& g, uint32_t xt, uint32_
     r1z *= iqz;
   }
   const float ex = g.dx, ey = g.dy, ez = g.dz;
-  const float t = fmaf(r1x, ex, fmaf(r1y, ey, fmaf(r1z, ez, g.q)));
+  const float t = fmaf(r1x, ex, fmaf(r1y, ey, r1z * ez));
   const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
-  const float n2 = n1 + t;
+  const float n2 = fmaf(2.0f, t, n1 + g.q);
   const float i1 = __builtin_amdgcn_rsqf(n1);
   const float i2 = __builtin_amdgcn_rsqf(n2);
-  const float sum = fmaf(n1, i1, n2 * i2);
-  float f = (i1 + i2) * __builtin_amdgcn_rcpf(fmaf(sum, sum, -g.q));
+  const float a = i1 * i2;
+  float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(fmaf(n1 + t, a, 1.0f));
   f = excluded ? 0.0f : f;
   ax = fmaf(f, fmaf(r1y, ez, -(r1z * ey)), ax);
   ay = fmaf(f, fmaf(r1z, ex, -(r1x * ez)), ay);
   az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
 }
 
-// FP64 pair sum (plain path), with the FP32 sum's q, R2 and s^2:
+// FP64 pair sum (plain path), with q and R2 as above and s = |R1| + |R2|:
 //   s^2 = |R1|^2 + |R2|^2 + 2 p,  p = |R1||R2| = sqrt(|R1|^2 |R2|^2),
 //   (|R1| + |R2|) / (p (p + R1.R2)) = 2 s / (p (s^2 - q))
 //                                   = 2 s^2 / sqrt(s^2 p^2 (s^2 - q)^2),

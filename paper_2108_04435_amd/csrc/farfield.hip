@@ -136,8 +136,8 @@ struct __align__(256) FfCell {
 
 struct __align__(32) FfSeg {
   uint32_t x[3];  // start on the grid
-  float d[3];     // twice the segment vector: wrapped grid difference (uniform) or lattice units
-  float dq;       // |d|^2 of the vector itself
+  float d[3];     // segment vector: wrapped grid difference (uniform) or lattice units
+  float dq;       // |d|^2
   int32_t idx;    // segment (point) index
 };
 
@@ -276,7 +276,6 @@ __global__ void k_ff_seg(const int32_t* __restrict__ so, const uint32_t* __restr
     r.d[a] = e;
   }
   r.dq = r.d[0] * r.d[0] + r.d[1] * r.d[1] + r.d[2] * r.d[2];
-  for (int a = 0; a < 3; ++a) r.d[a] *= 2.0f;
   r.idx = k;
   recs[p] = r;
 }
@@ -472,7 +471,7 @@ __device__ __forceinline__ void m2p_f32(float Rx, float Ry, float Rz, const M& m
 }
 
 // One (target, segment) pair of the exact straight-segment integral, in the
-// direct FP32 sum's form (bs_pair_f32): d is staged doubled.
+// direct FP32 sum's form (bs_pair_f32).
 template <bool kUniform>
 __device__ __forceinline__ void ff_pair(const FfSeg& g, uint32_t xt, uint32_t yt, uint32_t zt,
                                         const FfAxes& ax, float& vx, float& vy, float& vz,
