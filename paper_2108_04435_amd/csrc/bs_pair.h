@@ -146,15 +146,17 @@ __device__ __forceinline__ void bs_pair_f32(const BsSrc& g, uint32_t xt, uint32_
   az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
 }
 
-// FP64 pair sum (plain path), with q and R2 as above and s = |R1| + |R2|:
-//   s^2 = |R1|^2 + |R2|^2 + 2 p,  p = |R1||R2| = sqrt(|R1|^2 |R2|^2),
-//   (|R1| + |R2|) / (p (p + R1.R2)) = 2 s / (p (s^2 - q))
-//                                   = 2 s^2 / sqrt(s^2 p^2 (s^2 - q)^2),
+// FP64 pair sum (plain path), with q and R2 as above, s = |R1| + |R2| and
+// p = |R1||R2| = sqrt(|R1|^2 |R2|^2):
+//   w = 2 (p + R1.R2),  s^2 = w + q,
+//   (|R1| + |R2|) / (p (p + R1.R2)) = 2 s / (p w) = 2 s^2 / sqrt(s^2 p^2 w^2),
 // two inverse roots instead of two and a reciprocal.  Each is the hardware
 // approximation (relative error up to about 5e-8) refined by one Newton step
-// (which squares it), the first inside s^2, the second inside the factor:
+// (which squares it), the first inside w, the second inside the factor:
 // f = s^2 z (3 - arg z^2) with z ~ 1/sqrt(arg).  Sources are staged as 2 d;
-// the partial sums take the 1/2.
+// the partial sums take the 1/2.  (w as s^2 - q, as many instructions, cancels
+// beside the segment's start: the factor's error there, rms, at 0.001 from a
+// segment of 0.7 to 0.95: 5.6e-14, 1.6e-15 so.)
 //
 // The separation R1: on a closed axis the difference of the positions; on a
 // periodic axis (X_s - X_t) / q + (rho_s - rho_t), where the wrapped grid
@@ -166,7 +168,8 @@ __device__ __forceinline__ void bs_pair_f32(const BsSrc& g, uint32_t xt, uint32_
 // instruction and CU (no two waves issue together), an FP64 transcendental
 // four; 62.5 cycles per pair with three of them and four instructions per
 // axis of R1, 50 now (41 with two closed axes).  2e4 points, two closed axes:
-// 0.61 -> 0.76 Tpairs/s with the error against 64 bits 5.9e-15 -> 1.3e-15.
+// 0.59 -> 0.76 Tpairs/s; relative error against the sum in 80-bit arithmetic, L2
+// over 150 targets, 1.7e-15 -> 0.8e-15.
 struct __align__(16) BsSrcD {
   double rx, ry, rz;  // the segment's start: residual (periodic axis) or position (closed axis)
   double q;           // |d|^2
@@ -249,12 +252,13 @@ __device__ __forceinline__ void bs_pair_f64(const BsSrcD& g, BsTgtD& t, bool exc
   const double r1y = bs_sep<(kPer & 2) != 0>(g.y, t.y, g.ry, t.ry, gy);
   const double r1z = bs_sep<(kPer & 4) != 0>(g.z, t.z, g.rz, t.rz, gz);
   const double n1 = fma(r1x, r1x, fma(r1y, r1y, r1z * r1z));
-  const double n2 = n1 + fma(r1x, g.dx, fma(r1y, g.dy, fma(r1z, g.dz, g.q)));
+  const double v = n1 + fma(r1x, g.dx, fma(r1y, g.dy, r1z * g.dz));
+  const double n2 = v + g.q;
   const double n12 = n1 * n2;
   const double y = __builtin_amdgcn_rsq(n12);
   const double p = n12 * y;
-  const double s2 = fma(p, fma(-p, y, 1.0), fma(2.0, p, n1 + n2));
-  const double w = s2 - g.q;
+  const double w = fma(p, fma(-p, y, 3.0), n1 + v);
+  const double s2 = w + g.q;
   const double arg = (s2 * n12) * (w * w);
   const double z = __builtin_amdgcn_rsq(arg);
   double f = (s2 * z) * fma(-(arg * z), z, 3.0);

@@ -24,7 +24,9 @@ NEAR = 2.0 ** -12
 # dot products, roots, reciprocal and products add up to 32 roundings of 2^-24
 # at the most, where no step cancels; up to 80 pairs are added behind the near
 # one by the same wave, half a rounding each.
-TOL = {"f32": 72 * 2.0 ** -24}
+# FP64: the same count of 2^-53, up to 256 pairs by the same wave, and the two
+# inverse roots' Newton steps, 1.5 (6e-8)^2 each.
+TOL = {"f32": 72 * 2.0 ** -24, "f64": (32 + 128) * 2.0 ** -53 + 3 * 6e-8 ** 2}
 
 
 def _layout(pairs, dims, seed):
