@@ -368,7 +368,9 @@ int vlb_graph_destroy(vlb_graph* graph);
  *    segment adds nothing; not checked: invalid links give meaningless
  *    velocities, each entry is clamped into [0, n_pts) so no access leaves
  *    the arrays);
- *    v_dev: device output, n_pts x 3 doubles.
+ *    v_dev: device output, n_pts x 3 doubles; it may overlap xyz_dev and
+ *    next_dev, which it then overwrites (up to 1280 points are summed in one
+ *    launch otherwise, in two then).
  *  - dev_workspace: device scratch of at least vlb_biot_savart_workspace
  *    bytes, 256-byte aligned, owned by the caller; the call only enqueues
  *    work on hip_stream (NULL: the null stream) and returns: inputs,

@@ -504,6 +504,15 @@ size_t bs_solo_layout(int prec, long long n, char* base, BsSolo* b) {
   return (off + 255) / 256 * 256;
 }
 
+namespace {
+
+// Do the m bytes at a and the k bytes at b share any?
+bool overlap(const void* a, size_t m, const void* b, size_t k) {
+  return (uintptr_t)a < (uintptr_t)b + k && (uintptr_t)b < (uintptr_t)a + m;
+}
+
+}  // namespace
+
 hipError_t bs_solo(const BsAxes& ax, int prec, long long n, const double* xyz,
                    const int32_t* next, double kappa, double* v, const BsSolo& b,
                    hipStream_t stream) {
@@ -511,7 +520,10 @@ hipError_t bs_solo(const BsAxes& ax, int prec, long long n, const double* xyz,
   const int nb3 = (int)((3 * n + 255) / 256);
   const double s = kappa / (4.0 * M_PI);
   hipError_t e;
-  if (n <= kFewPoints) {
+  // (k_bs_few writes v while other blocks read the points: not for a caller
+  // whose output takes the place of its inputs)
+  const size_t bytes = 24 * (size_t)n;
+  if (n <= kFewPoints && !overlap(v, bytes, xyz, bytes) && !overlap(v, bytes, next, 4 * (size_t)n)) {
     using K = void (*)(BsPts, int, double, double*, BsAxes);
     static constexpr K f64[8] = {k_bs_few<false, 0>, k_bs_few<false, 1>, k_bs_few<false, 2>,
                                  k_bs_few<false, 3>, k_bs_few<false, 4>, k_bs_few<false, 5>,
