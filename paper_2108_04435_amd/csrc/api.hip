@@ -381,14 +381,18 @@ int report(vlb_run* h, int32_t flags) {
   return VLB_OK;
 }
 
-// The run's pinned memory for its points, from the first call that moves them.
-int pin_host(vlb_run* h) {
-  Run& r = h->r;
-  if (r.host) return VLB_OK;
-  r.host_bytes = host_io_need(r.ncap, 4, 0);
-  if (r.host_bytes > kHostIoBytes) r.host_bytes = kHostIoBytes;
-  HIP_OR_FAIL(h, hipHostMalloc((void**)&r.host, r.host_bytes));
-  return VLB_OK;
+// The run's pinned memory for its points, from the first call that moves them;
+// where none is to be had, host_bytes stays zero and the points go by copies.
+void pin_host(Run& r) {
+  if (r.host) return;
+  size_t bytes = host_io_need(r.ncap, 4, 0);
+  if (bytes > kHostIoBytes) bytes = kHostIoBytes;
+  if (hipHostMalloc((void**)&r.host, bytes) != hipSuccess) {
+    r.host = nullptr;
+    (void)hipGetLastError();
+    return;
+  }
+  r.host_bytes = bytes;
 }
 
 int latched(vlb_run* h) {
@@ -420,21 +424,30 @@ int copy_soa_to_host(vlb_run* h, const double* dev_soa, int n, double* host_aos)
 int fetch(vlb_run* h, const double* const* src, double* const* dst, int k, int32_t* next,
           int64_t cap, int64_t* n_pts) {
   Run& r = h->r;
-  int c = pin_host(h);
-  if (c != VLB_OK) return c;
-  HIP_OR_FAIL(h, fil_export(r, src, k, next != nullptr));
-  HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));
-  const int32_t* head = (const int32_t*)r.host;
-  const int n = head[0], flags = head[1];
+  pin_host(r);
+  int n = 0, flags = 0;
+  if (r.host) {
+    HIP_OR_FAIL(h, fil_export(r, src, k, next != nullptr));
+    HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));
+    const int32_t* head = (const int32_t*)r.host;
+    n = head[0];
+    flags = head[1];
+  } else {
+    int32_t cnt[8];
+    HIP_OR_FAIL(h, hipMemcpyAsync(cnt, r.cnt, sizeof(cnt), hipMemcpyDeviceToHost, r.stream));
+    HIP_OR_FAIL(h, hipStreamSynchronize(r.stream));
+    n = cnt[0];
+    flags = cnt[7];
+  }
   *n_pts = n;
   if (n > cap) return fail(h, VLB_ENOSPACE, "more points than cap");
   if (host_io_need(n, k, next ? 1 : 0) <= r.host_bytes) {
     const char* p = r.host + kHostIoHeader;
     for (int m = 0; m < k; ++m, p += 24 * (size_t)n) memcpy(dst[m], p, 24 * (size_t)n);
     if (next) memcpy(next, p, 4 * (size_t)n);
-  } else {
+  } else if (n > 0) {
     for (int m = 0; m < k; ++m) {
-      c = copy_soa_to_host(h, src[m], n, dst[m]);
+      const int c = copy_soa_to_host(h, src[m], n, dst[m]);
       if (c != VLB_OK) return c;
     }
     if (next) {
@@ -527,8 +540,7 @@ int vlb_seed_vortices(vlb_run* h, int64_t n_pts, const double* xyz, const int32_
   if (n_pts < 0 || n_pts > r.ncap) return fail(h, VLB_EINVAL, "n_pts must be in [0, n_cap]");
   if (n_pts > 0 && (!xyz || !next)) return fail(h, VLB_EINVAL, "xyz and next are required");
   const int n = (int)n_pts;
-  const int pc = pin_host(h);
-  if (pc != VLB_OK) return pc;
+  pin_host(r);
   // links: at most one predecessor besides itself per point; a point that
   // links to itself is the last point of an open line, one that no other
   // point links to is the first (it keeps itself as its predecessor)
@@ -582,11 +594,13 @@ int vlb_seed_vortices(vlb_run* h, int64_t n_pts, const double* xyz, const int32_
     if (n > 0) memcpy(links, next, n * sizeof(int32_t));
     HIP_OR_FAIL(h, fil_import(r, n));
   } else {
-    for (int a = 0; a < 3; ++a)
-      HIP_OR_FAIL(h, hipMemcpyAsync(r.pos + a * r.ncap, soa + (size_t)a * n, n * sizeof(double),
-                                    hipMemcpyHostToDevice, r.stream));
-    HIP_OR_FAIL(h, hipMemcpyAsync(r.nxt, next, n * sizeof(int32_t), hipMemcpyHostToDevice, r.stream));
-    HIP_OR_FAIL(h, hipMemcpyAsync(r.prv, prv, n * sizeof(int32_t), hipMemcpyHostToDevice, r.stream));
+    if (n > 0) {
+      for (int a = 0; a < 3; ++a)
+        HIP_OR_FAIL(h, hipMemcpyAsync(r.pos + a * r.ncap, soa + (size_t)a * n, n * sizeof(double),
+                                      hipMemcpyHostToDevice, r.stream));
+      HIP_OR_FAIL(h, hipMemcpyAsync(r.nxt, next, n * sizeof(int32_t), hipMemcpyHostToDevice, r.stream));
+      HIP_OR_FAIL(h, hipMemcpyAsync(r.prv, prv, n * sizeof(int32_t), hipMemcpyHostToDevice, r.stream));
+    }
     HIP_OR_FAIL(h, hipMemcpyAsync(r.cnt, &n, sizeof(int32_t), hipMemcpyHostToDevice, r.stream));
   }
   // grid coordinates of the seeded positions (FP32 sum of the first step)
