@@ -398,6 +398,13 @@ def measure(cfg, args, ref, graph):
         pairs = 20 * n_end * (n_end - 2)
         lbm_ms, lbm_n = run.time_kernel(1, reps=20) * 20, 20
         bs_basis = "20 launches back to back at the final state (HIP events)"
+    bs_name = "k_bs_f64" if prec == "f64" else "k_bs_f32"
+    if fused_stages(lat, cfg["vortex"], run.n_cap):
+        if direct:
+            bs_name = "k_stage"
+            bs_basis += ", each a whole stage (the sum and the points' update)"
+        else:
+            bs_basis += "; the steps of this run take their sums inside k_stage"
     bs_us = bs_ms * 1e3 / max(bs_n, 1)
     pairs_launch = pairs / max(bs_n, 1)
     lbm_us = lbm_ms * 1e3 / max(lbm_n, 1)
@@ -419,7 +426,7 @@ def measure(cfg, args, ref, graph):
         "bs_gpairs_s": round(pairs / max(bs_n, 1) * bs_n / wall / 1e9, 2) if direct else None,
         "points_start": int(n0),
         "points_end": int(n_end),
-        "bs_kernel": {"name": "k_bs_f64" if prec == "f64" else "k_bs_f32",
+        "bs_kernel": {"name": bs_name,
                       "avg_launch_us": round(bs_us, 2), "launches": int(bs_n),
                       "pairs_per_launch": int(pairs_launch),
                       "tpairs_s": round(pairs_launch / (bs_us * 1e-6) / 1e12, 4),
@@ -443,6 +450,19 @@ def point_capacity(n0, factor=1.4):
     growth (the tangle grows by 28% over 100 steps, counterflow by 26% over
     220); the capacity also sizes the Biot-Savart launch."""
     return int(n0 * factor) + 256
+
+
+def fused_stages(lat, vor, n_cap):
+    """Whether the library does each Runge-Kutta stage of such a run in one
+    launch (k_stage: few points, counted with their wall images), so that its
+    steps launch no pair sum by itself."""
+    if int(vor.get("ff_cell", 0)) > 0:
+        return False
+    copies = 3 ** sum(bool(w) for w in lat["walls"]) if vor.get("wall_images") else 1
+    f64 = lat["precision"] == "f64"
+    cells = lat["nx"] * lat["ny"] * lat["nz"]
+    lattice_s = cells * (57.0 * STORE_BYTES[lat["precision"]] + (48 if f64 else 24)) / 5e12
+    return n_cap * copies <= (1536 if lattice_s < 5e-5 else 1024)
 
 
 def lbm_kernel_name(lat):

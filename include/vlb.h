@@ -7,11 +7,14 @@
  * mutual-friction force (Sec. II.B).  All state lives in ONE caller-owned
  * block of device memory (the workspace); the library never allocates
  * device memory (a run owns up to 1 MiB of pinned host memory for the
- * transfers of its points, the process one page for flags).  Device work is ordered on ONE caller-owned HIP stream,
- * given at creation: inside vlb_step and a graph, the lattice part of a
- * step runs on a second, library-owned stream (default priority) forked
- * from the caller's stream at the start of the call and joined back to it
- * at the end, so to the caller every call is ordered on its stream.
+ * transfers of its points, the process one page for flags; both are done
+ * without where there is none to be had).  Device work is ordered on ONE
+ * caller-owned HIP stream, given at creation: inside vlb_step and a graph,
+ * the lattice part of a step runs on a second, library-owned stream (default
+ * priority) forked from the caller's stream at the start of the call and
+ * joined back to it at the end, so to the caller every call is ordered on
+ * its stream.  (Runs of few points on a small lattice keep the whole step on
+ * the caller's stream.)
  *
  * Conventions
  *  - Every function returns a vlb_status (0 = success, negative = error);
@@ -186,7 +189,8 @@ int vlb_seed_vortices(vlb_run* run, int64_t n_pts, const double* xyz_host,
  * spreading, one forced LBM update, remeshing / reconnection.  Returns
  * after enqueueing (asynchronous).  The filament stages stay on the run's
  * stream; the moments, the spreading and the LBM update go to the side
- * stream, with event dependencies where the two parts exchange data.      */
+ * stream, with event dependencies where the two parts exchange data (runs of
+ * few points on a small lattice: all on the run's stream).                 */
 int vlb_step(vlb_run* run, int64_t n_steps);
 
 /* Several runs advanced together (the served form): n_steps coupled steps
@@ -316,7 +320,14 @@ int vlb_get_step(vlb_run* run, int64_t* step);
 
 /* Kernel timing with HIP events recorded on the run's stream around every
  * launch of the named kernel class: 0 = Biot-Savart pair sum, 1 = LBM
- * collide+stream.  vlb_set_timing(run, e) clears the totals and enables
+ * collide+stream.  Runs of few points (n_cap times the source copies of the
+ * wall images up to 1024, up to 1536 on a lattice whose update and moments
+ * take less than about 50 us; no far field) do a whole Runge-Kutta stage in
+ * one launch, and class 0 is that launch: the sum, the interpolation, the
+ * local term and the stage's update.  A timed run of them on a small lattice
+ * also launches the spreading, the LBM update and the moments by themselves,
+ * which an untimed one does beside its stages, with the same bits: its steps
+ * take longer for it.  vlb_set_timing(run, e) clears the totals and enables
  * timing for e > 0 (e > 1 also pre-creates e events so that no event is
  * created while the timed steps are enqueued), disables it for e = 0; the
  * totals are read (after a sync) with vlb_get_timing.                      */
@@ -326,7 +337,9 @@ int vlb_get_timing(vlb_run* run, int32_t kernel_class, double* total_ms, int64_t
 /* Average duration of one launch of a kernel class (0 = Biot-Savart pair
  * sum at the current positions, 1 = LBM collide+stream) over reps >= 1
  * launches enqueued back to back between two HIP events on the run's
- * stream.  The Biot-Savart timing leaves the state unchanged; the LBM one
+ * stream.  The pair sum is the kernel of larger runs also for a run of few
+ * points, whose steps take their sums inside fused stages instead.  The
+ * Biot-Savart timing leaves the state unchanged; the LBM one
  * advances the normal fluid by reps updates (force field as last spread).
  * Synchronises the stream.                                                 */
 int vlb_time_kernel(vlb_run* run, int32_t kernel_class, int32_t reps, double* avg_ms);
