@@ -486,7 +486,11 @@ __global__ __launch_bounds__(kFinWaves * 64) void k_finalize(FinArgs A) {
 // whose order depends on timing, as a fixed function of the points: up to
 // kOrdered points are taken in ascending order; more are added as 64-bit
 // integers in units of 2^-(62 - log2 m) of the largest (exact sums, so the
-// order is irrelevant; a non-finite contribution makes the sum NaN).
+// order is irrelevant; a non-finite contribution makes the sum NaN).  Eight:
+// the line velocity of 5e3 points ten to a cell takes 118 us so, 112 with four
+// and 105 with sixteen, which takes 117 against 110 at twenty to a cell and 207
+// against 200 at a hundred; few cells hold more than three at the remeshed
+// spacing.
 constexpr int kOrdered = 8;
 
 struct BinPoint {
@@ -602,23 +606,34 @@ __device__ inline bool bin_around(const int e[3], int q, const SpreadGeom& sg, u
   return ok;
 }
 
-// Threads (point, stencil corner o).  Only the point at the head of its
-// bin's list acts: the node at that corner of the bin's stencil is written
-// by the occupied bin of smallest key among the (up to 8) bins whose
-// stencils contain it, which adds those bins' points in a fixed order.  The
-// nodes written are listed; the next moments kernel zeroes them.  kWave: one
-// wave per point, lane (o, q) adding bin q, the eight lanes of a node then
-// added in the order of q.
+// Only the point at the head of its bin's list acts: the node at a corner of
+// the bin's stencil is written by the occupied bin of smallest key among the
+// (up to 8) bins whose stencils contain it, which adds those bins' points in a
+// fixed order.  The nodes written are listed; the next moments kernel zeroes
+// them.  A wave takes a head's eight nodes together, lane (corner, bin) adding
+// one bin and the eight lanes of a node then added in the order of the bins, or
+// a lane per node walks the bins in turn, eight heads to a wave.
 //
 // What bounds it: latency (list heads, links, offsets: dependent loads).
 // With a stable sort of the points by bin in place of the lists, the
 // spreading was ten launches, 65 us of a served step (128x128x256, 2e3
 // points); this is one of 13.  A ring of 64 points, alone on the chip: 12 us
-// by threads walking the eight bins in turn, 4.8 by waves; beside the pair
+// by lanes walking the eight bins in turn, 4.8 by waves; beside the pair
 // sums of a large run the eight times more waves wait for their slots (9.4e3
-// points: 27 against 33 us), so waves are for small runs (kStagePoints) and,
-// up to kGatherWaves points, for a gather with nothing beside it (the line
-// velocity of 700 points 73 -> 65 us, of 9.4e3 196 -> 193, of 2e4 619 -> 621).
+// points: 27 against 33 us), so a wave has one point in small runs
+// (kStagePoints) and, up to kGatherWaves points, in a gather with nothing
+// beside it (the line velocity of 700 points 73 -> 65 us, of 9.4e3 196 -> 193,
+// of 2e4 619 -> 621), else eight.
+//
+// Of a wave's eight points, kManyHeads heads at the most are taken one after
+// another by the wave together: that many or fewer mean crowded bins, whose
+// lists a lane would walk eight times over.  Ten steps of about 5e3 points 0.02
+// apart (FP32) 3620 -> 1770 us, 0.05 apart 2010 -> 1290, 0.1 apart 1625 ->
+// 1540; always together, 2e3 points 0.95 apart take 955 against 938 and the
+// served steps 1.3% more.  With a line at two heads 0.05 apart takes 1515, at
+// six the served steps 0.4% more.
+constexpr int kManyHeads = 4;
+
 struct GatherArgs {
   const uint32_t* skeys;
   const int32_t* bins;
@@ -628,68 +643,100 @@ struct GatherArgs {
   int32_t* touched;
 };
 
-template <class FT, bool kWave>
-__device__ __forceinline__ void spread_gather(long long id, const GatherArgs& s,
-                                              int32_t* __restrict__ cnt, long long ncap,
-                                              const SpreadGeom& sg, long long cells,
-                                              FT* __restrict__ F) {
-  const int r = (int)(id >> (kWave ? 6 : 3));
-  const int o = (int)(id >> (kWave ? 3 : 0)) & 7;
-  const uint32_t me = r < ncap ? s.skeys[r] : 0u;  // (beyond the points: unused)
-  const int n = cnt[11];
-  if (id == 0) cnt[1] = 8 * n;
-  if (r >= n) return;
+// One node of the bin me that point r heads, written by this lane: corner o.
+template <class FT>
+__device__ __forceinline__ void gather_node(int r, int o, uint32_t me, int n, const GatherArgs& s,
+                                            long long ncap, const SpreadGeom& sg, long long cells,
+                                            FT* __restrict__ F) {
   int32_t* const mine = s.touched + 8LL * r + o;
   int e[3], lat[3];
-  double f[3] = {0.0, 0.0, 0.0};
-  if constexpr (kWave) {
-    const int q = threadIdx.x & 7;
-    if (s.bins[me] != r) {  // uniform over the wave
-      if (q == 0) *mine = -1;
-      return;
-    }
-    const bool inside = bin_corner(me, o, sg, e, lat);
+  if (!bin_corner(me, o, sg, e, lat)) {
+    *mine = -1;
+    return;
+  }
+  int head[8];
+  bool owner = true;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
     uint32_t key;
-    const int head = bin_around(e, q, sg, key) && inside ? s.bins[key] : -1;
-    const uint64_t smaller = __ballot(head >= 0 && key < me);
-    const bool owner = inside && ((smaller >> (8 * o)) & 0xffu) == 0;
-    if (owner && head >= 0) add_bin(head, n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
+    head[q] = bin_around(e, q, sg, key) ? s.bins[key] : -1;
+    owner = owner && !(head[q] >= 0 && key < me);
+  }
+  if (!owner) {
+    *mine = -1;
+    return;
+  }
+  double f[3] = {0.0, 0.0, 0.0};
+  for (int q = 0; q < 8; ++q)
+    if (head[q] >= 0) add_bin(head[q], n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
+  const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      double t = __shfl(f[a], 8 * o);
+  for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
+  *mine = (int32_t)node;
+}
+
+// All eight of them, written by the wave: lane (o, q) adds bin q.
+template <class FT>
+__device__ __forceinline__ void gather_nodes(int r, uint32_t me, int n, const GatherArgs& s,
+                                             long long ncap, const SpreadGeom& sg,
+                                             long long cells, FT* __restrict__ F) {
+  const int lane = threadIdx.x & 63, o = lane >> 3, q = lane & 7;
+  int e[3], lat[3];
+  const bool inside = bin_corner(me, o, sg, e, lat);
+  uint32_t key;
+  const int head = bin_around(e, q, sg, key) && inside ? s.bins[key] : -1;
+  const uint64_t smaller = __ballot(head >= 0 && key < me);
+  const bool owner = inside && ((smaller >> (8 * o)) & 0xffu) == 0;
+  double f[3] = {0.0, 0.0, 0.0};
+  if (owner && head >= 0) add_bin(head, n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
 #pragma unroll
-      for (int k = 1; k < 8; ++k) t += __shfl(f[a], 8 * o + k);
-      f[a] = t;
-    }
-    if (q != 0) return;
-    if (!owner) {
-      *mine = -1;
-      return;
-    }
-  } else {
-    if (s.bins[me] != r || !bin_corner(me, o, sg, e, lat)) {
-      *mine = -1;
-      return;
-    }
-    int head[8];
-    bool owner = true;
+  for (int a = 0; a < 3; ++a) {
+    double t = __shfl(f[a], 8 * o);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      uint32_t key;
-      head[q] = bin_around(e, q, sg, key) ? s.bins[key] : -1;
-      owner = owner && !(head[q] >= 0 && key < me);
-    }
-    if (!owner) {
-      *mine = -1;
-      return;
-    }
-    for (int q = 0; q < 8; ++q)
-      if (head[q] >= 0) add_bin(head[q], n, s.bnext, BinPoint{s.sfrac, s.gpt, ncap, q}, f);
+    for (int k = 1; k < 8; ++k) t += __shfl(f[a], 8 * o + k);
+    f[a] = t;
+  }
+  if (q != 0) return;
+  int32_t* const mine = s.touched + 8LL * r + o;
+  if (!owner) {
+    *mine = -1;
+    return;
   }
   const long long node = ((long long)lat[2] * sg.n[1] + lat[1]) * sg.n[0] + lat[0];
 #pragma unroll
   for (int a = 0; a < 3; ++a) F[a * cells + node] = (FT)f[a];
   *mine = (int32_t)node;
+}
+
+// kPts points per wave, lanes (point, corner) or the one point's.
+template <class FT, int kPts>
+__device__ __forceinline__ void spread_gather(long long id, const GatherArgs& s,
+                                              int32_t* __restrict__ cnt, long long ncap,
+                                              const SpreadGeom& sg, long long cells,
+                                              FT* __restrict__ F) {
+  const int lane = threadIdx.x & 63;
+  const int r0 = (int)(id >> 6) * kPts;
+  const int r = r0 + (kPts > 1 ? lane >> 3 : 0);
+  const uint32_t me = r < ncap ? s.skeys[r] : 0u;  // (beyond the points: unused)
+  const int n = cnt[11];
+  if (id == 0) cnt[1] = 8 * n;
+  if (r0 >= n) return;
+  const bool heads = r < n && s.bins[me] == r;
+  if (r < n && !heads && (kPts > 1 || lane < 8)) s.touched[8LL * r + (lane & 7)] = -1;
+  if constexpr (kPts == 1) {
+    if (heads) gather_nodes<FT>(r, me, n, s, ncap, sg, cells, F);  // (uniform)
+  } else {
+    uint64_t todo = __ballot(heads && (lane & 7) == 0);
+    if (__popcll(todo) > kManyHeads) {
+      if (heads) gather_node<FT>(r, lane & 7, me, n, s, ncap, sg, cells, F);
+      return;
+    }
+    for (; todo; todo &= todo - 1) {
+      const int p = __ffsll((unsigned long long)todo) - 1;
+      gather_nodes<FT>(r0 + (p >> 3), (uint32_t)__builtin_amdgcn_readlane((int)me, p), n, s, ncap,
+                       sg, cells, F);
+    }
+  }
 }
 
 // The work a stage carries, in blocks of kSideThreads (two items of 256
@@ -700,7 +747,7 @@ __device__ __forceinline__ void side_work(const SideWork& w, const FinArgs& A,
   const Geom& g = A.g;
   const int tid = threadIdx.x;
   if (w.kind == SideWork::kGather) {
-    spread_gather<UT, true>((long long)block * kSideThreads + tid, ga, A.cnt, A.ncap, A.sg, g.cells,
+    spread_gather<UT, 1>((long long)block * kSideThreads + tid, ga, A.cnt, A.ncap, A.sg, g.cells,
                             (UT*)w.force);
   } else if (w.kind == SideWork::kUpdate) {
     const int c = block * kSideThreads + tid;
@@ -801,11 +848,11 @@ __global__ __launch_bounds__(512) void k_stage(FinArgs A, BsPts in, BsAxes bx, S
   fin_combine(A, lane, j, vs, sh);
 }
 
-template <class FT, bool kWave>
+template <class FT, int kPts>
 __global__ __launch_bounds__(256) void k_spread_gather(GatherArgs s, int32_t* __restrict__ cnt,
                                                        long long ncap, SpreadGeom sg,
                                                        long long cells, FT* __restrict__ F) {
-  spread_gather<FT, kWave>((long long)blockIdx.x * blockDim.x + threadIdx.x, s, cnt, ncap, sg,
+  spread_gather<FT, kPts>((long long)blockIdx.x * blockDim.x + threadIdx.x, s, cnt, ncap, sg,
                            cells, F);
 }
 
@@ -1008,7 +1055,7 @@ constexpr long long kGatherWaves = 16384;
 
 template <class FT>
 void launch_gather(Run& r, bool waves) {
-  auto kern = waves ? k_spread_gather<FT, true> : k_spread_gather<FT, false>;
+  auto kern = waves ? k_spread_gather<FT, 1> : k_spread_gather<FT, 8>;
   hipLaunchKernelGGL(kern, dim3(nblocks((waves ? 64 : 8) * r.ncap, 256)), dim3(256), 0, r.stream,
                      gather_args(r), r.cnt, r.ncap, spread_geom(r), r.cells, (FT*)r.force);
 }
