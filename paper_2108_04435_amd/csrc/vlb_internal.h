@@ -575,7 +575,11 @@ constexpr long long kTopoPoints = 2048;
 // streams costs 5 to 9 us, twice a step, and the carried update gives up
 // block order and occupancy.  Ten steps of 500 points in 96^3 FP32 (45 us):
 // 1170 us on two streams, 1097 on one; 400 points in 128x128x64 (53 us): 1115
-// against 1205; 200 points in 80^3 FP64 (52 us): 946 against 892.
+// against 1205; 200 points in 80^3 FP64 (52 us): 946 against 892.  FP16, 56
+// points: 96^3 (24 us) 695 against 620, 128x128x110 (50 us) 827 against 824,
+// and rows of 256, whose update then goes node by node, 256x84x84 (50 us) 884
+// against 820 (102 points: 850 with the update launched by itself, four nodes to
+// a lane, against 824).
 constexpr double kShortLattice = 5e-5;
 
 // error flag bits in cnt[7]
