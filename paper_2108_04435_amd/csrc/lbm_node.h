@@ -276,9 +276,14 @@ __device__ inline void node_rho_u(const S* M, const Geom& g, int parity, int x, 
 }
 
 // The same for one AA parity, with 32-bit slot offsets where the population
-// array spans less than 4 GiB (I32) and non-temporal loads of the slots that
-// no other node's line holds (NT: lattices above the last-level cache;
-// 128x128x256 FP32, even parity 76 -> 63 us).
+// array spans less than 4 GiB (I32) and non-temporal loads of all slots (NT:
+// lattices above the last-level cache; 128x128x256 FP32, even parity 76 -> 63
+// us).  In odd parity a wave shares the lines of the x-shifted slots with its
+// neighbour, but the hint pays there too: a line velocity of 16 points, mostly
+// its moments, in 256^3 FP32 342 -> 310 us, 328 with the hint on the other
+// slots alone; FP16 221, 208, 216; 128x128x512 FP32 195, 181, 187; only
+// 128x128x256 by itself is faster that way (117, 113, 101), and its steps are
+// level (2716 against 2720 us).
 template <class S, int P, bool I32, bool NT>
 __device__ inline void node_u(const S* __restrict__ M, const Geom& g, int x, int y, int z,
                               double u[3]) {
