@@ -542,10 +542,23 @@ hipError_t copy_state(Run& r, const void* in, void* out) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// The GPU whose memory p points into, or -1.
+int gpu_of(const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  return at.type == hipMemoryTypeDevice ? at.device : -1;
+}
+
 }  // namespace
 
+// By a kernel where it may read the input, which is memory of the run's GPU;
+// the runtime's copy takes memory of any kind.
 hipError_t lbm_write_state(Run& r, const void* in) {
-  if (aligned16(in)) return copy_state(r, in, r.pops);
+  const int gpu = gpu_of(in);
+  if (aligned16(in) && gpu >= 0 && gpu == gpu_of(r.pops)) return copy_state(r, in, r.pops);
   return hipMemcpyAsync(r.pops, in, 19 * (size_t)r.cells * elt_size(r.prec),
                         hipMemcpyDeviceToDevice, r.stream);
 }
