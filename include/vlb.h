@@ -6,9 +6,10 @@
  * plus a set of closed vortex filaments (Sec. II.A), coupled through the
  * mutual-friction force (Sec. II.B).  All state lives in ONE caller-owned
  * block of device memory (the workspace); the library never allocates
- * device memory (a run owns up to 1 MiB of pinned host memory for the
- * transfers of its points, the process one page for flags; both are done
- * without where there is none to be had).  Device work is ordered on ONE
+ * device memory (the process keeps up to 16 MiB of pinned host memory, of
+ * which a run takes up to 1 MiB for the transfers of its points and gives it
+ * back in vlb_destroy, and a page more for flags; both are done without
+ * where there is none to be had).  Device work is ordered on ONE
  * caller-owned HIP stream, given at creation: inside vlb_step and a graph,
  * the lattice part of a step runs on a second, library-owned stream (default
  * priority) forked from the caller's stream at the start of the call and

@@ -138,6 +138,69 @@ void give_flag_slot(int32_t* s) {
   p.used &= ~(1ull << (((char*)s - p.page) / 64));
 }
 
+// Pinned blocks of the process for the runs' points, taken at the first call of
+// a run that moves points and given back at its end: freeing pinned memory
+// waits for all work on the GPU, other runs' too (destroying a run beside one
+// with 0.18 s of steps queued took as long, 0.1 ms so).  At most kHostBlocks of
+// them and kHostPoolBytes, kept until the process ends; a run that gets none,
+// or one too small, moves its points by copies.
+constexpr int kHostBlocks = 64;
+constexpr size_t kHostPoolBytes = 16 << 20;
+
+struct HostPool {
+  std::mutex m;
+  struct Block {
+    char* p;
+    size_t bytes;
+    bool used;
+  } b[kHostBlocks] = {};
+  int n = 0;
+  size_t total = 0;
+};
+
+HostPool& host_pool() {
+  static HostPool p;
+  return p;
+}
+
+// A block of `need` (<= kHostIoBytes) bytes, the smallest free one that holds
+// them or a new one; else the largest free one; else null.
+char* take_host(size_t need, size_t* bytes) {
+  HostPool& p = host_pool();
+  std::lock_guard<std::mutex> lock(p.m);
+  int fit = -1, most = -1;
+  for (int i = 0; i < p.n; ++i) {
+    if (p.b[i].used) continue;
+    if (p.b[i].bytes >= need && (fit < 0 || p.b[i].bytes < p.b[fit].bytes)) fit = i;
+    if (most < 0 || p.b[i].bytes > p.b[most].bytes) most = i;
+  }
+  size_t size = 4096;
+  while (size < need) size *= 2;
+  if (fit < 0 && p.n < kHostBlocks && p.total + size <= kHostPoolBytes) {
+    void* q = nullptr;
+    if (hipHostMalloc(&q, size, hipHostMallocPortable) == hipSuccess) {
+      p.b[p.n] = HostPool::Block{(char*)q, size, false};
+      p.total += size;
+      fit = p.n++;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  const int i = fit >= 0 ? fit : most;
+  if (i < 0) return nullptr;
+  p.b[i].used = true;
+  *bytes = p.b[i].bytes;
+  return p.b[i].p;
+}
+
+void give_host(char* q) {
+  if (!q) return;
+  HostPool& p = host_pool();
+  std::lock_guard<std::mutex> lock(p.m);
+  for (int i = 0; i < p.n; ++i)
+    if (p.b[i].p == q) p.b[i].used = false;
+}
+
 void release_streams(Run& r) {
   give_flag_slot(r.flag);
   r.flag = nullptr;
@@ -151,10 +214,9 @@ void release_streams(Run& r) {
     (void)hipStreamDestroy(r.side);
     r.side = nullptr;
   }
-  if (r.host) {
-    (void)hipHostFree(r.host);
-    r.host = nullptr;
-  }
+  give_host(r.host);
+  r.host = nullptr;
+  r.host_bytes = 0;
 }
 
 // Carve the workspace (base == nullptr: only measure).
@@ -381,18 +443,13 @@ int report(vlb_run* h, int32_t flags) {
   return VLB_OK;
 }
 
-// The run's pinned memory for its points, from the first call that moves them;
-// where none is to be had, host_bytes stays zero and the points go by copies.
+// The run's pinned memory for its points, from the first call that moves them
+// (none: host_bytes stays zero).
 void pin_host(Run& r) {
   if (r.host) return;
-  size_t bytes = host_io_need(r.ncap, 4, 0);
-  if (bytes > kHostIoBytes) bytes = kHostIoBytes;
-  if (hipHostMalloc((void**)&r.host, bytes) != hipSuccess) {
-    r.host = nullptr;
-    (void)hipGetLastError();
-    return;
-  }
-  r.host_bytes = bytes;
+  size_t need = host_io_need(r.ncap, 4, 0);
+  if (need > kHostIoBytes) need = kHostIoBytes;
+  r.host = take_host(need, &r.host_bytes);
 }
 
 int latched(vlb_run* h) {

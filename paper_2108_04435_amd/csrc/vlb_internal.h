@@ -446,7 +446,7 @@ struct Run {
   hipStream_t stream = nullptr;  // the caller's stream: every call's work joins it
   hipStream_t side = nullptr;    // library stream for the lattice part of a step
   hipEvent_t ev_fork = nullptr, ev_mom = nullptr, ev_fin1 = nullptr, ev_join = nullptr;
-  char* host = nullptr;  // host_bytes of pinned memory for transfers, one at a time
+  char* host = nullptr;  // host_bytes of the process's pinned memory for transfers, one at a time
   size_t host_bytes = 0;
   int32_t* flag = nullptr;  // pinned slot for the latched flags (or null)
   int device = 0;
