@@ -71,8 +71,10 @@ __device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
 // waves issue together (1.45 to 1.73 wave instructions per CU and cycle with
 // 8 waves per SIMD; 0.89 when an operand is a scalar register, so the source
 // data must come from vector registers), a transcendental one takes two
-// cycles alone: 29 ordinary and 3 transcendental per pair.  Two or four targets
-// per lane measured 3% and 13% slower (fewer waves in flight).
+// cycles alone: 29 ordinary and 3 transcendental per pair, 24.5 cycles per pair
+// of wave and source by those rates, 26.4 measured (1.46 to 1.48 Tpairs/s at
+// 1.0e5 points).  Two or four targets per lane measured 3% and 13% slower (fewer
+// waves in flight).
 struct __align__(16) BsSrc {
   uint32_t x, y, z;  // grid coordinates of the segment's start
   float q;           // |d|^2

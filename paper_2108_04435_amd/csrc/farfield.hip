@@ -717,7 +717,7 @@ __device__ __forceinline__ bool ff_take(const FfCell* __restrict__ cells, int c,
 // same cells, so that their records are read from the scalar cache.  Five
 // waves per SIMD (96 VGPRs, 15 spilled) beat four by 4% and six by 5%.  1e5
 // points of a 256^3 tangle, cells of 16 and 32, theta 0.25: 2.55 ms before
-// (each lane deciding each cell, a block's four waves on four cells), 1.81 ms.
+// (each lane deciding each cell, a block's four waves on four cells), 1.84 ms.
 template <bool kUniform, int kLevels>
 __global__ __launch_bounds__(256, 5) void k_ff_eval(
     const FfCell* __restrict__ cells0, const FfCell* __restrict__ cells1,
