@@ -135,17 +135,21 @@ __device__ __forceinline__ void bs_pair_f32(const BsSrc& g, uint32_t xt, uint32_
     r1z *= iqz;
   }
   const float ex = g.dx, ey = g.dy, ez = g.dz;
-  const float t = fmaf(r1x, ex, fmaf(r1y, ey, r1z * ez));
-  const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
+  const float t = r1x * ex + r1y * ey + r1z * ez;
+  const float n1 = r1x * r1x + r1y * r1y + r1z * r1z;
   const float n2 = fmaf(2.0f, t, n1 + g.q);
   const float i1 = __builtin_amdgcn_rsqf(n1);
   const float i2 = __builtin_amdgcn_rsqf(n2);
+  const float crx = r1y * ez - r1z * ey;
+  const float cry = r1z * ex - r1x * ez;
+  const float crz = r1x * ey - r1y * ex;
   const float a = i1 * i2;
-  float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(fmaf(n1 + t, a, 1.0f));
+  const float den = fmaf(n1 + t, a, 1.0f);
+  float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(den);
   f = excluded ? 0.0f : f;
-  ax = fmaf(f, fmaf(r1y, ez, -(r1z * ey)), ax);
-  ay = fmaf(f, fmaf(r1z, ex, -(r1x * ez)), ay);
-  az = fmaf(f, fmaf(r1x, ey, -(r1y * ex)), az);
+  ax = fmaf(f, crx, ax);
+  ay = fmaf(f, cry, ay);
+  az = fmaf(f, crz, az);
 }
 
 // FP64 pair sum (plain path), with q and R2 as above, s = |R1| + |R2| and
