@@ -41,7 +41,7 @@
 //    blockIdx.y one of S cell chunks (cells y modulo S of the coarsest level);
 //    the chunk partials are added in FP64 in chunk order (bitwise
 //    reproducible).
-#include "bs_pair.h"
+#include "vlb_internal.h"
 
 #include <cmath>
 
@@ -471,13 +471,36 @@ __device__ __forceinline__ void m2p_f32(float Rx, float Ry, float Rz, const M& m
 }
 
 // One (target, segment) pair of the exact straight-segment integral, in the
-// direct FP32 sum's form (bs_pair_f32).
+// direct FP32 sum's form (bs_pair_f32) with the products nested from the last
+// axis.
 template <bool kUniform>
 __device__ __forceinline__ void ff_pair(const FfSeg& g, uint32_t xt, uint32_t yt, uint32_t zt,
                                         const FfAxes& ax, float& vx, float& vy, float& vz,
                                         bool zero) {
-  const BsSrc s{g.x[0], g.x[1], g.x[2], g.dq, g.d[0], g.d[1], g.d[2], 0};
-  bs_pair_f32<kUniform>(s, xt, yt, zt, ax.iqf[0], ax.iqf[1], ax.iqf[2], zero, vx, vy, vz);
+  float r1x = (float)(int)(g.x[0] - xt);
+  float r1y = (float)(int)(g.x[1] - yt);
+  float r1z = (float)(int)(g.x[2] - zt);
+  if (!kUniform) {
+    r1x *= ax.iqf[0];
+    r1y *= ax.iqf[1];
+    r1z *= ax.iqf[2];
+  }
+  const float ex = g.d[0], ey = g.d[1], ez = g.d[2];
+  const float t = fmaf(r1x, ex, fmaf(r1y, ey, r1z * ez));
+  const float n1 = fmaf(r1x, r1x, fmaf(r1y, r1y, r1z * r1z));
+  const float n2 = fmaf(2.0f, t, n1 + g.dq);
+  const float i1 = __builtin_amdgcn_rsqf(n1);
+  const float i2 = __builtin_amdgcn_rsqf(n2);
+  const float crx = fmaf(r1y, ez, -r1z * ey);
+  const float cry = fmaf(r1z, ex, -r1x * ez);
+  const float crz = fmaf(r1x, ey, -r1y * ex);
+  const float a = i1 * i2;
+  const float den = fmaf(n1 + t, a, 1.0f);
+  float f = (i1 + i2) * a * __builtin_amdgcn_rcpf(den);
+  f = zero ? 0.0f : f;
+  vx = fmaf(f, crx, vx);
+  vy = fmaf(f, cry, vy);
+  vz = fmaf(f, crz, vz);
 }
 
 // Per-lane decision for one cell (FP64 and integers, no contraction).
