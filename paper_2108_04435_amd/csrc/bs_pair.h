@@ -60,7 +60,7 @@ __device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
 //
 // The denominator is 1 + cos of the angle between R1 and R2, not the
 // (|R1| + |R2|)^2 - q that it is a multiple of and that takes two instructions
-// less (1.0e5 points: 6.64 against 6.88 ms): beside the segment's start that
+// less (1.0e5 points: 6.48 against 6.86 ms): beside the segment's start that
 // difference cancels, and a q added into 2 R1.d before |R1|^2 is rounds at the
 // size of q.
 // Error of the factor beside the start of a segment of 0.7 to 0.95, rms, at 0.3,
@@ -72,8 +72,8 @@ __device__ inline uint32_t bs_grid_f32(double y, const BsAxes& ax, int a) {
 // 8 waves per SIMD; 0.89 when an operand is a scalar register, so the source
 // data must come from vector registers), a transcendental one takes two
 // cycles alone: 29 ordinary and 3 transcendental per pair, 24.5 cycles per pair
-// of wave and source by those rates, 26.4 measured (1.46 to 1.48 Tpairs/s at
-// 1.0e5 points).  Two or four targets per lane measured 3% and 13% slower (fewer
+// of wave and source by those rates, 26.7 measured (1.46 Tpairs/s at 1.0e5
+// points).  Two or four targets per lane measured 3% and 13% slower (fewer
 // waves in flight).
 struct __align__(16) BsSrc {
   uint32_t x, y, z;  // grid coordinates of the segment's start
